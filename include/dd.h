@@ -192,7 +192,9 @@ dd_status dd_simulate_batch(const dd_graph *g, const dd_sched *sched, const dd_v
  * dd_simulate_batch_vs -- dd_simulate_batch with an explicit launch shape.
  *   variants_per_wg  variants that each workgroup owns for the whole
  *                    schedule: 0 = chosen by the library (as
- *                    dd_simulate_batch), or 1, 2, 4, 8, 16;
+ *                    dd_simulate_batch), or 1, 2, 4, 8, 16 (1 runs the kernel
+ *                    made for one variant per workgroup where its arithmetic
+ *                    holds the times, see below);
  *                    -1, -2, -4, -8 = the few-variant path with that many
  *                    variants per workgroup: one launch per step, each step
  *                    cut into chunks of 256 positions taken by separate
@@ -201,7 +203,11 @@ dd_status dd_simulate_batch(const dd_graph *g, const dd_sched *sched, const dd_v
  *   dd_simulate_batch itself takes the few-variant path when the variants
  *   are fewer than 1,024, the schedule has at most 512 steps, and its steps
  *   hold more than about 4.4 rounds of 512 positions on average (where that
- *   path measured faster).
+ *   path measured faster).  Otherwise up to 768 variants (2,048 when steps
+ *   hold at most 32 positions on average) run one per workgroup, in a kernel
+ *   that holds times as integers in doubles (scaled times below 2.0e15 ns in
+ *   sum, durations and gaps below 2^32) and needs V * 256 KiB of scratch at
+ *   most; the strip kernel serves every other call.
  * The results do not depend on the shape (Algorithm 1 per variant, Sec. 4.1);
  * only the number of workgroups and the kernel instance do.  For tuning, and
  * for checking every compiled instance.

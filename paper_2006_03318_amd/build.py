@@ -24,7 +24,8 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
 # Per-file flags.  The simulation kernels hold integer times in doubles on
 # their uniform path and never make a NaN: with IEEE mode off a double max
 # is one instruction (IEEE mode would quiet each operand first).
-FILE_FLAGS = {"k_simulate.hip": ["-fno-honor-nans", "-Xarch_device", "-mno-amdgpu-ieee"]}
+_F64_TIMES = ["-fno-honor-nans", "-Xarch_device", "-mno-amdgpu-ieee"]
+FILE_FLAGS = {"k_simulate.hip": _F64_TIMES, "k_solo.hip": _F64_TIMES}
 
 
 def _compile(src: str) -> str:

@@ -84,6 +84,8 @@ void free_sched_arrays(dd_sched *x) {
     dd::dfree(x->gat_ptr, s); dd::dfree(x->gat_src, s); dd::dfree(x->gat_pos, s);
     dd::dfree(x->gat_cls, s); dd::dfree(x->gat_gap, s); dd::dfree(x->node_step, s);
     dd::dfree(x->gat_spos, s); dd::dfree(x->rec, s);
+    dd::dfree(x->bat, s); dd::dfree(x->nbat, s);
+    dd::dfree(x->so_rec, s);
 }
 
 }  // namespace
@@ -756,7 +758,7 @@ dd_status dd_simulate_plan(const dd_sched *sched, const dd_variants *var,
     g_err[0] = 0;
     if (!sched || !var || !variants_per_wg) return fail(DD_EINVAL, "NULL argument");
     const int sw = dd::split_width(sched, var);
-    *variants_per_wg = sw > 0 ? -sw : dd::strip_width(var->V);
+    *variants_per_wg = sw > 0 ? -sw : dd::solo_chosen(sched, var) ? 1 : dd::strip_width(var->V);
     return DD_OK;
 }
 

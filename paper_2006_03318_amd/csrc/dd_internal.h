@@ -68,6 +68,28 @@ constexpr int64_t kSplitMaxSteps = 512;
 // LDS during the simulation instead of gathering the previous task of a run.
 constexpr int kMaxCarryThreads = 64;
 
+// Batches of the one-variant-per-workgroup kernel (k_solo.hip): steps of at
+// most kSoloNarrow positions are grouped by the kSoloGroup-aligned span they
+// start in (so a group has fewer than kSoloPos positions), wider ones cut
+// into parts of kSoloPos positions.
+constexpr int kSoloNarrow = 128;
+constexpr int kSoloGroup = 384;
+constexpr int kSoloPos = 512;
+static_assert(kSoloGroup + kSoloNarrow <= kSoloPos, "a group of narrow steps is one batch");
+constexpr int kSoloCls = 2048;    // scale entries it keeps in LDS (16 bytes each)
+constexpr int kSoloRing = 32768;  // releases of recent positions it keeps per variant at most
+
+// A schedule position as that kernel reads it (durations and gaps below
+// 2^32).
+struct alignas(16) SoloRec {
+    uint32_t dur, gap;
+    int32_t node, g0_spos;    // task; schedule position of its first parent (-1: none)
+    uint32_t cls;             // as Rec::cls
+    uint32_t flags;           // bits 0..7 as Rec::flags; kSoG1; 16..31 parents beyond two (saturating)
+    int32_t g1_spos, pad;
+};
+constexpr uint32_t kSoG1 = 1u << 8;   // a second parent on another thread
+
 // Streams other than its own on which a handle's device memory was used.
 // A handle's blocks go back to the cache of the stream it was created on;
 // before that, its own stream waits for the last use on each other stream,
@@ -150,6 +172,9 @@ struct dd_sched {
     int32_t *gat_spos = nullptr;  // schedule position of the source task
     int32_t *node_step = nullptr; // [n]
     dd::Rec *rec = nullptr;       // [n] per position
+    int4 *bat = nullptr;          // batches of k_solo.hip
+    int32_t *nbat = nullptr;      // [1] how many
+    dd::SoloRec *so_rec = nullptr;    // [n] its records
     bool thread_carry = false;    // thread predecessors come from per-thread carries
     std::vector<int32_t> h_step_ptr;  // host copy of step_ptr (schedules of at most
                                       // kSplitMaxSteps steps; empty otherwise)
@@ -259,11 +284,13 @@ hipError_t launch_split(const dd_graph *g, const dd_sched *sch, const dd_variant
                         int64_t *finish, int64_t *start, int64_t *makespan, int vg, hipStream_t s);
 
 // variants per workgroup of the one-workgroup-per-strip kernel when the
-// caller leaves it to the library: enough workgroups to cover the 256
-// compute units, then the widest rows
+// caller leaves it to the library: the fewest with which all workgroups run
+// at once (one per compute unit).  A workgroup of twice the variants takes
+// 1.0 to 1.3 times as long, a second pass twice as long: 5 transformer
+// iterations, 1,000 variants: 1,634 us four to a workgroup, 3,247 two.
 inline int strip_width(int64_t V) {
     int vs = 1;
-    while (vs < 16 && V / (vs * 2) >= 256) vs *= 2;
+    while (vs < 16 && (V + vs - 1) / vs > 256) vs *= 2;
     return vs;
 }
 
@@ -277,6 +304,34 @@ hipError_t launch_simulate(const dd_graph *g, const dd_sched *sch, const dd_vari
 hipError_t simulate_noalloc(const dd_graph *g, const dd_sched *sch, const dd_variants *var,
                             int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s,
                             size_t *need, size_t *limit);
+
+// one variant per workgroup (k_solo.hip): the most batches a schedule can
+// have, the batch list of a schedule, and the launch (hipErrorOutOfMemory
+// when its scratch, mostly V * kSoloRing * 8 bytes, cannot be had)
+int64_t solo_batch_max(int64_t n, int64_t nsteps);
+hipError_t launch_batches(dd_sched *sch, hipStream_t s);
+hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants *var,
+                       int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s);
+
+// whether that kernel takes these handles: times and durations fit its
+// arithmetic (the schedule then has its records), the scales fit LDS
+inline bool solo_fits(const dd_sched *sch, const dd_variants *var) {
+    return sch->so_rec && sch->n > 0 && var->f64_ok && var->n_cls <= kSoloCls;
+}
+
+// Whether dd_simulate_batch takes it.  Two of its workgroups run on a compute
+// unit, so up to 512 variants run at once, at 0.35 to 0.4 us per narrow step
+// and 1.1 to 1.8 us per 512 positions of a wide one; the strip kernel costs
+// 1.5 us per step and 1.7 us per 512 positions, but packs up to 16 variants
+// into a workgroup.  Measured, us (solo / strip): 5 transformer iterations
+// (163,840 tasks in 256 steps) 565 / 1,073 at 256 variants, 819 / 1,402 at
+// 333, 916 / 1,390 at 512, 1,401 / 1,461 at 768, 2,108 / 1,490 at 1,024;
+// the offloading CNN (1,932 tasks in 173 steps) 70 / 284 at 256, 148 / 308
+// at 1,024.  Beyond 2,048 variants its passes add up on any schedule.
+inline bool solo_chosen(const dd_sched *sch, const dd_variants *var) {
+    if (!solo_fits(sch, var) || var->V > 2048) return false;
+    return var->V <= 768 || (int64_t)sch->n <= 32 * sch->n_steps;
+}
 
 // runtime breakdown (k_breakdown.hip): scratch [2 * V + n_cls + 1] int64,
 // order [n] int32, out [V][4]

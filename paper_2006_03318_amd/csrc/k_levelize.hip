@@ -770,7 +770,8 @@ __global__ __launch_bounds__(kBS) void k_records(
     const int64_t *__restrict__ pos_dur, const int64_t *__restrict__ pos_gap,
     const uint16_t *__restrict__ pos_cls, const int64_t *__restrict__ gptr,
     const int32_t *__restrict__ gsrc, const int32_t *__restrict__ gspos,
-    const uint8_t *__restrict__ gcls, const int64_t *__restrict__ ggap, Rec *__restrict__ rec) {
+    const uint8_t *__restrict__ gcls, const int64_t *__restrict__ ggap, Rec *__restrict__ rec,
+    SoloRec *__restrict__ so_rec) {
     const int64_t q = (int64_t)blockIdx.x * kBS + threadIdx.x;
     if (q >= n) return;
     Rec r;
@@ -796,6 +797,11 @@ __global__ __launch_bounds__(kBS) void k_records(
     r.flags = (uint32_t)(pos_flags[q] & 1) | (last ? 2u : 0u) |
               ((uint32_t)(t < kMaxCarryThreads ? t : 0) << 2) | ((uint32_t)extra << 8);
     rec[q] = r;
+    if (!so_rec) return;                     // durations or gaps past 32 bits
+    if (extra > 0xFFFF) extra = 0xFFFF;
+    so_rec[q] = SoloRec{(uint32_t)r.dur, (uint32_t)r.gap, r.node, r.g0_src >= 0 ? r.g0_spos : -1, r.cls,
+                        (r.flags & 0xffu) | (r.g1_src >= 0 ? kSoG1 : 0u) | ((uint32_t)extra << 16),
+                        r.g1_spos, 0};
 }
 
 __global__ __launch_bounds__(kBS) void k_step_width(int64_t nsteps, const int32_t *__restrict__ step_ptr,
@@ -1150,6 +1156,9 @@ dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sch
             CK(dalloc_n(&pos_of, N1, s));
             CK(dalloc_n(&sch->gat_spos, (size_t)Gmax + 1, s));
             CK(dalloc_n(&sch->rec, N1, s));
+            // (one more than n: idle lanes read it)
+            if (g->dmax < (int64_t(1) << 32) && g->gmax < (int64_t(1) << 32))
+                CK(dalloc_n(&sch->so_rec, N1, s));
             if (n > 0) {
                 k_inverse<<<gN, kBS, 0, s>>>(n, sch->pos_node, pos_of);
                 if (Gmax > 0)
@@ -1157,13 +1166,17 @@ dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sch
                                                                      pos_of, sch->gat_spos);
                 k_records<<<gN, kBS, 0, s>>>(n, g->thread_id, sch->pos_node, sch->pos_flags, sch->pos_dur,
                                              sch->pos_gap, sch->pos_cls, sch->gat_ptr, sch->gat_src,
-                                             sch->gat_spos, sch->gat_cls, sch->gat_gap, sch->rec);
+                                             sch->gat_spos, sch->gat_cls, sch->gat_gap, sch->rec,
+                                             sch->so_rec);
                 CK(hipGetLastError());
             }
             dfree(pos_of, s);
         }
         k_step_width<<<grid_for(sch->n_steps, kBS), kBS, 0, s>>>(sch->n_steps, sch->step_ptr, wmax);
         CK(hipGetLastError());
+        CK(dalloc_n(&sch->bat, (size_t)solo_batch_max(n, sch->n_steps), s));
+        CK(dalloc_n(&sch->nbat, 1, s));
+        CK(launch_batches(sch, s));
         int64_t h_G = 0;
         const bool keep_steps = sch->n_steps <= kSplitMaxSteps;
         if (keep_steps) sch->h_step_ptr.resize((size_t)sch->n_steps + 1);

@@ -34,6 +34,7 @@
 
 #include "dd_common.h"
 #include "dd_internal.h"
+#include "dd_time.h"
 
 #include <stdlib.h>
 
@@ -50,16 +51,6 @@ __device__ __forceinline__ int64_t scaled(int64_t d, const ScaleEntry &se) {
     const uint64_t hi = __umul64hi(a, se.magic) >> se.shift;
     const uint64_t lo = a >> se.shift;
     return (int64_t)(se.magic ? hi : lo);
-}
-
-__device__ __forceinline__ int64_t max64(int64_t a, int64_t b) { return a > b ? a : b; }
-
-// 64-bit value from its two 32-bit halves, as one register pair (left
-// visible as shift-or, the compiler adds the halves to a sum one at a time)
-__device__ __forceinline__ int64_t join64(int lo, int hi) {
-    int64_t r = (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-    asm("" : "+v"(r));
-    return r;
 }
 
 struct PipeArgs {
@@ -117,10 +108,6 @@ struct Dyn {
     int64_t g0gap[K];             // gap of that source
 };
 
-__device__ __forceinline__ bool cls_on(uint64_t eon, uint8_t c) {
-    return c == 255 || ((eon >> c) & 1ull);
-}
-
 // LDS scale entry: p (bits 0..31), shift (32..39), bit 40 = multiply-high
 // needed (q not a power of two; the 64-bit magic is then read from the table)
 __device__ __forceinline__ int64_t scaled8(int64_t d, uint64_t e, const ScaleEntry *tab,
@@ -129,98 +116,6 @@ __device__ __forceinline__ int64_t scaled8(int64_t d, uint64_t e, const ScaleEnt
     const uint32_t sh = (uint32_t)(e >> 32) & 0xff;
     if (e & (1ull << 40)) return (int64_t)(__umul64hi(a, tab[idx].magic) >> sh);
     return (int64_t)(a >> sh);
-}
-
-// Run heads without flags.  A range of positions maps the release entering
-// it to c -> max(c + a, b), with b >= a.  A range that holds the first task of
-// a run ignores c; it is written with a = kHead + (its weights after the
-// head), so c + a < 0 <= b for every c that occurs: every simulated time is
-// below 2^62 (the graph and transform checks reject anything larger), and c
-// plus the weights of later positions is itself such a time.  Composing keeps
-// a >= kHead, so no sum overflows.
-constexpr int64_t kHead = -(int64_t(1) << 62);
-
-// Time arithmetic.  Tm<false>: plain int64.  Tm<true>: every value is an
-// integer held in a double, which the hardware adds and compares in one
-// full-rate instruction each (int64 takes two to three).  Times are biased
-// by 2^52: the double of time t (0 <= t < 2^52) has the bit pattern
-// 0x4330000000000000 + t, so moving a time between HBM (int64) and a
-// register is one operation on its high word, and the bit patterns of
-// nonnegative doubles order as integers do.  Weights (durations, gaps and
-// their sums) stay unbiased, and a range holding a run head carries -inf,
-// which any sum keeps (c + -inf = -inf loses to every b in a max).  All of
-// it is exact while every simulated time stays below 2^51 and every
-// duration times the scale numerator below 2^53 (checked on the host; the
-// int64 form serves every other launch).  Values travel as int64 bit
-// patterns either way.
-template <bool FP> struct Tm;
-template <> struct Tm<false> {
-    static constexpr int64_t zero = 0;          // time 0
-    static constexpr int64_t head = kHead;      // weight sum of a range holding a run head
-    __device__ static __forceinline__ int64_t add(int64_t x, int64_t y) { return x + y; }
-    __device__ static __forceinline__ int64_t sub(int64_t x, int64_t y) { return x - y; }
-    __device__ static __forceinline__ int64_t mx(int64_t x, int64_t y) { return max64(x, y); }
-    __device__ static __forceinline__ int64_t from_time(int64_t t) { return t; }
-    __device__ static __forceinline__ int64_t to_time(int64_t x) { return x; }
-    __device__ static __forceinline__ int64_t w32(uint32_t w) { return (int64_t)w; }
-    __device__ static __forceinline__ double d(int64_t x) { return __longlong_as_double(x); }
-    __device__ static __forceinline__ int64_t i(double x) { return __double_as_longlong(x); }
-};
-template <> struct Tm<true> {
-    static constexpr int64_t zero = 0x4330000000000000ll;                    // 2^52
-    static constexpr int64_t head = (int64_t)0xFFF0000000000000ull;          // -inf
-    __device__ static __forceinline__ double d(int64_t x) { return __longlong_as_double(x); }
-    __device__ static __forceinline__ int64_t i(double x) { return __double_as_longlong(x); }
-    __device__ static __forceinline__ int64_t add(int64_t x, int64_t y) { return i(d(x) + d(y)); }
-    __device__ static __forceinline__ int64_t sub(int64_t x, int64_t y) { return i(d(x) - d(y)); }
-    __device__ static __forceinline__ int64_t mx(int64_t x, int64_t y) {
-        return i(__builtin_fmax(d(x), d(y)));
-    }
-    __device__ static __forceinline__ int64_t from_time(int64_t t) { return t | zero; }
-    __device__ static __forceinline__ int64_t to_time(int64_t x) { return x ^ zero; }
-    __device__ static __forceinline__ int64_t w32(uint32_t w) { return i((double)w); }
-};
-
-// (la, lb) then (a, b)
-template <bool FP = false>
-__device__ __forceinline__ void compose(int64_t la, int64_t lb, int64_t &a, int64_t &b) {
-    b = Tm<FP>::mx(Tm<FP>::add(lb, a), b);
-    if (FP) a = Tm<FP>::add(la, a);
-    else a = a < 0 ? a : la + a;
-}
-
-// one Kogge-Stone step of the max-plus scan across the wave, the left
-// operand taken with a DPP lane shift (lanes without one see the identity
-// (0, 0), as b >= a; in the double form the bits 0 are 0.0, below every
-// biased time).  Row shifts write every lane (bound control: 0 where the
-// source lies outside the row), so no lane needs its old value.
-template <int CTRL, int RMASK, bool FP = false>
-__device__ __forceinline__ void scan_step(int64_t &a, int64_t &b) {
-    constexpr bool BC = RMASK == 0xf;
-    const int alo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)a, CTRL, RMASK, 0xf, BC);
-    const int ahi = __builtin_amdgcn_update_dpp(0, (int)((uint64_t)a >> 32), CTRL, RMASK, 0xf, BC);
-    const int blo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, RMASK, 0xf, BC);
-    const int bhi = __builtin_amdgcn_update_dpp(0, (int)((uint64_t)b >> 32), CTRL, RMASK, 0xf, BC);
-    const int64_t la = join64(alo, ahi);
-    const int64_t lb = join64(blo, bhi);
-    compose<FP>(la, lb, a, b);
-}
-
-__device__ __forceinline__ int64_t readlane64(int64_t x, int l) {
-    const int lo = __builtin_amdgcn_readlane((int)(uint32_t)x, l);
-    const int hi = __builtin_amdgcn_readlane((int)((uint64_t)x >> 32), l);
-    return join64(lo, hi);
-}
-
-// inclusive scan over the 64 lanes of a wave
-template <bool FP = false>
-__device__ __forceinline__ void wave_scan(int64_t &a, int64_t &b) {
-    scan_step<0x111, 0xf, FP>(a, b);   // row_shr:1
-    scan_step<0x112, 0xf, FP>(a, b);   // row_shr:2
-    scan_step<0x114, 0xf, FP>(a, b);   // row_shr:4
-    scan_step<0x118, 0xf, FP>(a, b);   // row_shr:8
-    scan_step<0x142, 0xa, FP>(a, b);   // row_bcast:15 into rows 1 and 3
-    scan_step<0x143, 0xc, FP>(a, b);   // row_bcast:31 into rows 2 and 3
 }
 
 // Lane layout: slot = tid / LPS handles K consecutive positions; the LPS
@@ -1366,6 +1261,12 @@ unsigned char *g_scratch_ptr[kMaxDevices];
 hipError_t launch_simulate(const dd_graph *g, const dd_sched *sch, const dd_variants *var,
                            int64_t *finish, int64_t *start, int64_t *makespan, int vs_hint,
                            hipStream_t s) {
+    // one variant per workgroup: k_solo.hip where it takes the handles
+    if (vs_hint == 1 ? solo_fits(sch, var) : vs_hint == 0 && solo_chosen(sch, var)) {
+        const hipError_t e = launch_solo(g, sch, var, finish, start, makespan, s);
+        if (e != hipErrorOutOfMemory) return e;
+        (void)hipGetLastError();             // the strip kernel needs less scratch
+    }
     return with_shape(var, vs_hint, [&](auto lps, auto vpl, auto k) {
         return launch_pipe<decltype(lps)::value, decltype(vpl)::value, decltype(k)::value>(
             g, sch, var, finish, start, makespan, s, nullptr);
