@@ -66,6 +66,19 @@ hipError_t copy_in(T **dst, const T *src, size_t count, hipStream_t s) {
     return hipMemsetAsync(*dst, 0, count * sizeof(T), s);
 }
 
+// memory that kernels on the current device may read in place: a copy queued
+// on the call's stream would read it no earlier
+bool on_device(const void *p) {
+    if (!p) return false;
+    hipPointerAttribute_t at;
+    int dev = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();             // host memory the runtime does not know
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && at.device == dev;
+}
+
 void free_graph_arrays(dd_graph *g) {
     hipStream_t s = g->stream;
     dd::join_uses(g->uses, s);
@@ -539,6 +552,7 @@ dd_status dd_apply_transforms(const dd_graph *g, int32_t n_variants, int32_t n_c
         // the bound; 2^51 = 2.25e15 (a margin for rounding again)
         x->f64_ok = bound < 2.0e15L &&
                     (__int128)g->dmax * (__int128)pmax < ((__int128)1 << 53);
+        x->quot_ok = x->f64_ok && (__int128)g->dmax * (__int128)pmax < ((__int128)1 << 50);
     }
     TRY(hipStreamSynchronize(s), "sync");
     TRY(dd::note_use(g->uses, g->stream, s), "record stream use");
@@ -626,19 +640,14 @@ dd_status dd_runtime_breakdown(const dd_graph *g, const dd_variants *var, const 
     hipStream_t s = (hipStream_t)stream;
     dd_status st = DD_OK;
     uint8_t *d_role = nullptr;
-    int64_t *scratch = nullptr;
-    int32_t *order = nullptr;
-    TRY(copy_in(&d_role, role, (size_t)g->n, s), "copy role");
-    TRY(dd::dalloc_n(&scratch, 2 * (size_t)var->V + (size_t)var->n_cls + 2, s), "alloc");
-    TRY(dd::dalloc_n(&order, 2 * (size_t)g->n + 1, s), "alloc");
-    TRY(dd::launch_breakdown(g, var, d_role, d_finish, d_makespan, scratch, order, d_out, s),
+    if (!on_device(role)) TRY(copy_in(&d_role, role, (size_t)g->n, s), "copy role");
+    TRY(dd::launch_breakdown(g, var, d_role ? d_role : role, d_finish, d_makespan, nullptr, nullptr,
+                             d_out, s),
         "breakdown");
     TRY(dd::note_use(g->uses, g->stream, s), "record stream use");
     TRY(dd::note_use(var->uses, var->stream, s), "record stream use");
 fail_out:
     dd::dfree(d_role, s);
-    dd::dfree(scratch, s);
-    dd::dfree(order, s);
     return st;
 }
 

@@ -189,6 +189,7 @@ struct dd_variants {
     bool any_magic = false;       // some scale has q not a power of two
     bool f64_ok = false;          // every simulated time below 2^51 and every d * p below
                                   // 2^53: the double form of the time arithmetic is exact
+    bool quot_ok = false;         // f64_ok and every d * p below 2^50: so are quotients by any q
     hipStream_t stream = nullptr;
     dd::ScaleEntry *table = nullptr;  // [n_cls][V]
     uint32_t *rm_bits = nullptr;      // [n][W]
@@ -316,7 +317,7 @@ hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants
 // whether that kernel takes these handles: times and durations fit its
 // arithmetic (the schedule then has its records), the scales fit LDS
 inline bool solo_fits(const dd_sched *sch, const dd_variants *var) {
-    return sch->so_rec && sch->n > 0 && var->f64_ok && var->n_cls <= kSoloCls;
+    return sch->so_rec && sch->n > 0 && var->quot_ok && var->n_cls <= kSoloCls;
 }
 
 // Whether dd_simulate_batch takes it.  Two of its workgroups run on a compute
@@ -333,8 +334,8 @@ inline bool solo_chosen(const dd_sched *sch, const dd_variants *var) {
     return var->V <= 768 || (int64_t)sch->n <= 32 * sch->n_steps;
 }
 
-// runtime breakdown (k_breakdown.hip): scratch [2 * V + n_cls + 1] int64,
-// order [n] int32, out [V][4]
+// runtime breakdown (k_breakdown.hip): out [V][4]; scratch and order are not
+// used (nullptr)
 hipError_t launch_breakdown(const dd_graph *g, const dd_variants *var, const uint8_t *role_dev,
                             const int64_t *finish, const int64_t *makespan, int64_t *scratch,
                             int32_t *order, int64_t *out, hipStream_t s);

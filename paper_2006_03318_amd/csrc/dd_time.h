@@ -4,6 +4,7 @@
 #pragma once
 
 #include "dd_common.h"
+#include "dd_internal.h"
 
 namespace dd {
 namespace {
@@ -71,6 +72,21 @@ template <> struct Tm<true> {
     __device__ static __forceinline__ int64_t to_time(int64_t x) { return x ^ zero; }
     __device__ static __forceinline__ int64_t w32(uint32_t w) { return i((double)w); }
 };
+
+// floor(d * p / q) in doubles, for d * p < 2^50 (dd_variants::quot_ok).  With
+// x = d * p + 1/2 (exact), x / q lies at least 1/(2q) from any integer; the
+// rounded reciprocal and product are off by at most x / q * 2^-52 < 1/(2q),
+// so the floor is the quotient.
+__device__ __forceinline__ double scale_f64(double d, double p, double iq) {
+    return __builtin_floor(__builtin_fma(d, p, 0.5) * iq);
+}
+// 1 / q of a scale entry.  magic = floor(2^(64 + shift) / q) + 1 with
+// q < 2^31, so q is 2^(64 + shift) / magic to the nearest integer; without a
+// magic number q = 2^shift.
+__device__ __forceinline__ double inv_quotient(const ScaleEntry &e) {
+    if (!e.magic) return __builtin_ldexp(1.0, -(int)e.shift);
+    return 1.0 / __builtin_rint(__builtin_ldexp(1.0, 64 + (int)e.shift) / (double)e.magic);
+}
 
 // (la, lb) then (a, b)
 template <bool FP = false>

@@ -11,245 +11,219 @@
 // A call's start is its finish minus its scaled duration, and a release is
 // finish + g', so the finish array alone carries the schedule.
 //
-// The tasks with a role are first ordered by task class (a counting sort),
-// so along a workgroup's chunk the class, and with it each lane's scale
-// entry, changes rarely: a lane reloads its entry only when the (wave-
-// uniform) class changes.  Each workgroup owns 1,024 variants and a chunk of
-// the ordered tasks, so a task's fields are
-// wave-uniform and the per-variant reads (removal words, finish values of
-// waiting calls) are contiguous across the wave; a thread serves four
-// consecutive variants.  Partial sums go to a per-variant accumulator with
-// one atomic per variant and thread.
+// One pass (k_bd_sum) over (chunk of tasks) x (128 variants) per workgroup,
+// after a small launch that writes what does not depend on the sums
+// (k_bd_init).  Bound: the instructions per (kernel, variant) pair, about
+// nine: the workgroup first sorts its chunk's kernels by class in LDS, so a
+// lane's scale stays in registers along a run of one class; a wave takes 64
+// kernels at a time, lane j loading kernel j's removal words, and then walks
+// them with the duration and the removal masks in scalar registers, two
+// variants per lane.  Where every duration times its p stays below 2^50 the
+// scaled duration is floor((d * p + 0.5) * (1 / q)) in doubles (dd_time.h),
+// three instructions for any q.  Sums join the output with one atomic per
+// variant and workgroup.
 
 #include "dd_common.h"
 #include "dd_internal.h"
+#include "dd_time.h"
 
 namespace dd {
 namespace {
 
 constexpr int kBT = 256;          // threads per workgroup
-constexpr int kVL = 4;            // variants per thread (divides 32)
-constexpr int64_t kChunk = 512;   // ordered tasks per workgroup
-constexpr int kBatch = 8;         // tasks whose loads are issued together
+constexpr int kBW = kBT / 64;
+constexpr int kBV = 128;          // variants per workgroup, two per lane
+constexpr int kMaxChunk = 2048;   // tasks per workgroup at most
+constexpr int kKeys = 1024;       // buckets of the sort (classes, modulo this)
 
-
-__device__ __forceinline__ bool has_role(uint8_t r) { return r == 1u || r == 2u; }
-
-// Counting sort of the tasks with a role by class.  With few classes each
-// block first counts (and ranks) its own tasks in LDS, so one global atomic
-// per (block, class) replaces one per task: thousands of tasks share a
-// handful of counters.
-constexpr int kLdsCls = 2048;     // classes counted in LDS at most
-
-__global__ __launch_bounds__(kBT) void k_bd_count(int64_t n, int32_t n_cls,
-                                                  const uint8_t *__restrict__ role,
-                                                  const uint16_t *__restrict__ cls,
-                                                  unsigned long long *__restrict__ hist) {
-    __shared__ uint32_t h[kLdsCls];
-    const int64_t u = (int64_t)blockIdx.x * kBT + threadIdx.x;
-    const bool lds = n_cls <= kLdsCls;
-    const bool has = u < n && has_role(role[u]);
-    const uint32_t c = has ? cls[u] : 0u;
-    if (lds) {
-        for (int i = threadIdx.x; i < n_cls; i += kBT) h[i] = 0;
-        __syncthreads();
-        if (has) atomicAdd(&h[c], 1u);
-        __syncthreads();
-        for (int i = threadIdx.x; i < n_cls; i += kBT)
-            if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
-    } else if (has) {
-        atomicAdd(&hist[c], 1ull);
-    }
-}
-
-__global__ __launch_bounds__(kBT) void k_bd_scatter(int64_t n, int32_t n_cls,
-                                                    const uint8_t *__restrict__ role,
-                                                    const uint16_t *__restrict__ cls,
-                                                    unsigned long long *__restrict__ cursor,
-                                                    int32_t *__restrict__ order) {
-    __shared__ uint32_t h[kLdsCls];
-    __shared__ unsigned long long base[kLdsCls];
-    const int64_t u = (int64_t)blockIdx.x * kBT + threadIdx.x;
-    const bool has = u < n && has_role(role[u]);
-    const uint32_t c = has ? cls[u] : 0u;
-    if (n_cls <= kLdsCls) {
-        for (int i = threadIdx.x; i < n_cls; i += kBT) h[i] = 0;
-        __syncthreads();
-        const uint32_t rank = has ? atomicAdd(&h[c], 1u) : 0u;   // rank inside the block
-        __syncthreads();
-        for (int i = threadIdx.x; i < n_cls; i += kBT)
-            if (h[i]) base[i] = atomicAdd(&cursor[i], (unsigned long long)h[i]);
-        __syncthreads();
-        if (has) order[base[c] + rank] = (int32_t)u;
-    } else if (has) {
-        order[atomicAdd(&cursor[c], 1ull)] = (int32_t)u;
-    }
-}
-
-struct BdArgs {
-    int32_t V, W, nvb, nch;
-    const ScaleEntry *table;
-    const uint32_t *rm;
-    const int64_t *finish;
-    unsigned long long *acc;      // [2][V]: kernel time, blocked time
-};
-
-// scaled duration: MAGIC when some q of the launch is not a power of two
-// (else a shift suffices), D32 when every duration is below 2^32 (one 32x32
-// multiply); the multiply-high of the general form is four quarter-rate
-// multiplies, which bound the kernel when taken for every (task, variant)
-template <bool MAGIC, bool D32>
-__device__ __forceinline__ int64_t bd_scale(int64_t d, const ScaleEntry &se) {
-    const uint64_t a = D32 ? (uint64_t)(uint32_t)d * (uint64_t)se.p : (uint64_t)d * (uint64_t)se.p;
-    if (MAGIC && se.magic) return (int64_t)(__umul64hi(a, se.magic) >> se.shift);
-    return (int64_t)(a >> se.shift);
-}
-
-// per-task arrays are kernel arguments marked restrict, so the compiler
-// reads them with scalar loads (every lane of the workgroup needs the same
-// task's fields)
-template <bool MAGIC, bool D32>
-__global__ __launch_bounds__(kBT) void k_bd_accum(const int64_t *__restrict__ m_ptr,
-                                                  const int32_t *__restrict__ order,
-                                                  const uint8_t *__restrict__ role,
-                                                  const int64_t *__restrict__ dur,
-                                                  const int64_t *__restrict__ gap,
-                                                  const uint16_t *__restrict__ cls,
-                                                  const int32_t *__restrict__ tprev, BdArgs a) {
-    // XCD-aware: the workgroups of one XCD (b % 8) take consecutive
-    // (variant block, chunk) pairs
-    const int64_t total = (int64_t)a.nvb * a.nch;
-    int64_t b = blockIdx.x;
-    if ((total & 7) == 0) b = (int64_t)(blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
-    const int vb = (int)(b / a.nch), ch = (int)(b % a.nch);
-    // kVL consecutive variants per lane: one removal word serves them all,
-    // and the per-task work (order, class, duration, role) is shared
-    const int64_t V = a.V, W = a.W;
-    const int64_t vf = ((int64_t)vb * kBT + threadIdx.x) * kVL;
-    bool ok[kVL];
-    int64_t vc[kVL];
-#pragma unroll
-    for (int t = 0; t < kVL; t++) {
-        ok[t] = vf + t < V;
-        vc[t] = ok[t] ? vf + t : 0;
-    }
-    const int64_t vw = vc[0] >> 5;
-    const uint32_t vsh = (uint32_t)(vc[0] & 31);     // kVL divides 32: one word
-    const int64_t m = *m_ptr;
-    const int64_t i0 = (int64_t)ch * kChunk;
-    const int64_t i1 = i0 + kChunk < m ? i0 + kChunk : m;
-    int64_t ksum[kVL], wsum[kVL];
-    ScaleEntry se[kVL];
-#pragma unroll
-    for (int t = 0; t < kVL; t++) {
-        ksum[t] = 0;
-        wsum[t] = 0;
-        se[t] = ScaleEntry{0ull, 1u, 0u};
-    }
-    int32_t ccls = -1;
-    for (int64_t ib = i0; ib < i1; ib += kBatch) {
-        // a batch of tasks: every load of a stage issued before any is used
-        // (slots past the chunk's end read task 0 and are skipped)
-        int64_t uu[kBatch];
-        {   // one vector load brings the batch's task ids; lane j's goes to all
-            const int j = (int)(threadIdx.x & (kBatch - 1));
-            const int32_t mine = order[ib + j < i1 ? ib + j : i1 - 1];
-#pragma unroll
-            for (int t = 0; t < kBatch; t++) uu[t] = __builtin_amdgcn_readlane(mine, t);
-        }
-        int32_t cc[kBatch];
-        int64_t dd[kBatch];
-        uint32_t rr[kBatch], rw[kBatch];
-#pragma unroll
-        for (int j = 0; j < kBatch; j++) {
-            cc[j] = cls[uu[j]];
-            dd[j] = dur[uu[j]];
-            rr[j] = role[uu[j]];
-            rw[j] = a.rm[uu[j] * W + vw] >> vsh;
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; j++) {
-            if (ib + j >= i1) break;               // past the chunk's end (wave-uniform)
-            if (cc[j] != ccls) {                   // wave-uniform: the class changed
-#pragma unroll
-                for (int t = 0; t < kVL; t++) se[t] = a.table[(int64_t)cc[j] * V + vc[t]];
-                ccls = cc[j];
-            }
-            if (rr[j] != 1u) continue;             // waiting calls: k_bd_wait
-#pragma unroll
-            for (int t = 0; t < kVL; t++)
-                ksum[t] += ((rw[j] >> t) & 1u) ? 0 : bd_scale<MAGIC, D32>(dd[j], se[t]);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < kVL; t++)
-        if (ok[t] && ksum[t]) atomicAdd(&a.acc[vc[t]], (unsigned long long)ksum[t]);
-}
-
-// The waiting calls (a handful per iteration) as a list: one atomic per
-// wave that holds any.
-__global__ __launch_bounds__(kBT) void k_bd_wait_list(int64_t n, const uint8_t *__restrict__ role,
-                                                      unsigned long long *__restrict__ wcount,
-                                                      int32_t *__restrict__ wlist) {
-    const int64_t u = (int64_t)blockIdx.x * kBT + threadIdx.x;
-    const bool w = u < n && role[u] == 2u;
-    const uint64_t bal = __ballot(w);
-    if (!bal) return;
-    const int lane = threadIdx.x & 63;
-    const int first = __ffsll((unsigned long long)bal) - 1;
-    unsigned long long base = 0;
-    if (lane == first) base = atomicAdd(wcount, (unsigned long long)__popcll(bal));
-    base = (unsigned long long)__shfl((long long)base, first, 64);
-    if (w) wlist[base + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)u;
-}
-
-// GPU-only time of every waiting call u and variant v: its start minus the
-// moment its thread reached it.  Blocks along x cover the variants (one per
-// thread, so every load and atomic is contiguous across the wave); blocks
-// along y take the calls in turn.  Contributions are nonnegative integers,
-// so the order of the atomics does not change the sums.
-template <bool MAGIC, bool D32>
-__global__ __launch_bounds__(kBT) void k_bd_wait(const unsigned long long *__restrict__ wcount,
-                                                 const int32_t *__restrict__ wlist,
-                                                 const int64_t *__restrict__ dur,
-                                                 const int64_t *__restrict__ gap,
-                                                 const uint16_t *__restrict__ cls,
-                                                 const int32_t *__restrict__ tprev, BdArgs a) {
-    const int64_t V = a.V, W = a.W;
-    const int64_t v = (int64_t)blockIdx.x * kBT + threadIdx.x;
-    if (v >= V) return;
-    const int64_t cnt = (int64_t)*wcount;
-    const int64_t vw = v >> 5;
-    const uint32_t vb = (uint32_t)(v & 31);
-    int64_t sum = 0;
-    for (int64_t i = blockIdx.y; i < cnt; i += gridDim.y) {
-        const int64_t u = wlist[i];
-        const bool rmu = (a.rm[u * W + vw] >> vb) & 1u;
-        const int64_t dp = rmu ? 0 : bd_scale<MAGIC, D32>(dur[u], a.table[(int64_t)cls[u] * V + v]);
-        const int64_t start = a.finish[u * V + v] - dp;
-        const int32_t p = tprev[u];
-        int64_t reached = 0;
-        if (p >= 0) {
-            const bool rmp = (a.rm[(int64_t)p * W + vw] >> vb) & 1u;
-            reached = a.finish[(int64_t)p * V + v] + (rmp ? 0 : gap[p]);
-        }
-        sum += start - reached;
-    }
-    if (sum) atomicAdd(&a.acc[V + v], (unsigned long long)sum);
-}
-
-__global__ __launch_bounds__(kBT) void k_bd_final(int32_t V, const int64_t *__restrict__ makespan,
-                                                  const unsigned long long *__restrict__ acc,
-                                                  int64_t *__restrict__ out) {
+__global__ __launch_bounds__(kBT) void k_bd_init(int32_t V, const int64_t *__restrict__ makespan,
+                                                 int64_t *__restrict__ out) {
     const int64_t v = (int64_t)blockIdx.x * kBT + threadIdx.x;
     if (v >= V) return;
     const int64_t ms = makespan[v];
-    const int64_t cpu_only = ms - (int64_t)acc[v];
-    const int64_t gpu_only = (int64_t)acc[V + v];
     out[v * 4 + 0] = ms;
-    out[v * 4 + 1] = cpu_only;
-    out[v * 4 + 2] = gpu_only;
-    out[v * 4 + 3] = ms - cpu_only - gpu_only;
+    out[v * 4 + 1] = ms;
+    out[v * 4 + 2] = 0;
+    out[v * 4 + 3] = 0;
+}
+
+struct BdArgs {
+    int64_t n;
+    int32_t V, W, chunk, bx;      // bx: workgroups per chunk (128 variants each)
+    const uint8_t *role;
+    const int64_t *dur, *gap;
+    const uint16_t *cls;
+    const int32_t *tprev;
+    const ScaleEntry *table;
+    const uint32_t *rm;
+    const int64_t *finish;
+    unsigned long long *out;      // [V][4]
+};
+
+// a kernel of the chunk
+struct alignas(16) BdEnt {
+    int64_t dur;
+    int32_t u;
+    uint32_t cls;
+};
+
+// scaled duration and its sum, in doubles or (general form) in integers
+template <bool F64> struct BdScale;
+template <> struct BdScale<true> {
+    double p, iq;
+    typedef double T;
+    __device__ __forceinline__ void set(const ScaleEntry &e) {
+        p = (double)e.p;
+        iq = inv_quotient(e);
+    }
+    __device__ __forceinline__ static T dur(int64_t d) { return (double)d; }
+    __device__ __forceinline__ T of(T d) const { return scale_f64(d, p, iq); }
+    __device__ __forceinline__ static int64_t whole(T x) { return (int64_t)x; }
+};
+template <> struct BdScale<false> {
+    ScaleEntry e;
+    typedef int64_t T;
+    __device__ __forceinline__ void set(const ScaleEntry &x) { e = x; }
+    __device__ __forceinline__ static T dur(int64_t d) { return d; }
+    __device__ __forceinline__ T of(T d) const {
+        const uint64_t a = (uint64_t)d * (uint64_t)e.p;
+        return (int64_t)(e.magic ? (__umul64hi(a, e.magic) >> e.shift) : (a >> e.shift));
+    }
+    __device__ __forceinline__ static int64_t whole(T x) { return x; }
+};
+
+template <bool F64>
+__global__ __launch_bounds__(kBT) void k_bd_sum(BdArgs a) {
+    typedef BdScale<F64> S;
+    typedef typename S::T T;
+    __shared__ BdEnt sE[kMaxChunk];           // the chunk's kernels by class
+    __shared__ uint32_t sKey[kKeys];          // counts, then first places, of the buckets
+    __shared__ int32_t sWait[kMaxChunk];      // its waiting calls
+    __shared__ int sNk, sNw;
+    __shared__ int64_t sSum[kBW][kBV];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bx = (int)(blockIdx.x % (uint32_t)a.bx);
+    const int64_t u0 = (int64_t)(blockIdx.x / (uint32_t)a.bx) * a.chunk;
+    const int64_t u1 = u0 + a.chunk < a.n ? u0 + a.chunk : a.n;
+    const int64_t V = a.V, W = a.W;
+    const int64_t va = (int64_t)bx * kBV + lane, vb = va + 64;   // the lane's variants
+    const int64_t vac = va < V ? va : 0, vbc = vb < V ? vb : 0;
+
+    // sort: count, place
+    for (int i = tid; i < kKeys; i += kBT) sKey[i] = 0;
+    if (tid == 0) { sNk = 0; sNw = 0; }
+    __syncthreads();
+    constexpr int PER = kMaxChunk / kBT;
+    uint32_t rank[PER], c_[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const int64_t u = u0 + k * kBT + tid;
+        const uint8_t r = u < u1 ? a.role[u] : 0;
+        c_[k] = ~0u;
+        rank[k] = 0;
+        if (r == 1u) {
+            c_[k] = a.cls[u];
+            rank[k] = atomicAdd(&sKey[c_[k] & (kKeys - 1)], 1u);
+        } else if (r == 2u) {
+            sWait[atomicAdd(&sNw, 1)] = (int32_t)u;
+        }
+    }
+    __syncthreads();
+    {
+        constexpr int KP = kKeys / kBT;
+        uint32_t cnt[KP];
+        int64_t mine = 0, tot;
+#pragma unroll
+        for (int k = 0; k < KP; k++) { cnt[k] = sKey[tid * KP + k]; mine += cnt[k]; }
+        uint32_t at = (uint32_t)block_excl_scan<kBT>(mine, &tot);
+#pragma unroll
+        for (int k = 0; k < KP; k++) { sKey[tid * KP + k] = at; at += cnt[k]; }
+        if (tid == 0) sNk = (int)tot;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        if (c_[k] == ~0u) continue;
+        const int64_t u = u0 + k * kBT + tid;
+        sE[sKey[c_[k] & (kKeys - 1)] + rank[k]] = BdEnt{a.dur[u], (int32_t)u, c_[k]};
+    }
+    __syncthreads();
+
+    // kernels: each wave a contiguous quarter of the sorted list, 64 at a time
+    const int nk = sNk;
+    const int quarter = (nk + kBW - 1) / kBW;
+    const int e0 = wv * quarter, e1 = e0 + quarter < nk ? e0 + quarter : nk;
+    const int64_t w0 = (int64_t)bx * (kBV / 32);    // first removal word of the variants
+    S sa, sb;
+    T ka = 0, kb = 0;
+    uint32_t cur = ~0u;
+    for (int eb = e0; eb < e1; eb += 64) {
+        const int i = eb + lane < e1 ? eb + lane : e1 - 1;
+        const BdEnt x = sE[i];
+        uint32_t m[kBV / 32];
+#pragma unroll
+        for (int k = 0; k < kBV / 32; k++) {
+            const int64_t w = w0 + k < W ? w0 + k : W - 1;  // (past the last word: variants past V)
+            m[k] = a.rm[(int64_t)x.u * W + w];
+        }
+        const T d = S::dur(x.dur);
+        const uint32_t dlo = (uint32_t)__builtin_bit_cast(uint64_t, d),
+                       dhi = (uint32_t)(__builtin_bit_cast(uint64_t, d) >> 32);
+        const int cnt = e1 - eb < 64 ? e1 - eb : 64;
+        for (int j = 0; j < cnt; j++) {
+            const uint32_t c = __builtin_amdgcn_readlane(x.cls, j);
+            if (c != cur) {                                 // wave-uniform: the class changed
+                cur = c;
+                sa.set(a.table[(int64_t)c * V + vac]);
+                sb.set(a.table[(int64_t)c * V + vbc]);
+            }
+            const uint64_t db = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(dlo, j) |
+                                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(dhi, j) << 32);
+            const T dj = __builtin_bit_cast(T, db);
+            const uint64_t ma = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(m[0], j) |
+                                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(m[1], j) << 32);
+            const uint64_t mb = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(m[2], j) |
+                                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(m[3], j) << 32);
+            const T xa = sa.of(dj), xb = sb.of(dj);
+            ka += __builtin_amdgcn_inverse_ballot_w64(ma) ? (T)0 : xa;
+            kb += __builtin_amdgcn_inverse_ballot_w64(mb) ? (T)0 : xb;
+        }
+    }
+    sSum[wv][lane] = S::whole(ka);
+    sSum[wv][lane + 64] = S::whole(kb);
+    __syncthreads();
+    if (tid < kBV) {
+        const int64_t v = (int64_t)bx * kBV + tid;
+        int64_t k = 0, b = 0;
+#pragma unroll
+        for (int w = 0; w < kBW; w++) k += sSum[w][tid];
+        // waiting calls: start minus the moment the thread reached the call
+        const int nw = sNw;
+        if (v < V) {
+            const int64_t vw = v >> 5;
+            const uint32_t bit = (uint32_t)(v & 31);
+            for (int i = 0; i < nw; i++) {
+                const int64_t u = sWait[i];
+                const bool rmu = (a.rm[u * W + vw] >> bit) & 1u;
+                S s;
+                s.set(a.table[(int64_t)a.cls[u] * V + v]);
+                const int64_t dp = rmu ? 0 : S::whole(s.of(S::dur(a.dur[u])));
+                const int64_t start = a.finish[u * V + v] - dp;
+                const int32_t p = a.tprev[u];
+                int64_t reached = 0;
+                if (p >= 0) {
+                    const bool rmp = (a.rm[(int64_t)p * W + vw] >> bit) & 1u;
+                    reached = a.finish[(int64_t)p * V + v] + (rmp ? 0 : a.gap[p]);
+                }
+                b += start - reached;
+            }
+            // total - kernels, blocked, the rest (sums of integers: any order)
+            if (k) atomicAdd(&a.out[v * 4 + 1], (unsigned long long)-k);
+            if (b) atomicAdd(&a.out[v * 4 + 2], (unsigned long long)b);
+            if (k - b) atomicAdd(&a.out[v * 4 + 3], (unsigned long long)(k - b));
+        }
+    }
 }
 
 }  // namespace
@@ -257,58 +231,22 @@ __global__ __launch_bounds__(kBT) void k_bd_final(int32_t V, const int64_t *__re
 hipError_t launch_breakdown(const dd_graph *g, const dd_variants *var, const uint8_t *role_dev,
                             const int64_t *finish, const int64_t *makespan, int64_t *scratch,
                             int32_t *order, int64_t *out, hipStream_t s) {
-    // scratch: [2][V] accumulators, [n_cls + 1] class counts / cursors, the
-    // count of waiting calls; order: [n] tasks with a role by class, then
-    // [n] waiting calls
-    unsigned long long *acc = reinterpret_cast<unsigned long long *>(scratch);
-    unsigned long long *hist = acc + 2 * (size_t)var->V;
-    const int64_t C = var->n_cls;
-    unsigned long long *wcount = hist + C + 1;
-    int32_t *wlist = order + g->n;
-    hipError_t e = hipMemsetAsync(scratch, 0, sizeof(int64_t) * (2 * (size_t)var->V + C + 2), s);
-    if (e != hipSuccess) return e;
-    const int64_t n = g->n;
-    if (n > 0) {
-        k_bd_count<<<grid_for(n, kBT), kBT, 0, s>>>(n, var->n_cls, role_dev, g->cls, hist);
-        e = scan_exclusive(reinterpret_cast<int64_t *>(hist), reinterpret_cast<int64_t *>(hist),
-                           C, s);
-        if (e != hipSuccess) return e;
-        k_bd_scatter<<<grid_for(n, kBT), kBT, 0, s>>>(n, var->n_cls, role_dev, g->cls, hist, order);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    (void)scratch;
+    (void)order;
+    k_bd_init<<<grid_for(var->V, kBT), kBT, 0, s>>>(var->V, makespan, out);
+    if (g->n > 0) {
+        // chunks as long as leaves about four workgroups per compute unit,
+        // from 256 tasks (shorter ones are mostly sorting) to 2,048
+        const int64_t bx = (var->V + kBV - 1) / kBV;
+        int64_t chunk = kBT;
+        while (chunk < kMaxChunk && (g->n + chunk - 1) / chunk * bx > 1024) chunk *= 2;
+        const int64_t rows = (g->n + chunk - 1) / chunk;
+        BdArgs a{g->n, var->V, var->W, (int32_t)chunk, (int32_t)bx, role_dev, g->dur, g->gap, g->cls,
+                 g->thread_prev, var->table, var->rm_bits, finish,
+                 reinterpret_cast<unsigned long long *>(out)};
+        if (var->quot_ok) k_bd_sum<true><<<(unsigned)(rows * bx), kBT, 0, s>>>(a);
+        else k_bd_sum<false><<<(unsigned)(rows * bx), kBT, 0, s>>>(a);
     }
-    // chunks cover n tasks (a bound known without a read-back); each
-    // workgroup stops at the count of tasks with a role, hist[C], which the
-    // scatter leaves in place (no task has class C)
-    const int nvb = (var->V + kBT * kVL - 1) / (kBT * kVL);
-    const int64_t nch64 = (n + kChunk - 1) / kChunk;
-    if (n > 0) {
-        BdArgs a{var->V, var->W, nvb, (int32_t)nch64, var->table, var->rm_bits, finish, acc};
-        const unsigned grid = (unsigned)(nvb * nch64);
-        const int64_t *mp = reinterpret_cast<const int64_t *>(hist + C);
-        const bool d32 = g->dmax < (int64_t(1) << 32);
-        // waiting calls: at most 64 blocks of calls per variant block
-        const dim3 wg((unsigned)((var->V + kBT - 1) / kBT), 64u);
-        k_bd_wait_list<<<grid_for(n, kBT), kBT, 0, s>>>(n, role_dev, wcount, wlist);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        if (var->any_magic && d32) {
-            k_bd_accum<true, true><<<grid, kBT, 0, s>>>(mp, order, role_dev, g->dur, g->gap, g->cls, g->thread_prev, a);
-            k_bd_wait<true, true><<<wg, kBT, 0, s>>>(wcount, wlist, g->dur, g->gap, g->cls, g->thread_prev, a);
-        } else if (var->any_magic) {
-            k_bd_accum<true, false><<<grid, kBT, 0, s>>>(mp, order, role_dev, g->dur, g->gap, g->cls, g->thread_prev, a);
-            k_bd_wait<true, false><<<wg, kBT, 0, s>>>(wcount, wlist, g->dur, g->gap, g->cls, g->thread_prev, a);
-        } else if (d32) {
-            k_bd_accum<false, true><<<grid, kBT, 0, s>>>(mp, order, role_dev, g->dur, g->gap, g->cls, g->thread_prev, a);
-            k_bd_wait<false, true><<<wg, kBT, 0, s>>>(wcount, wlist, g->dur, g->gap, g->cls, g->thread_prev, a);
-        } else {
-            k_bd_accum<false, false><<<grid, kBT, 0, s>>>(mp, order, role_dev, g->dur, g->gap, g->cls, g->thread_prev, a);
-            k_bd_wait<false, false><<<wg, kBT, 0, s>>>(wcount, wlist, g->dur, g->gap, g->cls, g->thread_prev, a);
-        }
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    k_bd_final<<<grid_for(var->V, kBT), kBT, 0, s>>>(var->V, makespan, acc, out);
     return hipGetLastError();
 }
 

@@ -127,14 +127,9 @@ __global__ __launch_bounds__(256) void k_rm_bits(int64_t n, int32_t V, int32_t W
     }
 }
 
-// one scale entry as the kernel keeps it: floor(d * p / q) = floor(d * s)
-// with s = p / q rounded, off by at most one when q is not a power of two
-// (d * s is within 2 / q of the true quotient while d * p < 2^53), which the
-// exact remainder d * p - t * q then corrects; with q a power of two, s and
-// the product are exact
+// one scale entry as the kernel keeps it (scale_f64)
 struct alignas(16) SoScale {
-    double s;
-    uint32_t p, q;
+    double p, iq;
 };
 
 typedef __attribute__((address_space(1))) int64_t so_gi64;
@@ -154,7 +149,7 @@ struct alignas(16) SoPos {
 };
 constexpr uint32_t kSoHead = 1u, kSoLast = 2u, kSoTwo = 1u << 15, kSoMore = 1u << 16;
 
-template <bool START, bool MAGIC>
+template <bool START>
 __global__ __launch_bounds__(kSoNT, 4) void k_sim_solo(const int4 *__restrict__ bat,
                                                        const int32_t *__restrict__ nbat, SoloArgs a) {
     typedef Tm<true> TM;
@@ -188,22 +183,7 @@ __global__ __launch_bounds__(kSoNT, 4) void k_sim_solo(const int4 *__restrict__ 
 
     for (int c = tid; c < a.n_cls; c += kSoNT) {
         const ScaleEntry e = a.table[(int64_t)c * V + v];
-        SoScale z;
-        z.p = e.p;
-        z.q = 1u;
-        z.s = __builtin_ldexp((double)e.p, -(int)e.shift);
-        if (MAGIC) {
-            if (e.magic) {
-                // magic = floor(2^(64 + shift) / q) + 1 with q < 2^31: q is
-                // 2^(64 + shift) / magic to the nearest integer
-                const double q = __builtin_rint(__builtin_ldexp(1.0, 64 + (int)e.shift) / (double)e.magic);
-                z.q = (uint32_t)q;
-                z.s = (double)e.p / q;
-            } else {
-                z.q = 1u << e.shift;
-            }
-        }
-        sT[c] = z;
+        sT[c] = SoScale{(double)e.p, inv_quotient(e)};
     }
     if (tid <= kMaxCarryThreads) sTC[tid] = TM::zero;
     if (tid == 0) {
@@ -254,13 +234,7 @@ __global__ __launch_bounds__(kSoNT, 4) void k_sim_solo(const int4 *__restrict__ 
         const bool ok = q < B.p1;
         const uint32_t cl = r.w.x, flags = ok ? r.w.y : 0u;
         const SoScale sc = sT[ok ? cl & 0xffffu : 0u];
-        const double du = (double)r.u.x;
-        double t = __builtin_floor(du * sc.s);
-        if (MAGIC) {
-            const double rem = __builtin_fma(-t, (double)sc.q, du * (double)sc.p);
-            t = rem < 0.0 ? t - 1.0 : t;
-            t = rem >= (double)sc.q ? t + 1.0 : t;
-        }
+        const double t = scale_f64((double)r.u.x, sc.p, sc.iq);
         live = ok && !((r.rm >> (q & 31)) & 1u);
         dp = live ? TM::i(t) : 0;
         gp = live ? TM::w32(r.u.y) : 0;
@@ -509,10 +483,10 @@ __global__ __launch_bounds__(kSoNT, 4) void k_sim_solo(const int4 *__restrict__ 
     if (tid == 0) a.makespan[v] = TM::to_time((int64_t)sMs);
 }
 
-template <bool START, bool MAGIC>
+template <bool START>
 hipError_t launch_k(const dd_sched *sch, const SoloArgs &args, hipStream_t s) {
     const size_t dyn = sizeof(SoScale) * (size_t)args.n_cls;
-    k_sim_solo<START, MAGIC><<<(unsigned)args.V, kSoNT, dyn, s>>>(sch->bat, sch->nbat, args);
+    k_sim_solo<START><<<(unsigned)args.V, kSoNT, dyn, s>>>(sch->bat, sch->nbat, args);
     return hipGetLastError();
 }
 
@@ -553,8 +527,7 @@ hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants
                       sch->mask & g->cross_mask, var->n_cls, var->V, var->W,
                       sch->thread_carry ? 1 : 0, stride, rings + 16, ring, finish, start, makespan,
                       rings};
-        if (var->any_magic) e = start ? launch_k<true, true>(sch, args, s) : launch_k<false, true>(sch, args, s);
-        else e = start ? launch_k<true, false>(sch, args, s) : launch_k<false, false>(sch, args, s);
+        e = start ? launch_k<true>(sch, args, s) : launch_k<false>(sch, args, s);
     }
     dfree(rmb, s);
     dfree(rings, s);

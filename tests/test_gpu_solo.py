@@ -116,8 +116,9 @@ def test_many_parents(run):
 
 
 def test_scale_quotients():
-    """floor(d * p / q) where the rounded product lands on either side of an
-    integer: products up to 2^53, quotients at and next to multiples of q."""
+    """floor(d * p / q) where the rounded product comes closest to an integer:
+    products up to 2^50, quotients at and next to multiples of q; and the
+    same with products past 2^50, which the strip kernel takes."""
     require_gpu()
     rng = np.random.default_rng(880)
     qs = [3, 7, 10, 641, 65537, 1000003, 2**30 + 3, 2**31 - 1]
@@ -128,13 +129,15 @@ def test_scale_quotients():
         k = (2**32 - 2) // q
         dur[2 * i], dur[2 * i + 1] = k * q, k * q - 1
     g = H.graph(3, rng.integers(0, 3, n), [(i, i + 1) for i in range(n - 1)], dur, np.zeros(n, int))
-    s = np.ones((1, V, 2), np.int32)
-    for i, q in enumerate(qs):
-        s[0, 2 * i + 1] = (1, q)
-        s[0, 2 * i + 2] = (min(q - 1, 2**21 - 1), q)  # d * p just below 2^53
-    vs = VariantSet(V, s, pack_bits(np.zeros((n, V), bool)), np.full((V, 1), 1, np.uint64), [(0, V, 1)])
-    assert int(g.dur.max()) * int(s[..., 0].max()) < 2**53
-    _check(g, vs, "quotients")
+    for pmax in (2**18 - 1, 2**21 - 1):
+        s = np.ones((1, V, 2), np.int32)
+        for i, q in enumerate(qs):
+            s[0, 2 * i + 1] = (1, q)
+            s[0, 2 * i + 2] = (min(q - 1, pmax), q)
+        assert int(g.dur.max()) * int(s[..., 0].max()) < 2**32 * (pmax + 1)
+        vs = VariantSet(V, s, pack_bits(np.zeros((n, V), bool)), np.full((V, 1), 1, np.uint64),
+                        [(0, V, 1)])
+        _check(g, vs, "quotients")
 
 
 def test_plan_and_fallback():
