@@ -25,7 +25,8 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
 # their uniform path and never make a NaN: with IEEE mode off a double max
 # is one instruction (IEEE mode would quiet each operand first).
 _F64_TIMES = ["-fno-honor-nans", "-Xarch_device", "-mno-amdgpu-ieee"]
-FILE_FLAGS = {"k_simulate.hip": _F64_TIMES, "k_solo.hip": _F64_TIMES}
+FILE_FLAGS = {"k_simulate.hip": _F64_TIMES, "k_solo.hip": _F64_TIMES,
+              "k_event.hip": _F64_TIMES, "k_breakdown.hip": _F64_TIMES}
 
 
 def _compile(src: str) -> str:

@@ -694,12 +694,26 @@ dd_status dd_simulate_policy(const dd_graph *g, const dd_variants *var, int32_t 
         TRY(copy_in(&d_pp, pp, (size_t)g->n, s), "copy pp");
         TRY(copy_in(&d_prio, prio, (size_t)g->n, s), "copy prio");
     }
-    TRY(dd::dalloc_n(&ref, nv, s), "alloc reference counts");
-    TRY(dd::dalloc_n(&est, nv, s), "alloc start times");
     TRY(copy_in(&err, (const uint32_t *)nullptr, 1, s), "alloc");
-    TRY(dd::launch_sim_event(g, g->ev, var, policy, d_pp, d_prio, ref, est, d_finish, d_start,
-                             d_makespan, err, s), "simulate");
     {
+        const hipError_t e = dd::launch_sim_event(g, g->ev, var, policy, d_pp, d_prio, nullptr, nullptr,
+                                                  d_finish, d_start, d_makespan, err, s);
+        if (e != hipErrorNotSupported) {
+            TRY(e, "simulate");
+            dd::ReadBack rb(s, sizeof(uint32_t));
+            TRY(rb.add(&h_err, err, sizeof(uint32_t)), "read err");
+            TRY(rb.finish(), "sync");
+        } else {
+            h_err = 4u;
+        }
+    }
+    if (h_err & 4u) {
+        h_err = 0;
+        TRY(hipMemsetAsync(err, 0, sizeof(uint32_t), s), "memset");
+        TRY(dd::dalloc_n(&ref, nv, s), "alloc reference counts");
+        TRY(dd::dalloc_n(&est, nv, s), "alloc start times");
+        TRY(dd::launch_sim_event(g, g->ev, var, policy, d_pp, d_prio, ref, est, d_finish, d_start,
+                                 d_makespan, err, s), "simulate");
         dd::ReadBack rb(s, sizeof(uint32_t));
         TRY(rb.add(&h_err, err, sizeof(uint32_t)), "read err");
         TRY(rb.finish(), "sync");

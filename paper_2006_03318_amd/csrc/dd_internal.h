@@ -121,6 +121,7 @@ struct EventLists {
     uint4 *e4 = nullptr;        // [n] the first four out-edges (0 past the count)
     uint32_t *edges = nullptr;  // [n_edges]
     int64_t n_edges = 0;
+    uint64_t cls_mask = 0;      // edge classes present
 };
 constexpr uint32_t kEdgeAlways = 255;
 }  // namespace dd
@@ -314,6 +315,11 @@ hipError_t launch_batches(dd_sched *sch, hipStream_t s);
 hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants *var,
                        int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s);
 
+// removal bits [n][W] as one bit string per variant, [V][stride] words
+// (stride even, at least n / 32), in the order of `order` (null: by task)
+hipError_t launch_rm_bits(int64_t n, int32_t V, int32_t W, int64_t stride, const int32_t *order,
+                          const uint32_t *rm, uint32_t *rmb, hipStream_t s);
+
 // whether that kernel takes these handles: times and durations fit its
 // arithmetic (the schedule then has its records), the scales fit LDS
 inline bool solo_fits(const dd_sched *sch, const dd_variants *var) {
@@ -345,7 +351,10 @@ hipError_t launch_breakdown(const dd_graph *g, const dd_variants *var, const uin
 hipError_t build_event_lists(const dd_graph *g, EventLists *ev, hipStream_t s);
 void free_event_lists(EventLists *ev, hipStream_t s);
 // ref: int32 [V][n], est: int64 [V][n] working memory; err: uint32, zeroed
-// by the caller (bit 0: a cycle, bit 1: frontier capacity exceeded)
+// by the caller (bit 0: a cycle, bit 1: frontier capacity exceeded).  With
+// ref == nullptr (est is not used): the kernel that keeps its frontier in
+// registers; hipErrorNotSupported where it does not take the call, and err
+// bit 2 when a variant outgrew it (outputs undefined: call again with ref)
 hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_variants *var,
                             int32_t policy, const uint8_t *pp, const int32_t *prio, int32_t *ref,
                             int64_t *est, int64_t *finish, int64_t *start, int64_t *makespan,

@@ -30,8 +30,14 @@
 // task's record, the children's atomics), so the rate is set by how many
 // variants run at once: every variant is one wave of ~20 KB of LDS, eight
 // per CU, so about 2,000 variants are resident together.
+//
+// Two kernels.  k_sim_event_reg, below, serves what fits it; k_sim_event
+// (described above) everything else.
 #include "dd_common.h"
 #include "dd_internal.h"
+#include "dd_time.h"
+
+#include <type_traits>
 
 namespace dd {
 namespace {
@@ -109,14 +115,18 @@ __global__ __launch_bounds__(kBS) void k_ev_fill(int32_t n, const int64_t *__res
                                                  const int32_t *__restrict__ prev,
                                                  const int64_t *__restrict__ beg,
                                                  unsigned long long *__restrict__ cur,
-                                                 uint32_t *__restrict__ edges) {
+                                                 uint32_t *__restrict__ edges,
+                                                 unsigned long long *__restrict__ mask) {
     const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
     if (u >= n) return;
+    uint64_t cm = 0;
     for (int64_t e = in_ptr[u]; e < in_ptr[u + 1]; e++) {
         const int32_t s = in_src[e];
         const int64_t at = beg[s] + (int64_t)atomicAdd(&cur[s], 1ull);
         edges[at] = ((uint32_t)u << 8) | (in_cls ? (uint32_t)in_cls[e] : 0u);
+        cm |= 1ull << (in_cls ? in_cls[e] : 0);
     }
+    if (cm) atomic_or_hot(mask, (unsigned long long)cm);
     const int32_t p = prev[u];
     if (p >= 0) {
         const int64_t at = beg[p] + (int64_t)atomicAdd(&cur[p], 1ull);
@@ -369,6 +379,383 @@ __global__ __launch_bounds__(64) void k_sim_event(EvArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same simulation with the frontier in registers: a lane holds up to
+// kRegK ready tasks, each with everything that dispatching it needs, so a
+// step reads global memory once, for its children's records.  What a step
+// costs is the chain of latencies when few variants run, and the
+// instructions of its wave when 2,048 do (two waves per SIMD), so both are
+// kept short:
+//   * every ready task carries its time max(P[thread], start) as a double
+//     (dd_time.h); dispatching raises the times of its thread's other ready
+//     tasks, and schedule(Q) is one DPP minimum over the lanes, resolved by
+//     a ballot (ties: by id, or by the priority rule);
+//   * the lane that loads a child's record is a lane with a free place, so a
+//     child that becomes ready is where it belongs; the records of its own
+//     first two children are touched at once, so that they are in the CU's
+//     cache when it is dispatched;
+//   * a child with one parent is ready at once; the others wait in a small
+//     LDS table (id -> parents done, start so far), buckets of four ids, so
+//     no per-variant array of counts and starts exists and none has to be
+//     cleared.
+// Capacity (ready tasks, table buckets) is not known beforehand: a wave that
+// runs out sets error bit 2 and stops, as do the others when they see it,
+// and the caller runs k_sim_event.
+// VGG-19 with P3's slices, P3 rule: 14,688 tasks x 2,048 variants 25.8 ms a
+// call (33.7 with k_sim_event), x 30 variants 22.7; 918 tasks x 30 variants,
+// default rule: 1.13 ms (1.43).
+constexpr int kRegK = 4;              // ready tasks per lane
+constexpr int kPendB = 256;           // buckets of four waiting tasks
+constexpr int kRegCls = 512;          // scale entries in LDS at most
+constexpr int kRegT = 1024;           // thread progress words in LDS at most
+constexpr int kRegN = 32768;          // tasks whose removal bits go to LDS at most
+
+struct alignas(64) EvTask {
+    uint32_t dur, gap, ebeg, ecnt;    // duration and gap (below 2^32), out-edges
+    uint32_t meta;                    // thread, push/pull << 12, class << 16
+    int32_t prio;
+    uint32_t parents, pad;            // all parents (every edge class on)
+    uint4 e4;                         // its first four out-edges (child << 8 | class)
+};
+
+__global__ __launch_bounds__(kBS) void k_ev_task(int32_t n, const int4 *__restrict__ rec,
+                                                 const uint4 *__restrict__ e4,
+                                                 const int64_t *__restrict__ dur,
+                                                 const int64_t *__restrict__ gap,
+                                                 const int64_t *__restrict__ in_ptr,
+                                                 const int32_t *__restrict__ prev,
+                                                 const uint8_t *__restrict__ pp,
+                                                 const int32_t *__restrict__ prio,
+                                                 EvTask *__restrict__ out) {
+    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
+    if (u >= n) return;
+    const int4 r = rec[u];
+    EvTask t;
+    t.dur = (uint32_t)dur[u];
+    t.gap = (uint32_t)gap[u];
+    t.ebeg = (uint32_t)r.x;
+    t.ecnt = (uint32_t)r.y;
+    t.meta = (uint32_t)r.z | ((pp && pp[u]) ? 1u << 12 : 0u) | ((uint32_t)r.w << 16);
+    t.prio = prio ? prio[u] : 0;
+    t.parents = (uint32_t)(in_ptr[u + 1] - in_ptr[u]) + (prev[u] >= 0 ? 1u : 0u);
+    t.pad = 0;
+    t.e4 = e4[u];
+    out[u] = t;
+}
+
+struct EvRegArgs {
+    int32_t n, V, W, T, n_cls;
+    const EvTask *__restrict__ task;
+    const uint32_t *__restrict__ edges;
+    const ScaleEntry *__restrict__ table;  // [n_cls][V]
+    const uint32_t *__restrict__ rm;       // [n][W]
+    const uint32_t *__restrict__ rmb;      // [V][rmb_stride] removal bits by task, or null
+    int64_t rmb_stride;
+    int64_t *finish, *start, *makespan;
+    uint32_t *err;
+};
+
+// minimum over the wave (every lane active), in lane 63
+template <int CTRL, int RMASK>
+__device__ __forceinline__ double dpp_min_step(double x) {
+    const int64_t b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp((int)(uint32_t)b, (int)(uint32_t)b, CTRL, RMASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)((uint64_t)b >> 32), (int)((uint64_t)b >> 32), CTRL,
+                                               RMASK, 0xf, false);
+    return __builtin_fmin(x, __longlong_as_double(join64(lo, hi)));
+}
+__device__ __forceinline__ double wave_min_f64(double x) {
+    x = dpp_min_step<0x111, 0xf>(x);
+    x = dpp_min_step<0x112, 0xf>(x);
+    x = dpp_min_step<0x114, 0xf>(x);
+    x = dpp_min_step<0x118, 0xf>(x);
+    x = dpp_min_step<0x142, 0xa>(x);
+    x = dpp_min_step<0x143, 0xc>(x);
+    return __longlong_as_double(readlane64(__double_as_longlong(x), 63));
+}
+
+// one place of the frontier
+struct EvSlot {
+    double t, dp;          // time (infinite: free), duration as transformed
+    uint32_t id, gap;      // id: task | kPPb | kRMb; gap as transformed
+    uint32_t th, ebeg, ecnt;
+    int32_t pr;
+    uint4 e4;
+};
+
+template <bool START, bool PRIO, bool RLDS>
+__global__ __launch_bounds__(64, 2) void k_sim_event_reg(EvRegArgs a) {
+    __shared__ __align__(16) uint32_t pKey[kPendB * 4];   // waiting tasks: id + 1 (0: free)
+    __shared__ uint32_t pCnt[kPendB * 4];     // parents done
+    __shared__ unsigned long long pEst[kPendB * 4];   // start so far (times as double bits)
+    extern __shared__ double sLds[];          // [T] thread progress, [n_cls] {p, 1/q}, removal bits
+    double *const sP = sLds;
+    double2 *const sTab = reinterpret_cast<double2 *>(sLds + ((a.T + 1) & ~1));
+    uint32_t *const sRm = reinterpret_cast<uint32_t *>(sTab + a.n_cls);
+    const int lane = threadIdx.x;
+    const int v = blockIdx.x;
+    const int64_t V = a.V;
+    const uint32_t vbit = 1u << (v & 31);
+    const uint32_t *const rmv = a.rm + (v >> 5);
+    const double kInf = __longlong_as_double(0x7ff0000000000000ll);
+    const double kZero = 4503599627370496.0;  // 2^52: time zero (dd_time.h)
+    for (int t = lane; t < a.T; t += 64) sP[t] = kZero;
+    for (int c = lane; c < a.n_cls; c += 64) {
+        const ScaleEntry e = a.table[(int64_t)c * V + v];
+        sTab[c] = make_double2((double)e.p, inv_quotient(e));
+    }
+    if (RLDS)
+        for (int i = lane; i < (a.n + 31) / 32; i += 64) sRm[i] = a.rmb[(int64_t)v * a.rmb_stride + i];
+    for (int i = lane; i < kPendB * 4; i += 64) {
+        pKey[i] = 0;
+        pCnt[i] = 0;
+        pEst[i] = 0;
+    }
+    __syncthreads();
+
+    EvSlot s[kRegK];
+#pragma unroll
+    for (int k = 0; k < kRegK; k++) {
+        s[k].t = kInf;
+        s[k].id = ~0u;
+        s[k].th = ~0u;
+        s[k].dp = 0;
+        s[k].gap = s[k].ebeg = s[k].ecnt = 0;
+        s[k].pr = 0;
+        s[k].e4 = make_uint4(0u, 0u, 0u, 0u);
+    }
+    uint32_t err = 0;
+    uint32_t touch0 = 0, touch1 = 0;
+    // a lane takes task c, ready at `est`, into place k
+    auto fill = [&](EvSlot &z, uint32_t c, const uint4 &w0, const uint4 &w1, const uint4 &w2,
+                    uint32_t rmw, double est) {
+        const bool gone = RLDS ? (sRm[c >> 5] >> (c & 31)) & 1u : (rmw & vbit) != 0u;
+        const double2 sc = sTab[w1.x >> 16];
+        z.th = w1.x & 0xfffu;
+        const double p = sP[z.th];
+        z.t = __builtin_fmax(p, est);
+        z.dp = gone ? 0.0 : scale_f64((double)w0.x, sc.x, sc.y);
+        z.gap = gone ? 0u : w0.y;
+        z.id = c | ((w1.x & (1u << 12)) ? kPPb : 0u) | (gone ? kRMb : 0u);
+        z.ebeg = w0.z;
+        z.ecnt = w0.w;
+        z.pr = (int32_t)w1.y;
+        z.e4 = w2;
+    };
+    auto words = [&](uint32_t c, uint4 &w0, uint4 &w1, uint4 &w2, uint32_t &rmw) {
+        const uint4 *r = reinterpret_cast<const uint4 *>(a.task + c);
+        w0 = r[0];
+        w1 = r[1];
+        w2 = r[2];
+        rmw = RLDS ? 0u : rmv[(int64_t)c * a.W];
+    };
+
+    // tasks without parents
+    for (int32_t base = 0; base < a.n; base += 64) {
+        const int32_t u = base + lane;
+        const bool root = u < a.n && a.task[u < a.n ? u : 0].parents == 0u;
+        uint64_t todo = __ballot(root);
+        while (todo) {
+            int kk = -1;
+            uint64_t fr = 0;
+#pragma unroll
+            for (int k = kRegK - 1; k >= 0; k--) {
+                const uint64_t f = __ballot(s[k].t == kInf);
+                if (f) { kk = k; fr = f; }
+            }
+            if (kk < 0) { err |= 4u; break; }
+            // the r-th free lane takes the r-th root of the block
+            const int r = __popcll(fr & ((1ull << lane) - 1ull));
+            const bool mine = ((fr >> lane) & 1ull) && r < __popcll(todo);
+            uint64_t m = todo;
+            int at = 0;
+            for (int i = 0; i <= r && m; i++) {
+                at = __ffsll((unsigned long long)m) - 1;
+                m &= m - 1;
+            }
+            if (mine) {
+                uint4 w0, w1, w2;
+                uint32_t rw;
+                words((uint32_t)(base + at), w0, w1, w2, rw);
+#pragma unroll
+                for (int k = 0; k < kRegK; k++)
+                    if (k == kk) fill(s[k], (uint32_t)(base + at), w0, w1, w2, rw, kZero);
+            }
+            int took = __popcll(fr) < __popcll(todo) ? __popcll(fr) : __popcll(todo);
+            for (; took > 0; took--) todo &= todo - 1;
+        }
+        if (err) break;
+    }
+
+    double ms = kZero;
+    int32_t done = 0;
+    uint32_t bu = 0;                // this lane's buffered result: task, finish, start
+    double bf = kZero, bs = kZero;
+    err = __any(err != 0u) ? 4u : 0u;
+    while (!err) {
+        // ---- schedule(Q) ----
+        double tl = s[0].t;
+#pragma unroll
+        for (int k = 1; k < kRegK; k++) tl = __builtin_fmin(tl, s[k].t);
+        const double T0 = wave_min_f64(tl);
+        if (T0 == kInf) break;                            // the frontier is empty
+        uint32_t key = ~0u;                               // least id of the lane's tasks of that time
+#pragma unroll
+        for (int k = 0; k < kRegK; k++) {
+            const uint32_t i = s[k].t == T0 ? s[k].id & kIdMask : ~0u;
+            key = i < key ? i : key;
+        }
+        uint32_t wid;
+        {
+            const uint64_t at = __ballot(key != ~0u);
+            if ((at & (at - 1)) == 0) wid = __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)at) - 1);
+            else wid = wave_min_u32(key);
+        }
+        if (PRIO) {
+            // when it is a push/pull task: of those of least time, the one of
+            // highest priority, least id among equals
+            bool ppw = false;
+#pragma unroll
+            for (int k = 0; k < kRegK; k++) ppw |= s[k].t == T0 && s[k].id == ((s[k].id & kRMb) | kPPb | wid);
+            if (__any(ppw)) {
+                uint32_t best = ~0u;                      // descending priority
+#pragma unroll
+                for (int k = 0; k < kRegK; k++) {
+                    const uint32_t d = ~((uint32_t)s[k].pr ^ 0x80000000u);
+                    if (s[k].t == T0 && (s[k].id & kPPb) && d < best) best = d;
+                }
+                const uint32_t b0 = wave_min_u32(best);
+                key = ~0u;
+#pragma unroll
+                for (int k = 0; k < kRegK; k++) {
+                    const uint32_t d = ~((uint32_t)s[k].pr ^ 0x80000000u);
+                    const uint32_t i = s[k].t == T0 && (s[k].id & kPPb) && d == b0 ? s[k].id & kIdMask : ~0u;
+                    key = i < key ? i : key;
+                }
+                const uint64_t at = __ballot(key != ~0u);
+                if ((at & (at - 1)) == 0)
+                    wid = __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)at) - 1);
+                else
+                    wid = wave_min_u32(key);
+            }
+        }
+        // ---- dispatch: the winner's fields, uniform ----
+        uint32_t id = 0, th = 0, ebeg = 0, ecnt = 0, gp = 0, x0 = 0, x1 = 0, x2 = 0, x3 = 0;
+        double dp = 0;
+#pragma unroll
+        for (int k = 0; k < kRegK; k++) {
+            const uint64_t at = __ballot(s[k].t == T0 && (s[k].id & kIdMask) == wid);
+            if (at) {
+                const int l = __ffsll((unsigned long long)at) - 1;
+                id = __builtin_amdgcn_readlane(s[k].id, l);
+                th = __builtin_amdgcn_readlane(s[k].th, l);
+                ebeg = __builtin_amdgcn_readlane(s[k].ebeg, l);
+                ecnt = __builtin_amdgcn_readlane(s[k].ecnt, l);
+                gp = __builtin_amdgcn_readlane(s[k].gap, l);
+                x0 = __builtin_amdgcn_readlane(s[k].e4.x, l);
+                x1 = __builtin_amdgcn_readlane(s[k].e4.y, l);
+                x2 = __builtin_amdgcn_readlane(s[k].e4.z, l);
+                x3 = __builtin_amdgcn_readlane(s[k].e4.w, l);
+                dp = __longlong_as_double(readlane64(__double_as_longlong(s[k].dp), l));
+                if (lane == l) s[k].t = kInf;
+            }
+        }
+        const double f = T0 + dp;
+        const double rel = f + (double)gp;
+        if (!(id & kRMb)) ms = __builtin_fmax(ms, f);
+        // results go out 64 at a time, one per lane
+        if (lane == (done & 63)) {
+            bu = wid;
+            bf = f;
+            bs = T0;
+        }
+        done++;
+        if ((done & 63) == 0) {
+            a.finish[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bf));
+            if (START) a.start[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bs));
+            // another wave ran out of room: this run is thrown away
+            if (load_coherent(a.err) & 4u) break;
+        }
+        sP[th] = rel;
+#pragma unroll
+        for (int k = 0; k < kRegK; k++)
+            s[k].t = s[k].th == th ? __builtin_fmax(s[k].t, rel) : s[k].t;   // (free places stay infinite)
+        // ---- children ----
+        for (uint32_t base = 0; base < ecnt;) {
+            int kk = -1;
+            uint64_t fr = 0;
+#pragma unroll
+            for (int k = kRegK - 1; k >= 0; k--) {
+                const uint64_t z = __ballot(s[k].t == kInf);
+                if (z) { kk = k; fr = z; }
+            }
+            if (kk < 0) { err = 4u; break; }
+            const uint32_t r = base + (uint32_t)__popcll(fr & ((1ull << lane) - 1ull));
+            const bool mine = ((fr >> lane) & 1ull) && r < ecnt;
+            base += (uint32_t)__popcll(fr);
+            uint32_t c = (r == 0 ? x0 : r == 1 ? x1 : r == 2 ? x2 : x3) >> 8;
+            if (ecnt > 4u) {
+                if (mine && r >= 4u) c = a.edges[(int64_t)ebeg + r] >> 8;
+            }
+            bool ready = false;
+            if (mine) {
+                uint4 w0, w1, w2;
+                uint32_t rw;
+                words(c, w0, w1, w2, rw);
+                double est = rel;
+                ready = w1.z == 1u;
+                if (!ready) {
+                    // find the child in its bucket, or take a free word there
+                    const uint32_t b = (c >> 1) & (kPendB - 1);
+                    uint32_t *const kb = pKey + b * 4u;
+                    const uint32_t k0 = kb[0], k1 = kb[1], k2 = kb[2], k3 = kb[3];
+                    int e = k0 == c + 1u ? 0 : k1 == c + 1u ? 1 : k2 == c + 1u ? 2 : k3 == c + 1u ? 3 : -1;
+                    for (int i = 0; i < 4 && e < 0; i++) {
+                        const uint32_t was = atomicCAS(&kb[i], 0u, c + 1u);
+                        if (was == 0u || was == c + 1u) e = i;
+                    }
+                    if (e < 0) {
+                        err = 4u;
+                    } else {
+                        const uint32_t p = b * 4u + (uint32_t)e;
+                        // (bit patterns of nonnegative doubles order as integers)
+                        const unsigned long long oe =
+                            atomicMax(&pEst[p], (unsigned long long)__double_as_longlong(rel));
+                        const uint32_t before = atomicAdd(&pCnt[p], 1u);
+                        if (before + 1u == w1.z) {        // its last parent: out of the table
+                            ready = true;
+                            est = __builtin_fmax(rel, __longlong_as_double((long long)oe));
+                            pCnt[p] = 0;
+                            pEst[p] = 0;
+                            kb[e] = 0;
+                        }
+                    }
+                }
+                if (ready) {
+#pragma unroll
+                    for (int k = 0; k < kRegK; k++)
+                        if (k == kk) fill(s[k], c, w0, w1, w2, rw, est);
+                    // bring the records of its first two children into the cache
+                    asm volatile("" ::"v"(touch0), "v"(touch1));   // (of an earlier step)
+                    touch0 = a.task[w2.x >> 8].dur;
+                    touch1 = a.task[w2.y >> 8].dur;
+                }
+            }
+            if (__any(err != 0u)) { err = 4u; break; }
+        }
+        if (__any(err != 0u)) { err = 4u; break; }
+    }
+    if (lane < (done & 63)) {
+        a.finish[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bf));
+        if (START) a.start[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bs));
+    }
+    if (done != a.n && !err) err = 1u;
+    if (lane == 0) {
+        a.makespan[v] = Tm<true>::to_time(__double_as_longlong(ms));
+        if (err) atomicOr(a.err, err);
+    }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -377,6 +764,7 @@ hipError_t build_event_lists(const dd_graph *g, EventLists *ev, hipStream_t s) {
     hipError_t e = hipSuccess;
     unsigned long long *cnt = nullptr;
     int64_t *beg = nullptr;
+    unsigned long long *mask = nullptr;
     int64_t m = 0;
     const int blocks = grid_for(n, kBS);
 #define EV_TRY(x)                  \
@@ -386,6 +774,8 @@ hipError_t build_event_lists(const dd_graph *g, EventLists *ev, hipStream_t s) {
     } while (0)
     EV_TRY(dalloc_n(&cnt, (size_t)n + 1, s));
     EV_TRY(dalloc_n(&beg, (size_t)n + 1, s));
+    EV_TRY(dalloc_n(&mask, 1, s));
+    EV_TRY(hipMemsetAsync(mask, 0, sizeof(unsigned long long), s));
     EV_TRY(hipMemsetAsync(cnt, 0, sizeof(unsigned long long) * ((size_t)n + 1), s));
     if (n > 0) {
         k_ev_count<<<blocks, kBS, 0, s>>>(n, g->xin_ptr, g->xin_src, g->thread_prev, cnt);
@@ -400,18 +790,22 @@ hipError_t build_event_lists(const dd_graph *g, EventLists *ev, hipStream_t s) {
     EV_TRY(hipMemsetAsync(cnt, 0, sizeof(unsigned long long) * ((size_t)n + 1), s));
     if (n > 0) {
         k_ev_fill<<<blocks, kBS, 0, s>>>(n, g->xin_ptr, g->xin_src, g->xin_cls, g->thread_prev,
-                                         beg, cnt, ev->edges);
+                                         beg, cnt, ev->edges, mask);
         EV_TRY(hipGetLastError());
         k_ev_rec<<<blocks, kBS, 0, s>>>(n, beg, g->thread_id, g->cls, ev->edges, ev->rec, ev->e4);
         EV_TRY(hipGetLastError());
     }
     ev->n_edges = m;
-    // complete before any stream uses the lists
-    EV_TRY(hipStreamSynchronize(s));
+    {   // (also waits: the lists are complete before any stream uses them)
+        ReadBack rb(s, sizeof(uint64_t));
+        EV_TRY(rb.add(&ev->cls_mask, mask, sizeof(uint64_t)));
+        EV_TRY(rb.finish());
+    }
 out:
 #undef EV_TRY
     dfree(cnt, s);
     dfree(beg, s);
+    dfree(mask, s);
     return e;
 }
 
@@ -426,6 +820,50 @@ hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_va
                             int32_t policy, const uint8_t *pp, const int32_t *prio, int32_t *ref,
                             int64_t *est, int64_t *finish, int64_t *start, int64_t *makespan,
                             uint32_t *err, hipStream_t s) {
+    if (!ref) {
+        // the frontier in registers: every edge class of the graph on in
+        // every variant (a task's parents are then the same in all of them),
+        // 32-bit durations and gaps, times that doubles hold
+        if (g->n == 0 || !var->quot_ok || g->dmax >= (int64_t(1) << 32) || g->gmax >= (int64_t(1) << 32) ||
+            var->n_cls > kRegCls || g->n_threads > kRegT || (ev.cls_mask & ~var->all_mask))
+            return hipErrorNotSupported;
+        EvTask *task = nullptr;
+        hipError_t e = dalloc_n(&task, (size_t)g->n, s);
+        if (e != hipSuccess) return e;
+        k_ev_task<<<grid_for(g->n, kBS), kBS, 0, s>>>(g->n, ev.rec, ev.e4, g->dur, g->gap, g->xin_ptr,
+                                                     g->thread_prev, pp, prio, task);
+        const bool rlds = g->n <= kRegN;
+        const int64_t stride = (g->n + 63) / 64 * 2;
+        uint32_t *rmb = nullptr;
+        if (rlds) {
+            e = dalloc_n(&rmb, (size_t)var->V * (size_t)stride, s);
+            if (e == hipSuccess)
+                e = launch_rm_bits(g->n, var->V, var->W, stride, nullptr, var->rm_bits, rmb, s);
+            if (e != hipSuccess) {
+                dfree(task, s);
+                dfree(rmb, s);
+                return e;
+            }
+        }
+        EvRegArgs r{g->n, var->V, var->W, g->n_threads, var->n_cls, task, ev.edges, var->table,
+                    var->rm_bits, rmb, stride, finish, start, makespan, err};
+        const size_t lds = sizeof(double) * (size_t)((g->n_threads + 1) & ~1) +
+                           sizeof(double2) * (size_t)var->n_cls + (rlds ? sizeof(uint32_t) * (size_t)stride : 0);
+        auto go = [&](auto st, auto pr, auto rl) {
+            k_sim_event_reg<decltype(st)::value, decltype(pr)::value, decltype(rl)::value>
+                <<<var->V, 64, lds, s>>>(r);
+        };
+        const std::true_type yes{};
+        const std::false_type no{};
+        auto by_rl = [&](auto st, auto pr) { if (rlds) go(st, pr, yes); else go(st, pr, no); };
+        auto by_pr = [&](auto st) { if (policy == DD_POLICY_PRIORITY) by_rl(st, yes); else by_rl(st, no); };
+        if (start) by_pr(yes);
+        else by_pr(no);
+        e = hipGetLastError();
+        dfree(task, s);
+        dfree(rmb, s);
+        return e;
+    }
     EvArgs a;
     a.n = g->n;
     a.V = var->V;

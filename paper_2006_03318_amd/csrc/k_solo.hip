@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void k_rm_bits(int64_t n, int32_t V, int32_t W
     const int64_t q0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
     if (q0 >= n) return;
     const int64_t q = q0 + lane;
-    const int64_t u = q < n ? pos_node[q] : 0;
+    const int64_t u = q < n ? (pos_node ? pos_node[q] : q) : 0;
     for (int w = blockIdx.y; w < W; w += gridDim.y) {
         const uint32_t x = q < n ? rm[u * W + w] : 0u;
         uint64_t mine = 0;
@@ -503,6 +503,16 @@ hipError_t launch_batches(dd_sched *sch, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_rm_bits(int64_t n, int32_t V, int32_t W, int64_t stride, const int32_t *order,
+                          const uint32_t *rm, uint32_t *rmb, hipStream_t s) {
+    const int64_t bx = (n + 255) / 256;
+    // enough blocks along the words that few positions still fill the chip
+    int64_t by = bx < 1024 ? 1024 / bx : 1;
+    if (by > W) by = W;
+    k_rm_bits<<<dim3((unsigned)bx, (unsigned)by), 256, 0, s>>>(n, V, W, stride, order, rm, rmb);
+    return hipGetLastError();
+}
+
 hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants *var,
                        int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s) {
     // scratch of the call: removal bits by position, the rings, the target
@@ -516,12 +526,9 @@ hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants
     hipError_t e = dalloc_n(&rmb, (size_t)var->V * (size_t)stride, s);
     if (e == hipSuccess) e = dalloc_n(&rings, (size_t)var->V * (size_t)ring + 16, s);
     if (e == hipSuccess) {
-        const int64_t bx = (n + 255) / 256;
-        // enough blocks along the words that few positions still fill the chip
-        int64_t by = bx < 1024 ? 1024 / bx : 1;
-        if (by > var->W) by = var->W;
-        k_rm_bits<<<dim3((unsigned)bx, (unsigned)by), 256, 0, s>>>(n, var->V, var->W, stride, sch->pos_node,
-                                                                  var->rm_bits, rmb);
+        e = launch_rm_bits(n, var->V, var->W, stride, sch->pos_node, var->rm_bits, rmb, s);
+    }
+    if (e == hipSuccess) {
         SoloArgs args{sch->step_ptr, sch->so_rec, sch->gat_ptr, sch->gat_src, sch->gat_spos,
                       sch->gat_cls, g->gap, var->table, var->rm_bits, rmb, var->edge_on,
                       sch->mask & g->cross_mask, var->n_cls, var->V, var->W,
