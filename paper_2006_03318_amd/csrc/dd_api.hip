@@ -13,12 +13,6 @@
 
 #include "dd_internal.h"
 
-namespace dd {
-// tiled chain ranking (k_graph.hip)
-hipError_t launch_rank_tiles(const dd_graph *g, int32_t *dloc, int32_t *ext, int32_t *xlist,
-                             int64_t *xidx, uint32_t *err, hipStream_t s);
-}  // namespace dd
-
 namespace {
 
 thread_local char g_err[512] = "";
@@ -68,8 +62,9 @@ hipError_t copy_in(T **dst, const T *src, size_t count, hipStream_t s) {
 
 // memory that kernels on the current device may read in place: a copy queued
 // on the call's stream would read it no earlier
-bool on_device(const void *p) {
-    if (!p) return false;
+// (align: their elements, as a copy would not have minded)
+bool on_device(const void *p, size_t align = 1) {
+    if (!p || reinterpret_cast<uintptr_t>(p) % align) return false;
     hipPointerAttribute_t at;
     int dev = 0;
     if (hipPointerGetAttributes(&at, p) != hipSuccess) {
@@ -92,13 +87,10 @@ void free_graph_arrays(dd_graph *g) {
 void free_sched_arrays(dd_sched *x) {
     hipStream_t s = x->stream;
     dd::join_uses(x->uses, s);
-    dd::dfree(x->step_ptr, s); dd::dfree(x->pos_node, s); dd::dfree(x->pos_flags, s);
-    dd::dfree(x->pos_dur, s); dd::dfree(x->pos_gap, s); dd::dfree(x->pos_cls, s);
-    dd::dfree(x->gat_ptr, s); dd::dfree(x->gat_src, s); dd::dfree(x->gat_pos, s);
-    dd::dfree(x->gat_cls, s); dd::dfree(x->gat_gap, s); dd::dfree(x->node_step, s);
-    dd::dfree(x->gat_spos, s); dd::dfree(x->rec, s);
-    dd::dfree(x->bat, s); dd::dfree(x->nbat, s);
-    dd::dfree(x->so_rec, s);
+    dd::dfree(x->step_ptr, s); dd::dfree(x->pos_node, s); dd::dfree(x->node_step, s);
+    dd::dfree(x->gat_rng, s); dd::dfree(x->gat_src, s); dd::dfree(x->gat_spos, s);
+    dd::dfree(x->gat_cls, s); dd::dfree(x->gat_gap, s); dd::dfree(x->rec, s);
+    dd::dfree(x->bat, s); dd::dfree(x->nbat, s); dd::dfree(x->so_rec, s);
 }
 
 }  // namespace
@@ -235,6 +227,20 @@ char *stage_buf(size_t bytes, hipError_t *e) {
 }
 }  // namespace
 
+hipError_t direct_buf(void **host, void **dev) {
+    thread_local void *buf = nullptr, *dbuf = nullptr;
+    if (!buf) {
+        void *nb = nullptr;
+        hipError_t e = hipHostMalloc(&nb, kDirectBytes, hipHostMallocPortable | hipHostMallocMapped);
+        if (e == hipSuccess) e = hipHostGetDevicePointer(&dbuf, nb, 0);
+        if (e != hipSuccess) return e;
+        buf = nb;
+    }
+    *host = buf;
+    *dev = dbuf;
+    return hipSuccess;
+}
+
 ReadBack::ReadBack(hipStream_t s, size_t cap) : s_(s) {
     cap_ = cap + 8 * 16;                  // room for aligning up to 16 items
     buf_ = stage_buf(cap_, &err_);
@@ -322,124 +328,130 @@ dd_status dd_graph_load_ex(int32_t n, int32_t n_threads, const int64_t *in_ptr,
     g->stream = s;
     g->id = g_next_id.fetch_add(1);
     (void)hipGetDevice(&g->device);
-    int64_t *d_in_ptr = nullptr, *cnt = nullptr, *len = nullptr;
-    int32_t *d_in_src = nullptr, *succ = nullptr, *heads = nullptr, *nxt = nullptr,
-            *nxt2 = nullptr, *rank2 = nullptr;
+    int64_t *d_in_ptr = nullptr;
+    int32_t *d_in_src = nullptr;
     uint8_t *d_ecls = nullptr;
-    uint32_t *err = nullptr;
-    dd::LoadStats *stats = nullptr;
-    int64_t ends[2] = {0, 0};
-    uint32_t h_err = 0;
-    uint32_t h_err2[2] = {0u, 0u};     // error bits; too many tile exits for the tiled ranking
-    dd::LoadStats hs{};
-    const size_t N1 = (size_t)n + 1;
-    int64_t E = 0;
+    dd::LoadOut *lo = nullptr, *lo_dev = nullptr;
+    dd::LoadIn in;
+    const size_t N = (size_t)n;
+    // a field of the graph: kernels copy it from device memory, anything else
+    // is copied here and then checked in place
+    auto field = [&](auto **dst, const auto *src, const auto **from) -> hipError_t {
+        *from = nullptr;
+        hipError_t e = dd::dalloc_n(dst, N, s);
+        if (e != hipSuccess || !src) return e;
+        if (on_device(src, sizeof(*src))) {
+            *from = src;
+            return e;
+        }
+        *from = *dst;
+        return hipMemcpyAsync(*dst, src, N * sizeof(*src), hipMemcpyDefault, s);
+    };
+    // the edge arrays, once their length is known
+    auto edges = [&](int64_t e_count) -> hipError_t {
+        if (e_count < 0 || e_count >= (int64_t(1) << 31)) {
+            st = lo && lo->ends[0] != 0 ? fail(DD_EINVAL, "in_ptr[0] != 0")
+                                        : fail(DD_EINVAL, "edge count outside [0, 2^31)");
+            return hipErrorInvalidValue;
+        }
+        if (e_count > 0 && !in_src) {
+            st = fail(DD_EINVAL, "in_src is NULL");
+            return hipErrorInvalidValue;
+        }
+        g->n_edges = e_count;
+        const size_t E = (size_t)e_count;
+        hipError_t e = hipSuccess;
+        // (shared threads: the graph keeps every dependency edge as given)
+        if (g->shared || !on_device(in_src, sizeof(int32_t))) {
+            e = copy_in(&d_in_src, in_src, E, s);
+            in.in_src = d_in_src;
+        } else {
+            in.in_src = in_src;
+        }
+        if (e == hipSuccess && (g->shared || (edge_cls && !on_device(edge_cls)))) {
+            e = copy_in(&d_ecls, edge_cls, E, s);
+            in.ecls = edge_cls ? d_ecls : nullptr;
+        } else {
+            in.ecls = edge_cls;
+        }
+        if (e == hipSuccess && !g->shared) e = dd::dalloc_n(&g->xin_src, E + 1, s);
+        if (e == hipSuccess && !g->shared) e = dd::dalloc_n(&g->xin_cls, E + 1, s);
+        if (e != hipSuccess) st = hip_fail(e, "copy edges");
+        return e;
+    };
 
-    TRY(copy_in(&d_in_ptr, in_ptr, N1, s), "copy in_ptr");
     {
-        dd::ReadBack rb(s, 2 * sizeof(int64_t));
-        TRY(rb.add(&ends[0], d_in_ptr, sizeof(int64_t)), "read in_ptr");
-        TRY(rb.add(&ends[1], d_in_ptr + n, sizeof(int64_t)), "read in_ptr");
-        TRY(rb.finish(), "sync");
+        void *h = nullptr, *d = nullptr;
+        TRY(dd::direct_buf(&h, &d), "alloc read-back buffer");
+        lo = static_cast<dd::LoadOut *>(h);
+        lo_dev = static_cast<dd::LoadOut *>(d);
     }
-    if (ends[0] != 0) { st = fail(DD_EINVAL, "in_ptr[0] != 0"); goto fail_out; }
-    E = ends[1];
-    if (E < 0 || E >= (int64_t(1) << 31)) { st = fail(DD_EINVAL, "edge count outside [0, 2^31)"); goto fail_out; }
-    if (E > 0 && !in_src) { st = fail(DD_EINVAL, "in_src is NULL"); goto fail_out; }
-    g->n_edges = E;
-    TRY(copy_in(&d_in_src, in_src, (size_t)E, s), "copy in_src");
-    TRY(copy_in(&d_ecls, edge_cls, (size_t)E, s), "copy edge_cls");
-    TRY(copy_in(&g->thread_prev, thread_prev, (size_t)n, s), "copy thread_prev");
-    TRY(copy_in(&g->thread_id, thread_id, (size_t)n, s), "copy thread_id");
-    TRY(copy_in(&g->dur, dur_ns, (size_t)n, s), "copy dur");
-    TRY(copy_in(&g->gap, gap_ns, (size_t)n, s), "copy gap");
-    TRY(copy_in(&g->cls, node_cls, (size_t)n, s), "copy node_cls");
-    TRY(copy_in(&succ, (const int32_t *)nullptr, (size_t)n, s), "alloc");
-    TRY(copy_in(&heads, (const int32_t *)nullptr, (size_t)n_threads, s), "alloc");
-    TRY(copy_in(&err, (const uint32_t *)nullptr, 2, s), "alloc");
-    TRY(copy_in(&stats, (const dd::LoadStats *)nullptr, 1, s), "alloc");
-    // the edge pass and the chain ranking clamp every index they follow, so
-    // the per-task errors are read together with theirs (invalid-input bits
-    // take precedence in map_err_bits)
-    if (n > 0) TRY(dd::launch_validate_nodes(g, d_in_ptr, succ, heads, err, stats, s), "validate");
-    if (n > 0) TRY(dd::launch_validate_edges(g, d_in_ptr, d_in_src, edge_cls ? d_ecls : nullptr, succ, err, s), "validate edges");
-    TRY(dd::dalloc_n(&g->rank, N1, s), "alloc rank");
-    TRY(dd::dalloc_n(&nxt, N1, s), "alloc");
-    TRY(dd::dalloc_n(&nxt2, N1, s), "alloc");
-    TRY(dd::dalloc_n(&rank2, N1, s), "alloc");
-    TRY(dd::dalloc_n(&cnt, N1, s), "alloc");
-    if (n > 0) TRY(dd::launch_rank_tiles(g, nxt, nxt2, rank2, cnt, err, s), "rank chains");
+    *lo = dd::LoadOut{};
+    TRY(dd::dalloc_n(&g->rank, N + 1, s), "alloc rank");
+    if (!g->shared) {
+        TRY(dd::dalloc_n(&g->thread_base, (size_t)n_threads + 1, s), "alloc");
+        TRY(dd::dalloc_n(&g->order, N + 1, s), "alloc");
+        TRY(dd::dalloc_n(&g->xin_ptr, N + 1, s), "alloc");
+    }
+    TRY(field(&g->thread_prev, thread_prev, &in.prev), "copy thread_prev");
+    TRY(field(&g->thread_id, thread_id, &in.tid), "copy thread_id");
+    TRY(field(&g->dur, dur_ns, &in.dur), "copy dur");
+    TRY(field(&g->gap, gap_ns, &in.gap), "copy gap");
+    TRY(field(&g->cls, node_cls, &in.cls), "copy node_cls");
     {
-        dd::ReadBack rb(s, sizeof(h_err2));
-        TRY(rb.add(h_err2, err, sizeof(h_err2)), "read err");
-        TRY(rb.finish(), "sync");
+        const bool there = on_device(in_ptr, sizeof(int64_t));
+        if (there && !g->shared) {
+            in.in_ptr = in_ptr;
+        } else {
+            TRY(copy_in(&d_in_ptr, in_ptr, N + 1, s), "copy in_ptr");
+            in.in_ptr = d_in_ptr;
+        }
+        if (n == 0) {
+            dd::ReadBack rb(s, sizeof(int64_t));
+            TRY(rb.add(&lo->ends[0], in.in_ptr, sizeof(int64_t)), "read in_ptr");
+            TRY(rb.finish(), "sync");
+            if (lo->ends[0] != 0) { st = fail(DD_EINVAL, "in_ptr[0] != 0"); goto fail_out; }
+            if (edges(0) != hipSuccess) goto fail_out;
+            if (!g->shared) {
+                TRY(hipMemsetAsync(g->xin_ptr, 0, sizeof(int64_t), s), "memset");
+                TRY(hipMemsetAsync(g->thread_base, 0, sizeof(int64_t) * ((size_t)n_threads + 1), s), "memset");
+            }
+            TRY(hipStreamSynchronize(s), "sync");
+        } else {
+            TRY(dd::load_device(g, in, -1, lo, lo_dev, s, edges), "load");
+            if (st != DD_OK) goto fail_out;
+        }
     }
-    if (h_err2[1] && !h_err2[0]) {
-        // more tile exits than one workgroup ranks: plain pointer jumping
-        TRY(dd::launch_rank_chains(g, succ, nxt, nxt2, rank2, err, s), "rank chains");
-        dd::ReadBack rb(s, sizeof(uint32_t));
-        TRY(rb.add(h_err2, err, sizeof(uint32_t)), "read err");
-        TRY(rb.finish(), "sync");
-    }
-    h_err = h_err2[0];
-    if (h_err) { st = map_err_bits(h_err); goto fail_out; }
+    if (lo->err[0]) { st = map_err_bits(lo->err[0]); goto fail_out; }
+    g->n_cross = lo->n_cross;
     if (g->shared) {
         // several chains per thread: no thread-major order and no dropped
         // edges; every dependency edge stays for the schedule-rule path
         g->xin_ptr = d_in_ptr; d_in_ptr = nullptr;
         g->xin_src = d_in_src; d_in_src = nullptr;
         g->xin_cls = d_ecls; d_ecls = nullptr;
-        g->n_cross = E;
-        dd::ReadBack rb(s, sizeof(hs));
-        TRY(rb.add(&hs, stats, sizeof(hs)), "read stats");
-        TRY(rb.finish(), "sync");
-    } else {
-        TRY(dd::dalloc_n(&g->thread_base, (size_t)n_threads + 1, s), "alloc");
-        TRY(dd::dalloc_n(&len, (size_t)n_threads + 1, s), "alloc");
-        TRY(dd::dalloc_n(&g->order, N1, s), "alloc");
-        TRY(dd::launch_build_order(g, succ, len, s), "order");
-        TRY(dd::dalloc_n(&g->xin_ptr, N1, s), "alloc");
-        if (n > 0) {
-            TRY(dd::launch_cross_edges(g, d_in_ptr, d_in_src, edge_cls ? d_ecls : nullptr, cnt, err, stats, s), "cross edges");
-        } else {
-            TRY(hipMemsetAsync(g->xin_ptr, 0, sizeof(int64_t), s), "memset");
-        }
-        // cross-edge lists sized by the edge count (an upper bound), so they are
-        // filled before the one read-back of the counts and error bits
-        TRY(dd::dalloc_n(&g->xin_src, (size_t)E + 1, s), "alloc");
-        TRY(dd::dalloc_n(&g->xin_cls, (size_t)E + 1, s), "alloc");
-        if (n > 0) TRY(dd::launch_cross_fill(g, d_in_ptr, d_in_src, edge_cls ? d_ecls : nullptr, s), "cross fill");
-        dd::ReadBack rb(s, sizeof(uint32_t) + sizeof(int64_t) + sizeof(hs));
-        TRY(rb.add(&h_err, err, sizeof(uint32_t)), "read err");
-        TRY(rb.add(&g->n_cross, g->xin_ptr + n, sizeof(int64_t)), "read");
-        TRY(rb.add(&hs, stats, sizeof(hs)), "read stats");
-        TRY(rb.finish(), "sync");
+        g->n_cross = g->n_edges;
     }
-    if (h_err) { st = map_err_bits(h_err); goto fail_out; }
-    g->dsum = ((__int128)hs.dsum_hi << 32) + (__int128)hs.dsum_lo;
     {
+        const dd::LoadStats hs = lo->st;
+        g->dsum = ((__int128)hs.dsum_hi << 32) + (__int128)hs.dsum_lo;
         const __int128 gs = ((__int128)hs.gsum_hi << 32) + (__int128)hs.gsum_lo;
         g->gsum = gs >= ((__int128)1 << 62) ? ((int64_t)1 << 62) : (int64_t)gs;
+        g->dmax = (int64_t)hs.dmax;
+        g->gmax = (int64_t)hs.gmax;
+        g->max_cls = (int32_t)hs.cls_max;
+        g->cross_mask = hs.cross_mask;
     }
-    g->dmax = (int64_t)hs.dmax;
-    g->gmax = (int64_t)hs.gmax;
-    g->max_cls = (int32_t)hs.cls_max;
-    g->cross_mask = hs.cross_mask;
     if (g->dsum + (__int128)g->gsum >= ((__int128)1 << 62)) {
         st = fail(DD_ERANGE, "sum of durations and gaps reaches 2^62 ns");
         goto fail_out;
     }
-    TRY(hipStreamSynchronize(s), "sync");
-    dd::dfree(d_in_ptr, s); dd::dfree(d_in_src, s); dd::dfree(d_ecls, s); dd::dfree(succ, s);
-    dd::dfree(heads, s); dd::dfree(err, s); dd::dfree(stats, s); dd::dfree(nxt, s);
-    dd::dfree(nxt2, s); dd::dfree(rank2, s); dd::dfree(cnt, s); dd::dfree(len, s);
+    dd::dfree(d_in_ptr, s); dd::dfree(d_in_src, s); dd::dfree(d_ecls, s);
     *out = g;
     return DD_OK;
 fail_out:
     (void)hipStreamSynchronize(s);
-    dd::dfree(d_in_ptr, s); dd::dfree(d_in_src, s); dd::dfree(d_ecls, s); dd::dfree(succ, s);
-    dd::dfree(heads, s); dd::dfree(err, s); dd::dfree(stats, s); dd::dfree(nxt, s);
-    dd::dfree(nxt2, s); dd::dfree(rank2, s); dd::dfree(cnt, s); dd::dfree(len, s);
+    dd::dfree(d_in_ptr, s); dd::dfree(d_in_src, s); dd::dfree(d_ecls, s);
     free_graph_arrays(g);
     delete g;
     return st;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <functional>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -47,7 +48,7 @@ struct alignas(16) ScaleEntry {
 // One schedule position as the simulation reads it: the task, its
 // duration, gap and class, and up to two of its gathers inline (source task,
 // the source's schedule position, edge class).  Gathers beyond two stay in
-// the gather arrays (gat_ptr[q] + 2 onwards).
+// the gather arrays (gat_rng).
 struct alignas(16) Rec {
     int64_t dur, gap;
     int32_t node, g0_src, g1_src, g0_spos;
@@ -162,12 +163,8 @@ struct dd_sched {
     hipStream_t stream = nullptr;
     int32_t *step_ptr = nullptr;  // [n_steps+1] position offsets
     int32_t *pos_node = nullptr;  // [n]
-    uint8_t *pos_flags = nullptr; // [n] bit0: first task of a thread run
-    int64_t *pos_dur = nullptr, *pos_gap = nullptr;
-    uint16_t *pos_cls = nullptr;
-    int64_t *gat_ptr = nullptr;   // [n+1] per position
+    uint64_t *gat_rng = nullptr;  // [n] gathers of each position: first entry | entries << 32
     int32_t *gat_src = nullptr;   // source task of each gather
-    int32_t *gat_pos = nullptr;   // position it feeds
     uint8_t *gat_cls = nullptr;   // edge class; 255 = always present (thread order)
     int64_t *gat_gap = nullptr;   // gap of the source task
     int32_t *gat_spos = nullptr;  // schedule position of the source task
@@ -245,27 +242,44 @@ inline int grid_for(int64_t n, int bs) {
     return (int)g;
 }
 
-// graph load kernels (k_graph.hip)
-hipError_t launch_validate_nodes(const dd_graph *g, const int64_t *in_ptr, int32_t *succ,
-                                 int32_t *heads, uint32_t *err, LoadStats *st, hipStream_t s);
-hipError_t launch_validate_edges(const dd_graph *g, const int64_t *in_ptr, const int32_t *in_src,
-                                 const uint8_t *edge_cls, const int32_t *succ, uint32_t *err,
-                                 hipStream_t s);
-hipError_t launch_rank_chains(const dd_graph *g, const int32_t *succ, int32_t *tmp_nxt,
-                              int32_t *tmp_nxt2, int32_t *tmp_rank2, uint32_t *err,
-                              hipStream_t s);
-hipError_t launch_build_order(const dd_graph *g, const int32_t *succ, int64_t *len_tmp,
-                              hipStream_t s);
-hipError_t launch_cross_edges(dd_graph *g, const int64_t *in_ptr, const int32_t *in_src,
-                              const uint8_t *edge_cls, int64_t *cnt_tmp, uint32_t *err,
-                              LoadStats *st, hipStream_t s);
-hipError_t launch_cross_fill(dd_graph *g, const int64_t *in_ptr, const int32_t *in_src,
-                             const uint8_t *edge_cls, hipStream_t s);
+// Results that kernels write straight into host memory (a pinned buffer per
+// host thread, kept until the process ends; read after the stream has been
+// waited for): no copy, and no launch for one.  *dev receives the address
+// kernels use.
+constexpr size_t kDirectBytes = 64 << 10;
+hipError_t direct_buf(void **host, void **dev);
+
+// Device passes that only the full library has: weak, so that the API layer
+// links (and its host-side checks run) without them.
+#define DD_PASS __attribute__((weak))
+
+// graph load (k_graph.hip)
+struct LoadIn {                   // the caller's arrays where kernels can read them
+    const int64_t *in_ptr = nullptr;
+    const int32_t *in_src = nullptr;
+    const uint8_t *ecls = nullptr;
+    const int32_t *prev = nullptr, *tid = nullptr;
+    const int64_t *dur = nullptr, *gap = nullptr;
+    const uint16_t *cls = nullptr;
+};
+struct LoadOut {
+    int64_t ends[2];              // in_ptr[0], in_ptr[n]
+    int64_t n_cross;
+    uint32_t err[2];
+    LoadStats st;
+};
+// All passes of a load with n > 0, complete on return.  E: the edge count, or
+// -1 when in_ptr is on the device; edges(E) (E = -1: in_ptr[0] != 0) then
+// checks it and provides in.in_src, in.ecls and the lists of g that it sizes,
+// or fails, and nothing more runs.  out: results (host memory, see direct_buf).
+DD_PASS hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, LoadOut *out_dev,
+                               hipStream_t s, const std::function<hipError_t(int64_t)> &edges);
 
 // levelization (k_levelize.hip)
 struct LevelizeOut {
     int64_t n_steps, n_segments, max_width, n_gathers;
-    uint32_t err;
+    uint32_t err, pad;
+    int32_t steps[kSplitMaxSteps + 1];   // step offsets, of at most kSplitMaxSteps steps
 };
 dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sched *sch,
                           hipStream_t s, char *msg, size_t msg_len);
@@ -307,11 +321,14 @@ hipError_t simulate_noalloc(const dd_graph *g, const dd_sched *sch, const dd_var
                             int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s,
                             size_t *need, size_t *limit);
 
-// one variant per workgroup (k_solo.hip): the most batches a schedule can
-// have, the batch list of a schedule, and the launch (hipErrorOutOfMemory
-// when its scratch, mostly V * kSoloRing * 8 bytes, cannot be had)
-int64_t solo_batch_max(int64_t n, int64_t nsteps);
-hipError_t launch_batches(dd_sched *sch, hipStream_t s);
+// one variant per workgroup (k_solo.hip): the most entries the batch list of
+// n positions can have (a wide step has at least kSoloNarrow + 1 positions and
+// ends a group of narrow ones; a group starts in each kSoloGroup-aligned
+// span), and the launch (hipErrorOutOfMemory when its scratch, mostly
+// V * kSoloRing * 8 bytes, cannot be had)
+inline int64_t solo_batch_max(int64_t n) {
+    return 2 * (n / kSoloNarrow) + n / kSoloPos + n / kSoloGroup + 8;
+}
 hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants *var,
                        int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s);
 

@@ -93,42 +93,83 @@ hipError_t scan_exclusive(const int64_t *in, int64_t *out, int64_t n, hipStream_
 }
 
 // ---------------------------------------------------------------------------
-// validation of per-task fields
+// The passes of dd_graph_load, in the order they run (load_device below):
+//   k_load_nodes   per task: copy the fields into the graph, check them, sum
+//                  the statistics, claim the thread predecessor;
+//   k_load_tiles   per tile of 1,024 tasks: check the in-edges, rank the
+//                  chains inside the tile;
+//   k_load_exits   one workgroup: rank the tile exits, lay out the threads;
+//   k_cross_count  ranks and order of all tasks, cross-thread edges per chunk;
+//   k_cross_fill   the cross-thread in-edge lists.
+// Small graphs are bound by the launches and host waits (a load was some 27
+// launches, 10 copies, 6 fills and 5 waits, 0.2 ms for 1,612 tasks), so every
+// pass does all that its inputs allow, nothing comes back to the host before
+// the end but the edge count, and results are written straight into the
+// pinned read-back buffer.  Large graphs: each pass is bound by HBM.
 namespace {
 constexpr int kBS = 256;
 
-constexpr int kValBlocks = 256;    // grid-stride blocks: one set of atomics per block
+constexpr int kValBlocks = 512;    // grid-stride blocks: one set of atomics per block
 
-__global__ __launch_bounds__(kBS) void k_validate_nodes(
-    int32_t n, int32_t T, const int32_t *__restrict__ prev, const int32_t *__restrict__ tid,
-    const int64_t *__restrict__ dur, const int64_t *__restrict__ gap,
-    const uint16_t *__restrict__ cls, const int64_t *__restrict__ in_ptr,
-    int32_t *__restrict__ succ, int32_t *__restrict__ heads, uint32_t *__restrict__ err,
-    LoadStats *__restrict__ st, bool one_head) {
+// what the passes share besides the graph
+struct LoadWork {
+    const int64_t *in_ptr;         // [n+1] dependency in-edges as given
+    const int32_t *in_src;
+    const uint8_t *ecls;           // null: all class 0
+    int32_t *succ;                 // [n] successor on the thread + 1 (zeroed)
+    int32_t *heads;                // [T] first tasks (zeroed)
+    int32_t *last;                 // [T] last task + 1 (zeroed)
+    int32_t *xslot;                // [n] number of a tile exit + 1 (zeroed)
+    uint32_t *err;                 // [2] error bits; more exits than one workgroup ranks (zeroed)
+    int32_t *xcount;               // [1] tile exits (zeroed)
+    LoadStats *st;                 // (zeroed)
+    int32_t *dloc, *ext;           // [n] distance to, and id of, the task the tile leaves by
+    int32_t *xlist, *xrank;        // [kRankXMax] the exits and their ranks
+    int64_t *csum;                 // [kChunks] cross-thread edges per chunk of tasks
+    LoadOut *out;                  // host memory
+};
+
+template <class T>
+__device__ __forceinline__ T take(const T *src, T *dst, int64_t u) {
+    const T x = src[u];
+    if (dst != src) dst[u] = x;
+    return x;
+}
+
+__global__ __launch_bounds__(kBS) void k_load_nodes(
+    int32_t n, int32_t T, const int32_t *s_prev, const int32_t *s_tid, const int64_t *s_dur,
+    const int64_t *s_gap, const uint16_t *s_cls, int32_t *prev, int32_t *tid, int64_t *dur,
+    int64_t *gap, uint16_t *cls, LoadWork w, bool one_head) {
     uint32_t e = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        w.out->ends[0] = w.in_ptr[0];
+        w.out->ends[1] = w.in_ptr[n];
+    }
     // sums split at bit 32 so that no partial sum can overflow
     int64_t dhi = 0, dlo = 0, ghi = 0, glo = 0, dm = 0, gm = 0, cm = 0;
     for (int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x; u < n;
          u += (int64_t)gridDim.x * kBS) {
-        const int32_t t = tid[u];
+        const int32_t t = take(s_tid, tid, u);
         const bool t_ok = t >= 0 && t < T;
         if (!t_ok) e |= ERR_THREAD_RANGE;
-        const int32_t p = prev[u];
+        const int32_t p = take(s_prev, prev, u);
         if (p < -1 || p >= n || p == u) {
             e |= ERR_PREV_RANGE;
         } else if (p >= 0) {
-            if (tid[p] != t) e |= ERR_PREV_THREAD;
-            else succ[p] = (int32_t)u + 1;   // one claimer wins; the others are found later
+            if (s_tid[p] != t) e |= ERR_PREV_THREAD;
+            else w.succ[p] = (int32_t)u + 1;   // one claimer wins; the others are found later
         } else if (t_ok && one_head) {
-            if (atomicAdd(&heads[t], 1) != 0) e |= ERR_HEADS;
+            if (atomicAdd(&w.heads[t], 1) != 0) e |= ERR_HEADS;
         }
-        int64_t d = dur[u], g = gap[u];
+        int64_t d = take(s_dur, dur, u), g = take(s_gap, gap, u);
         if (d < 0 || g < 0) e |= ERR_NEG_TIME;
         if (d >= kTimeLimit || g >= kTimeLimit) e |= ERR_BIG_TIME;
         if (d < 0 || d >= kTimeLimit) d = 0;
         if (g < 0 || g >= kTimeLimit) g = 0;
-        if (in_ptr[u + 1] < in_ptr[u]) e |= ERR_PTR_ORDER;
-        const int64_t c = cls ? cls[u] : 0;
+        if (w.in_ptr[u + 1] < w.in_ptr[u]) e |= ERR_PTR_ORDER;
+        int64_t c = 0;
+        if (s_cls) c = take(s_cls, cls, u);
+        else cls[u] = 0;
         dhi += d >> 32; dlo += d & 0xffffffffll;
         ghi += g >> 32; glo += g & 0xffffffffll;
         dm = d > dm ? d : dm;
@@ -142,10 +183,10 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(
     for (int o = 32; o > 0; o >>= 1) e |= (uint32_t)__shfl_xor((int)e, o, 64);
     constexpr int NW = kBS / 64;
     __shared__ int64_t red[8][NW];
-    const int w = threadIdx.x >> 6;
+    const int wv = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
-        red[0][w] = dhi; red[1][w] = dlo; red[2][w] = ghi; red[3][w] = glo;
-        red[4][w] = dm; red[5][w] = cm; red[6][w] = e; red[7][w] = gm;
+        red[0][wv] = dhi; red[1][wv] = dlo; red[2][wv] = ghi; red[3][wv] = glo;
+        red[4][wv] = dm; red[5][wv] = cm; red[6][wv] = e; red[7][wv] = gm;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -156,43 +197,15 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(
             e |= (uint32_t)red[6][i];
             gm = red[7][i] > gm ? red[7][i] : gm;
         }
-        if (dhi) atomicAdd(&st->dsum_hi, (unsigned long long)dhi);
-        if (dlo) atomicAdd(&st->dsum_lo, (unsigned long long)dlo);
-        if (ghi) atomicAdd(&st->gsum_hi, (unsigned long long)ghi);
-        if (glo) atomicAdd(&st->gsum_lo, (unsigned long long)glo);
-        atomic_max_hot(&st->dmax, (unsigned long long)dm);
-        atomic_max_hot(&st->gmax, (unsigned long long)gm);
-        atomic_max_hot(&st->cls_max, (unsigned long long)cm);
-        atomic_or_hot(err, e);
+        if (dhi) atomicAdd(&w.st->dsum_hi, (unsigned long long)dhi);
+        if (dlo) atomicAdd(&w.st->dsum_lo, (unsigned long long)dlo);
+        if (ghi) atomicAdd(&w.st->gsum_hi, (unsigned long long)ghi);
+        if (glo) atomicAdd(&w.st->gsum_lo, (unsigned long long)glo);
+        atomic_max_hot(&w.st->dmax, (unsigned long long)dm);
+        atomic_max_hot(&w.st->gmax, (unsigned long long)gm);
+        atomic_max_hot(&w.st->cls_max, (unsigned long long)cm);
+        atomic_or_hot(w.err, e);
     }
-}
-
-// (runs right after the per-task pass, before its errors are read, so every
-// index is clamped to its array; also reports a task named as previous task
-// by two tasks, which left only one of them in succ)
-__global__ __launch_bounds__(kBS) void k_validate_edges(int32_t n, int64_t E,
-                                                        const int64_t *__restrict__ in_ptr,
-                                                        const int32_t *__restrict__ in_src,
-                                                        const uint8_t *__restrict__ ecls,
-                                                        const int32_t *__restrict__ prev,
-                                                        const int32_t *__restrict__ succ,
-                                                        uint32_t *__restrict__ err) {
-    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    uint32_t e = 0;
-    if (u < n) {
-        const int32_t p = prev[u];
-        if (p >= 0 && p < n && succ[p] != (int32_t)u + 1) e |= ERR_SUCC;
-        const int64_t k0 = in_ptr[u] > 0 ? in_ptr[u] : 0;
-        const int64_t k1 = in_ptr[u + 1] < E ? in_ptr[u + 1] : E;
-        for (int64_t k = k0; k < k1; k++) {
-            const int32_t s = in_src[k];
-            if (s < 0 || s >= n) e |= ERR_SRC_RANGE;
-            else if (s == u) e |= ERR_SELF_LOOP;
-            if (ecls && ecls[k] >= 64) e |= ERR_EDGE_CLS;
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) e |= (uint32_t)__shfl_xor((int)e, o, 64);
-    if ((threadIdx.x & 63) == 0 && e) atomicOr(err, e);
 }
 
 // pointer jumping (Wyllie): rank = number of predecessors on the thread
@@ -237,17 +250,20 @@ __global__ __launch_bounds__(kBS) void k_rank_check(int32_t n, const int32_t *__
 // d (predecessors up to and including the first one outside the tile) and
 // e (that outside task, -1 if the chain starts in the tile), so that
 // rank(u) = d + rank(e).  The outside tasks named as e (the tile exits) are
-// then ranked by one workgroup, again by pointer jumping in LDS, and every
-// task adds its exit's rank.  A thread order that loops inside a tile or
-// across exits is reported like the plain pointer jumping does.
+// numbered by the one task of each chain that leaves its tile and ranked by
+// one workgroup, again by pointer jumping in LDS.  A thread order that loops
+// inside a tile or across exits is reported like the plain pointer jumping
+// does.
 constexpr int kRankTile = 1024;
 constexpr int kRankXMax = 8192;     // tile exits ranked in LDS at most
+constexpr int kChunks = 1024;       // chunks of tasks that the cross-edge lists are cut into
 
-__global__ __launch_bounds__(kRankTile) void k_rank_tile(int32_t n, const int32_t *__restrict__ prev,
-                                                         int32_t *__restrict__ dloc,
-                                                         int32_t *__restrict__ ext,
-                                                         int64_t *__restrict__ xflag,
-                                                         uint32_t *__restrict__ err) {
+// (every index is clamped to its array: the errors of k_load_nodes have not
+// been read; also reports a task named as previous task by two tasks, which
+// left only one of them in succ)
+__global__ __launch_bounds__(kRankTile) void k_load_tiles(int32_t n, int32_t T, int64_t E,
+                                                          const int32_t *__restrict__ prev,
+                                                          const int32_t *__restrict__ tid, LoadWork w) {
     __shared__ int32_t sn[2][kRankTile], sd[2][kRankTile], se[2][kRankTile];
     const int64_t b0 = (int64_t)blockIdx.x * kRankTile;
     const int i = threadIdx.x;
@@ -255,10 +271,33 @@ __global__ __launch_bounds__(kRankTile) void k_rank_tile(int32_t n, const int32_
     const bool ok = u < n;
     int32_t p = ok ? prev[u] : -1;
     if (p < -1 || p >= n || p == u) p = -1;   // reported by the per-task pass
+    uint32_t er = 0;
+    if (ok) {
+        if (p >= 0 && w.succ[p] != (int32_t)u + 1) er |= ERR_SUCC;
+        const int32_t t = tid[u];
+        if (w.succ[u] == 0 && t >= 0 && t < T) w.last[t] = (int32_t)u + 1;
+        const int64_t k0 = w.in_ptr[u] > 0 ? w.in_ptr[u] : 0;
+        const int64_t k1 = w.in_ptr[u + 1] < E ? w.in_ptr[u + 1] : E;
+        for (int64_t k = k0; k < k1; k++) {
+            const int32_t s = w.in_src[k];
+            if (s < 0 || s >= n) er |= ERR_SRC_RANGE;
+            else if (s == u) er |= ERR_SELF_LOOP;
+            if (w.ecls && w.ecls[k] >= 64) er |= ERR_EDGE_CLS;
+        }
+    }
     const bool in = p >= b0 && p < b0 + kRankTile && p < n;
     int nn = in ? (int)(p - b0) : -1;
     int d = p >= 0 ? 1 : 0;
     int e = in ? -1 : p;
+    if (p >= 0 && !in && atomicCAS(&w.xslot[p], 0, -1) == 0) {
+        const int x = atomicAdd(w.xcount, 1);
+        if (x < kRankXMax) {
+            w.xlist[x] = p;
+            w.xslot[p] = x + 1;
+        } else {
+            w.err[1] = 1u;
+        }
+    }
     int buf = 0;
     sn[0][i] = nn; sd[0][i] = d; se[0][i] = e;
     __syncthreads();
@@ -271,194 +310,203 @@ __global__ __launch_bounds__(kRankTile) void k_rank_tile(int32_t n, const int32_
         }
         buf ^= 1;
         sn[buf][i] = nn; sd[buf][i] = d; se[buf][i] = e;
-        __syncthreads();
+        if (!__syncthreads_or(nn >= 0)) break;
     }
-    if (__any(ok && nn >= 0) && (i & 63) == 0) atomicOr(err, ERR_CHAIN_CYCLE);
+    if (ok && nn >= 0) er |= ERR_CHAIN_CYCLE;
     if (ok) {
-        dloc[u] = d;
-        ext[u] = e;
-        if (e >= 0) xflag[e] = 1;
+        w.dloc[u] = d;
+        w.ext[u] = e;
     }
+    for (int o = 32; o > 0; o >>= 1) er |= (uint32_t)__shfl_xor((int)er, o, 64);
+    if ((i & 63) == 0 && er) atomicOr(w.err, er);
 }
 
-__global__ __launch_bounds__(kBS) void k_rank_xlist(int32_t n, const int64_t *__restrict__ xidx,
-                                                    int32_t *__restrict__ xlist) {
-    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (u < n && xidx[u + 1] != xidx[u]) xlist[xidx[u]] = (int32_t)u;
+__device__ __forceinline__ void report(const LoadWork &w) {
+    w.out->err[0] = load_coherent(&w.err[0]);
+    w.out->err[1] = load_coherent(&w.err[1]);
+    w.out->st = *w.st;
 }
 
-// ranks of the tile exits (one workgroup); err[1] is set when there are more
-// than kRankXMax of them (the caller then ranks by plain pointer jumping)
-__global__ __launch_bounds__(1024) void k_rank_exits(int32_t n, const int64_t *__restrict__ xidx,
-                                                     const int32_t *__restrict__ xlist,
-                                                     const int32_t *__restrict__ dloc,
-                                                     const int32_t *__restrict__ ext,
-                                                     int32_t *__restrict__ rank,
-                                                     uint32_t *__restrict__ err) {
+// one workgroup: the ranks of the tile exits, then where each thread starts
+// in the order (base == null: shared threads have none; then this is the last
+// pass and it reports)
+__global__ __launch_bounds__(1024) void k_load_exits(int32_t T, int64_t *__restrict__ base, LoadWork w) {
     __shared__ int32_t sn[2][kRankXMax], sd[2][kRankXMax];
-    const int64_t nx = xidx[n];
-    if (nx > kRankXMax) {
-        if (threadIdx.x == 0) err[1] = 1u;
-        return;
-    }
-    constexpr int PER = kRankXMax / 1024;
-    int nn[PER], d[PER];
-#pragma unroll
-    for (int k = 0; k < PER; k++) {
-        const int x = threadIdx.x + k * 1024;
-        nn[k] = -1; d[k] = 0;
-        if (x < nx) {
-            const int32_t u = xlist[x];
-            const int32_t e = ext[u];
-            d[k] = dloc[u];
-            nn[k] = e >= 0 ? (int)xidx[e] : -1;
-        }
-        sn[0][x] = nn[k]; sd[0][x] = d[k];
-    }
-    __syncthreads();
-    int buf = 0;
-    for (int it = 0; it < 14; it++) {        // 2^13 = kRankXMax: every exit chain ends
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            if (nn[k] >= 0) {
-                const int j = nn[k];
-                d[k] += sd[buf][j];
-                nn[k] = sn[buf][j];
-            }
-        }
-        buf ^= 1;
+    const int nx = *w.xcount;
+    if (w.err[0] == 0u && nx <= kRankXMax) {
+        constexpr int PER = kRankXMax / 1024;
+        int nn[PER], d[PER];
 #pragma unroll
         for (int k = 0; k < PER; k++) {
             const int x = threadIdx.x + k * 1024;
-            sn[buf][x] = nn[k]; sd[buf][x] = d[k];
-        }
-        __syncthreads();
-    }
-    bool bad = false;
-#pragma unroll
-    for (int k = 0; k < PER; k++) {
-        const int x = threadIdx.x + k * 1024;
-        bad |= x < nx && nn[k] >= 0;
-        if (x < nx) rank[xlist[x]] = d[k];
-    }
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(err, ERR_CHAIN_CYCLE);
-}
-
-__global__ __launch_bounds__(kBS) void k_rank_final(int32_t n, const int32_t *__restrict__ dloc,
-                                                    const int32_t *__restrict__ ext,
-                                                    const int64_t *__restrict__ xidx,
-                                                    int32_t *__restrict__ rank) {
-    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (u >= n || xidx[u + 1] != xidx[u]) return;   // exits hold their rank already
-    const int32_t e = ext[u];
-    rank[u] = dloc[u] + (e >= 0 ? rank[e] : 0);
-}
-
-__global__ __launch_bounds__(kBS) void k_thread_len(int32_t n, const int32_t *__restrict__ succ,
-                                                    const int32_t *__restrict__ tid,
-                                                    const int32_t *__restrict__ rank,
-                                                    int64_t *__restrict__ len) {
-    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (u < n && succ[u] == 0) len[tid[u]] = (int64_t)rank[u] + 1;   // last task of its thread (no successor)
-}
-
-__global__ __launch_bounds__(kBS) void k_order(int32_t n, const int32_t *__restrict__ tid,
-                                               const int32_t *__restrict__ rank,
-                                               const int64_t *__restrict__ base,
-                                               int32_t *__restrict__ order) {
-    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (u < n) order[base[tid[u]] + rank[u]] = (int32_t)u;
-}
-
-// same-thread dependencies: must point forward; dropped.  Cross-thread: counted.
-__global__ __launch_bounds__(kBS) void k_cross_count(
-    int32_t n, const int64_t *__restrict__ in_ptr, const int32_t *__restrict__ in_src,
-    const uint8_t *__restrict__ ecls, const int32_t *__restrict__ tid,
-    const int32_t *__restrict__ rank, int64_t *__restrict__ cnt, uint32_t *__restrict__ err,
-    LoadStats *__restrict__ st) {
-    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    uint32_t e = 0;
-    uint64_t mask = 0;
-    if (u < n) {
-        int64_t c = 0;
-        const int32_t tu = tid[u];
-        for (int64_t k = in_ptr[u]; k < in_ptr[u + 1]; k++) {
-            const int32_t s = in_src[k];
-            if (tid[s] == tu) {
-                if (rank[s] >= rank[u]) e |= ERR_BACK_EDGE;
-            } else {
-                c++;
-                mask |= 1ull << (ecls ? ecls[k] : 0);
+            nn[k] = -1; d[k] = 0;
+            if (x < nx) {
+                const int32_t u = w.xlist[x];
+                const int32_t e = w.ext[u];
+                d[k] = w.dloc[u];
+                nn[k] = e >= 0 ? w.xslot[e] - 1 : -1;
+                sn[0][x] = nn[k]; sd[0][x] = d[k];
             }
         }
-        cnt[u] = c;
+        __syncthreads();
+        int buf = 0;
+        bool open = false;
+        for (int it = 0; it < 14; it++) {        // 2^13 = kRankXMax: every exit chain ends
+            open = false;
+#pragma unroll
+            for (int k = 0; k < PER; k++) {
+                if (nn[k] >= 0) {
+                    const int j = nn[k];
+                    d[k] += sd[buf][j];
+                    nn[k] = sn[buf][j];
+                    open |= nn[k] >= 0;
+                }
+            }
+            buf ^= 1;
+#pragma unroll
+            for (int k = 0; k < PER; k++) {
+                const int x = threadIdx.x + k * 1024;
+                if (x < nx) { sn[buf][x] = nn[k]; sd[buf][x] = d[k]; }
+            }
+            if (!__syncthreads_or(open)) break;
+        }
+        if (__any(open) && (threadIdx.x & 63) == 0) atomicOr(w.err, ERR_CHAIN_CYCLE);
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            const int x = threadIdx.x + k * 1024;
+            if (x < nx) w.xrank[x] = d[k];
+        }
+        __syncthreads();
+        if (base) {
+            int64_t carry = 0;
+            for (int64_t t0 = 0; t0 < T; t0 += 1024) {
+                const int64_t t = t0 + threadIdx.x;
+                const int32_t u = t < T ? w.last[t] - 1 : -1;
+                int64_t len = 0;
+                if (u >= 0) len = (int64_t)w.dloc[u] + (w.ext[u] >= 0 ? w.xrank[w.xslot[w.ext[u]] - 1] : 0) + 1;
+                int64_t tot;
+                const int64_t ex = block_excl_scan<1024>(len, &tot);
+                if (t < T) base[t] = carry + ex;
+                carry += tot;
+            }
+            if (threadIdx.x == 0) base[T] = carry;
+        }
     }
+    __syncthreads();
+    if (!base && threadIdx.x == 0) report(w);
+}
+
+// thread starts when the ranks are known (graphs with more tile exits)
+__global__ __launch_bounds__(1024) void k_thread_base(int32_t T, const int32_t *__restrict__ last,
+                                                      const int32_t *__restrict__ rank,
+                                                      int64_t *__restrict__ base) {
+    int64_t carry = 0;
+    for (int64_t t0 = 0; t0 < T; t0 += 1024) {
+        const int64_t t = t0 + threadIdx.x;
+        const int32_t u = t < T ? last[t] - 1 : -1;
+        const int64_t len = u >= 0 ? (int64_t)rank[u] + 1 : 0;
+        int64_t tot;
+        const int64_t ex = block_excl_scan<1024>(len, &tot);
+        if (t < T) base[t] = carry + ex;
+        carry += tot;
+    }
+    if (threadIdx.x == 0) base[T] = carry;
+}
+
+// ranks and order of the tasks; same-thread dependencies must point forward
+// (dropped), cross-thread ones are counted, per chunk of tasks
+template <bool RANKED>
+__global__ __launch_bounds__(kBS) void k_cross_count(int32_t n, int64_t chunk,
+                                                     const int32_t *__restrict__ tid,
+                                                     const int64_t *__restrict__ base, int32_t *rank,
+                                                     int32_t *__restrict__ order, LoadWork w) {
+    if (w.err[0] | (RANKED ? 0u : w.err[1])) return;
+    uint32_t e = 0;
+    uint64_t mask = 0;
+    int64_t c = 0;
+    auto rank_of = [&](int32_t u) -> int32_t {
+        if (RANKED) return rank[u];
+        const int32_t x = w.ext[u];
+        return w.dloc[u] + (x >= 0 ? w.xrank[w.xslot[x] - 1] : 0);
+    };
+    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    for (int64_t u = lo + threadIdx.x; u < hi; u += kBS) {
+        const int32_t tu = tid[u], ru = rank_of((int32_t)u);
+        if (!RANKED) rank[u] = ru;
+        order[base[tu] + ru] = (int32_t)u;
+        for (int64_t k = w.in_ptr[u]; k < w.in_ptr[u + 1]; k++) {
+            const int32_t s = w.in_src[k];
+            if (tid[s] == tu) {
+                if (rank_of(s) >= ru) e |= ERR_BACK_EDGE;
+            } else {
+                c++;
+                mask |= 1ull << (w.ecls ? w.ecls[k] : 0);
+            }
+        }
+    }
+    c = wave_sum64(c);
     for (int o = 32; o > 0; o >>= 1) {
         e |= (uint32_t)__shfl_xor((int)e, o, 64);
         mask |= (uint64_t)shfl_xor64((int64_t)mask, o);
     }
+    __shared__ int64_t part[kBS / 64];
     if ((threadIdx.x & 63) == 0) {
-        atomic_or_hot(err, e);
-        atomic_or_hot(&st->cross_mask, (unsigned long long)mask);
+        part[threadIdx.x >> 6] = c;
+        atomic_or_hot(w.err, e);
+        atomic_or_hot(&w.st->cross_mask, (unsigned long long)mask);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kBS / 64; i++) c += part[i];
+        w.csum[blockIdx.x] = c;
     }
 }
 
-__global__ __launch_bounds__(kBS) void k_cross_fill(
-    int32_t n, const int64_t *__restrict__ in_ptr, const int32_t *__restrict__ in_src,
-    const uint8_t *__restrict__ ecls, const int32_t *__restrict__ tid,
-    const int64_t *__restrict__ xptr, int32_t *__restrict__ xsrc, uint8_t *__restrict__ xcls) {
-    const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (u >= n) return;
-    int64_t o = xptr[u];
-    const int32_t tu = tid[u];
-    for (int64_t k = in_ptr[u]; k < in_ptr[u + 1]; k++) {
-        const int32_t s = in_src[k];
-        if (tid[s] != tu) {
-            xsrc[o] = s;
-            xcls[o] = ecls ? ecls[k] : 0;
-            o++;
+// each chunk starts after the edges of the chunks before it, whose counts
+// (at most kChunks) every workgroup sums itself
+__global__ __launch_bounds__(kBS) void k_cross_fill(int32_t n, int64_t chunk,
+                                                    const int32_t *__restrict__ tid,
+                                                    int64_t *__restrict__ xptr, int32_t *__restrict__ xsrc,
+                                                    uint8_t *__restrict__ xcls, LoadWork w) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) report(w);
+    if (w.err[0] | w.err[1]) return;
+    int64_t before = 0, tot;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBS) before += w.csum[i];
+    (void)block_excl_scan<kBS>(before, &tot);
+    int64_t at = tot;
+    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    for (int64_t b = lo; b < hi; b += kBS) {
+        const int64_t u = b + threadIdx.x;
+        int64_t c = 0, k0 = 0, k1 = 0;
+        int32_t tu = 0;
+        if (u < hi) {
+            tu = tid[u];
+            k0 = w.in_ptr[u];
+            k1 = w.in_ptr[u + 1];
+            for (int64_t k = k0; k < k1; k++) c += tid[w.in_src[k]] != tu;
+        }
+        int64_t o = at + block_excl_scan<kBS>(c, &tot);
+        at += tot;
+        if (u < hi) {
+            xptr[u] = o;
+            for (int64_t k = k0; k < k1; k++) {
+                const int32_t s = w.in_src[k];
+                if (tid[s] != tu) {
+                    xsrc[o] = s;
+                    xcls[o] = w.ecls ? w.ecls[k] : 0;
+                    o++;
+                }
+            }
         }
     }
-}
-}  // namespace
-
-hipError_t launch_validate_nodes(const dd_graph *g, const int64_t *in_ptr, int32_t *succ,
-                                 int32_t *heads, uint32_t *err, LoadStats *st, hipStream_t s) {
-    int blocks = grid_for(g->n, kBS);
-    if (blocks > kValBlocks) blocks = kValBlocks;
-    k_validate_nodes<<<blocks, kBS, 0, s>>>(g->n, g->n_threads, g->thread_prev,
-                                                         g->thread_id, g->dur, g->gap, g->cls,
-                                                         in_ptr, succ, heads, err, st,
-                                                         !g->shared);
-    return hipGetLastError();
+    if (hi == n && threadIdx.x == 0) {
+        xptr[n] = at;
+        w.out->n_cross = at;
+    }
 }
 
-hipError_t launch_validate_edges(const dd_graph *g, const int64_t *in_ptr, const int32_t *in_src,
-                                 const uint8_t *edge_cls, const int32_t *succ, uint32_t *err,
-                                 hipStream_t s) {
-    k_validate_edges<<<grid_for(g->n, kBS), kBS, 0, s>>>(g->n, g->n_edges, in_ptr, in_src, edge_cls,
-                                                         g->thread_prev, succ, err);
-    return hipGetLastError();
-}
-
-hipError_t launch_rank_tiles(const dd_graph *g, int32_t *dloc, int32_t *ext, int32_t *xlist,
-                             int64_t *xidx, uint32_t *err, hipStream_t s) {
-    const int32_t n = g->n;
-    hipError_t e = hipMemsetAsync(xidx, 0, sizeof(int64_t) * ((size_t)n + 1), s);
-    if (e != hipSuccess) return e;
-    k_rank_tile<<<(unsigned)((n + kRankTile - 1) / kRankTile), kRankTile, 0, s>>>(n, g->thread_prev,
-                                                                               dloc, ext, xidx, err);
-    e = scan_exclusive(xidx, xidx, n, s);
-    if (e != hipSuccess) return e;
-    k_rank_xlist<<<grid_for(n, kBS), kBS, 0, s>>>(n, xidx, xlist);
-    k_rank_exits<<<1, 1024, 0, s>>>(n, xidx, xlist, dloc, ext, g->rank, err);
-    k_rank_final<<<grid_for(n, kBS), kBS, 0, s>>>(n, dloc, ext, xidx, g->rank);
-    return hipGetLastError();
-}
-
-hipError_t launch_rank_chains(const dd_graph *g, const int32_t *succ, int32_t *nxt,
-                              int32_t *nxt2, int32_t *rank2, uint32_t *err, hipStream_t s) {
-    (void)succ;
+void rank_chains(const dd_graph *g, int32_t *nxt, int32_t *nxt2, int32_t *rank2, uint32_t *err,
+                 hipStream_t s) {
     const int32_t n = g->n;
     int gr = grid_for(n, kBS);
     k_rank_init<<<gr, kBS, 0, s>>>(n, g->thread_prev, nxt, g->rank);
@@ -474,36 +522,89 @@ hipError_t launch_rank_chains(const dd_graph *g, const int32_t *succ, int32_t *n
     if (a_r != g->rank) (void)hipMemcpyAsync(g->rank, a_r, sizeof(int32_t) * (size_t)n,
                                        hipMemcpyDeviceToDevice, s);
     k_rank_check<<<gr, kBS, 0, s>>>(n, a_n, err);
-    return hipGetLastError();
 }
+}  // namespace
 
-hipError_t launch_build_order(const dd_graph *g, const int32_t *succ, int64_t *len,
-                              hipStream_t s) {
-    const int32_t n = g->n;
-    (void)hipMemsetAsync(len, 0, sizeof(int64_t) * ((size_t)g->n_threads + 1), s);
-    k_thread_len<<<grid_for(n, kBS), kBS, 0, s>>>(n, succ, g->thread_id, g->rank, len);
-    hipError_t e = scan_exclusive(len, g->thread_base, g->n_threads, s);
+hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, LoadOut *out_dev,
+                       hipStream_t s, const std::function<hipError_t(int64_t)> &edges) {
+    const int32_t n = g->n, T = g->n_threads;
+    // one block of working memory, the part that starts at zero first
+    size_t off = 0;
+    auto put = [&](size_t bytes) {
+        const size_t at = off;
+        off = (off + bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t N4 = sizeof(int32_t) * (size_t)n, T4 = sizeof(int32_t) * (size_t)T;
+    const size_t o_succ = put(N4), o_heads = put(T4), o_last = put(T4), o_xslot = put(N4),
+                 o_err = put(8), o_xcount = put(4), o_st = put(sizeof(LoadStats));
+    const size_t zero = off;
+    const size_t o_dloc = put(N4), o_ext = put(N4), o_xlist = put(4 * kRankXMax),
+                 o_xrank = put(4 * kRankXMax), o_csum = put(8 * kChunks);
+    char *m = nullptr;
+    hipError_t e = dalloc(reinterpret_cast<void **>(&m), off, s);
     if (e != hipSuccess) return e;
-    k_order<<<grid_for(n, kBS), kBS, 0, s>>>(n, g->thread_id, g->rank, g->thread_base, g->order);
-    return hipGetLastError();
-}
-
-hipError_t launch_cross_edges(dd_graph *g, const int64_t *in_ptr, const int32_t *in_src,
-                              const uint8_t *edge_cls, int64_t *cnt, uint32_t *err, LoadStats *st,
-                              hipStream_t s) {
-    k_cross_count<<<grid_for(g->n, kBS), kBS, 0, s>>>(g->n, in_ptr, in_src, edge_cls,
-                                                      g->thread_id, g->rank, cnt, err, st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return scan_exclusive(cnt, g->xin_ptr, g->n, s);
-}
-
-hipError_t launch_cross_fill(dd_graph *g, const int64_t *in_ptr, const int32_t *in_src,
-                             const uint8_t *edge_cls, hipStream_t s) {
-    k_cross_fill<<<grid_for(g->n, kBS), kBS, 0, s>>>(g->n, in_ptr, in_src, edge_cls,
-                                                     g->thread_id, g->xin_ptr, g->xin_src,
-                                                     g->xin_cls);
-    return hipGetLastError();
+    LoadWork w{in.in_ptr, in.in_src, in.ecls, (int32_t *)(m + o_succ), (int32_t *)(m + o_heads),
+               (int32_t *)(m + o_last), (int32_t *)(m + o_xslot), (uint32_t *)(m + o_err),
+               (int32_t *)(m + o_xcount), (LoadStats *)(m + o_st), (int32_t *)(m + o_dloc),
+               (int32_t *)(m + o_ext), (int32_t *)(m + o_xlist), (int32_t *)(m + o_xrank),
+               (int64_t *)(m + o_csum), out_dev};
+    *out = LoadOut{};
+    int32_t *nxt = nullptr, *nxt2 = nullptr, *rank2 = nullptr;
+    const int64_t chunk = ((n + kChunks - 1) / kChunks + kBS - 1) / kBS * kBS;
+    const unsigned nc = (unsigned)((n + chunk - 1) / chunk);
+    const unsigned nv = (unsigned)(grid_for(n, kBS) < kValBlocks ? grid_for(n, kBS) : kValBlocks);
+#define LD(x) do { if (e == hipSuccess) e = (x); } while (0)
+    LD(hipMemsetAsync(m, 0, zero, s));
+    if (e == hipSuccess)
+        k_load_nodes<<<nv, kBS, 0, s>>>(n, T, in.prev, in.tid, in.dur, in.gap, in.cls, g->thread_prev,
+                                        g->thread_id, g->dur, g->gap, g->cls, w, !g->shared);
+    LD(hipGetLastError());
+    if (E < 0) {                               // in_ptr is on the device: its ends come back first
+        LD(hipStreamSynchronize(s));
+        E = out->ends[0] != 0 ? -1 : out->ends[1];
+    }
+    if (e == hipSuccess && edges(E) == hipSuccess) {
+        w.in_src = in.in_src;
+        w.ecls = in.ecls;
+        k_load_tiles<<<(unsigned)((n + kRankTile - 1) / kRankTile), kRankTile, 0, s>>>(n, T, E, g->thread_prev,
+                                                                                     g->thread_id, w);
+        k_load_exits<<<1, 1024, 0, s>>>(T, g->shared ? nullptr : g->thread_base, w);
+        if (!g->shared) {
+            k_cross_count<false><<<nc, kBS, 0, s>>>(n, chunk, g->thread_id, g->thread_base, g->rank, g->order, w);
+            k_cross_fill<<<nc, kBS, 0, s>>>(n, chunk, g->thread_id, g->xin_ptr, g->xin_src, g->xin_cls, w);
+        }
+        LD(hipGetLastError());
+        LD(hipStreamSynchronize(s));
+        if (e == hipSuccess && out->err[1] && !out->err[0]) {
+            // more tile exits than one workgroup ranks: plain pointer jumping
+            LD(dalloc_n(&nxt, (size_t)n, s));
+            LD(dalloc_n(&nxt2, (size_t)n, s));
+            LD(dalloc_n(&rank2, (size_t)n, s));
+            LD(hipMemsetAsync(w.err, 0, 8, s));
+            if (e == hipSuccess) {
+                rank_chains(g, nxt, nxt2, rank2, w.err, s);
+                if (g->shared) {
+                    ReadBack rb(s, sizeof(uint32_t));
+                    LD(rb.add(&out->err[0], w.err, sizeof(uint32_t)));
+                    LD(rb.finish());
+                } else {
+                    k_thread_base<<<1, 1024, 0, s>>>(T, w.last, g->rank, g->thread_base);
+                    k_cross_count<true><<<nc, kBS, 0, s>>>(n, chunk, g->thread_id, g->thread_base, g->rank, g->order, w);
+                    k_cross_fill<<<nc, kBS, 0, s>>>(n, chunk, g->thread_id, g->xin_ptr, g->xin_src, g->xin_cls, w);
+                    LD(hipGetLastError());
+                    LD(hipStreamSynchronize(s));
+                }
+            }
+        }
+    }
+#undef LD
+    if (e != hipSuccess) (void)hipStreamSynchronize(s);
+    dfree(m, s);
+    dfree(nxt, s);
+    dfree(nxt2, s);
+    dfree(rank2, s);
+    return e;
 }
 
 }  // namespace dd

@@ -25,8 +25,11 @@
 
 #include "dd_common.h"
 #include "dd_internal.h"
+#include "dd_batches.h"
 
+#include <stddef.h>
 #include <stdio.h>
+#include <string.h>
 
 namespace dd {
 namespace {
@@ -46,17 +49,37 @@ struct Req {
 
 __device__ __forceinline__ bool on(uint64_t mask, uint8_t c) { return (mask >> c) & 1ull; }
 
-// per order position: number of active cross-thread parents
-__global__ __launch_bounds__(kBS) void k_req_count(int32_t n, Req r, uint64_t mask,
-                                                   int64_t *__restrict__ cnt,
-                                                   int64_t *__restrict__ flag) {
-    const int64_t p = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (p >= n) return;
-    const int32_t u = r.order[p];
-    int64_t c = 0;
-    for (int64_t k = r.xin_ptr[u]; k < r.xin_ptr[u + 1]; k++) c += on(mask, r.xin_cls[k]);
-    cnt[p] = c;
-    flag[p] = c > 0;
+constexpr int kChunks = 1024;      // chunks of order positions in the candidate passes
+
+// small results of the passes (device memory, cleared by the first of them)
+struct LevWork {
+    int64_t result[2];             // steps, segments
+    int64_t reqs;                  // active cross-thread dependencies
+    unsigned long long gctr;       // gather entries handed out
+    uint32_t err, pad;
+};
+
+// per chunk of order positions: candidates (positions with an active
+// cross-thread parent) << 32 | active cross-thread parents
+__global__ __launch_bounds__(kBS) void k_req_count(int32_t n, int64_t chunk, Req r, uint64_t mask,
+                                                   int64_t *__restrict__ csum, LevWork *__restrict__ lw) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *lw = LevWork{};
+    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    int64_t sum = 0;
+    for (int64_t p = lo + threadIdx.x; p < hi; p += kBS) {
+        const int32_t u = r.order[p];
+        int64_t c = 0;
+        for (int64_t k = r.xin_ptr[u]; k < r.xin_ptr[u + 1]; k++) c += on(mask, r.xin_cls[k]);
+        sum += c ? ((int64_t)1 << 32) | c : 0;
+    }
+    sum = wave_sum64(sum);
+    __shared__ int64_t part[kBS / 64];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kBS / 64; i++) sum += part[i];
+        csum[blockIdx.x] = sum;
+    }
 }
 
 constexpr int kWinT = 16;               // graph threads of the windowed rounds at most
@@ -77,79 +100,127 @@ struct alignas(16) CandEnt {
 // threads by id; T <= kEntT: the first two met in the list, which serves
 // the same test)
 constexpr int kEntT = 255;              // graph threads a packed entry can name (8 bits)
-__global__ __launch_bounds__(kBS) void k_req_fill(int32_t n, int32_t T, Req r, uint64_t mask,
-                                                  const int64_t *__restrict__ cidx,
-                                                  const int64_t *__restrict__ rptr_by_pos,
+// (each chunk starts after the chunks before it, whose counts every workgroup
+// sums itself; also closes the lists: cidx[n] = C, req_ptr[C] = R)
+__global__ __launch_bounds__(kBS) void k_req_fill(int32_t n, int32_t T, int64_t chunk, Req r, uint64_t mask,
+                                                  const int64_t *__restrict__ csum,
+                                                  int32_t *__restrict__ cidx,
                                                   int64_t *__restrict__ cand_pos,
                                                   int64_t *__restrict__ req_ptr,
                                                   int32_t *__restrict__ req_chain,
                                                   int64_t *__restrict__ req_gpos,
-                                                  CandEnt *__restrict__ pent) {
-    const int64_t p = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (p >= n) return;
-    if (cidx[p + 1] == cidx[p]) return;
-    const int64_t i = cidx[p];
-    cand_pos[i] = p;
-    int64_t o = rptr_by_pos[p];
-    req_ptr[i] = o;
-    const int32_t u = r.order[p];
-    int32_t mx[kWinT];                  // largest requirement per parent thread (-1: none)
+                                                  CandEnt *__restrict__ pent, LevWork *__restrict__ lw) {
+    int64_t before = 0, tot;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBS) before += csum[i];
+    (void)block_excl_scan<kBS>(before, &tot);
+    int64_t at = tot;
+    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    for (int64_t b = lo; b < hi; b += kBS) {
+        const int64_t p = b + threadIdx.x;
+        int32_t u = 0;
+        int64_t c = 0, k0 = 0, k1 = 0;
+        if (p < hi) {
+            u = r.order[p];
+            k0 = r.xin_ptr[u];
+            k1 = r.xin_ptr[u + 1];
+            for (int64_t k = k0; k < k1; k++) c += on(mask, r.xin_cls[k]);
+        }
+        const int64_t mine = at + block_excl_scan<kBS>(c ? ((int64_t)1 << 32) | c : 0, &tot);
+        at += tot;
+        if (p >= hi) continue;
+        const int64_t i = mine >> 32;
+        cidx[p] = (int32_t)i;
+        if (!c) continue;
+        cand_pos[i] = p;
+        int64_t o = mine & 0xffffffffll;
+        req_ptr[i] = o;
+        int32_t mx[kWinT];                  // largest requirement per parent thread (-1: none)
 #pragma unroll
-    for (int z = 0; z < kWinT; z++) mx[z] = -1;
-    int32_t t0 = -1, t1 = -1, m0 = -1, m1 = -1;   // T > kWinT: the first two threads met
-    bool many = false;                            // a third parent thread
-    for (int64_t k = r.xin_ptr[u]; k < r.xin_ptr[u + 1]; k++) {
-        if (!on(mask, r.xin_cls[k])) continue;
-        const int32_t s = r.xin_src[k];
-        const int32_t ts = r.tid[s];
-        const int64_t gp = r.base[ts] + r.rank[s];
-        req_chain[o] = ts;
-        req_gpos[o] = gp;
+        for (int z = 0; z < kWinT; z++) mx[z] = -1;
+        int32_t t0 = -1, t1 = -1, m0 = -1, m1 = -1;   // T > kWinT: the first two threads met
+        bool many = false;                            // a third parent thread
+        for (int64_t k = k0; k < k1; k++) {
+            if (!on(mask, r.xin_cls[k])) continue;
+            const int32_t s = r.xin_src[k];
+            const int32_t ts = r.tid[s];
+            const int64_t gp = r.base[ts] + r.rank[s];
+            req_chain[o] = ts;
+            req_gpos[o] = gp;
 #pragma unroll
-        for (int z = 0; z < kWinT; z++)
-            if (z == ts && (int32_t)gp > mx[z]) mx[z] = (int32_t)gp;
-        if (ts == t0) m0 = (int32_t)gp > m0 ? (int32_t)gp : m0;
-        else if (ts == t1) m1 = (int32_t)gp > m1 ? (int32_t)gp : m1;
-        else if (t0 < 0) { t0 = ts; m0 = (int32_t)gp; }
-        else if (t1 < 0) { t1 = ts; m1 = (int32_t)gp; }
-        else many = true;
-        o++;
-    }
-    if (!pent) return;                  // (more than kEntT threads: no packed entries)
-    if (T > kWinT) {
-        const uint32_t nd = (t0 >= 0 ? 1u : 0u) + (t1 >= 0 ? 1u : 0u) + (many ? 1u : 0u);
-        pent[i] = CandEnt{(int32_t)p, m0 < 0 ? 0 : m0, m1 < 0 ? 0 : m1,
-                          (uint32_t)(t0 < 0 ? 0 : t0) | ((uint32_t)(t1 < 0 ? 0 : t1) << 8) | (nd << 16)};
-        return;
-    }
-    CandEnt ce{(int32_t)p, 0, 0, 0u};
-    uint32_t nd = 0;
+            for (int z = 0; z < kWinT; z++)
+                if (z == ts && (int32_t)gp > mx[z]) mx[z] = (int32_t)gp;
+            if (ts == t0) m0 = (int32_t)gp > m0 ? (int32_t)gp : m0;
+            else if (ts == t1) m1 = (int32_t)gp > m1 ? (int32_t)gp : m1;
+            else if (t0 < 0) { t0 = ts; m0 = (int32_t)gp; }
+            else if (t1 < 0) { t1 = ts; m1 = (int32_t)gp; }
+            else many = true;
+            o++;
+        }
+        if (!pent) continue;                // (more than kEntT threads: no packed entries)
+        if (T > kWinT) {
+            const uint32_t nd = (t0 >= 0 ? 1u : 0u) + (t1 >= 0 ? 1u : 0u) + (many ? 1u : 0u);
+            pent[i] = CandEnt{(int32_t)p, m0 < 0 ? 0 : m0, m1 < 0 ? 0 : m1,
+                              (uint32_t)(t0 < 0 ? 0 : t0) | ((uint32_t)(t1 < 0 ? 0 : t1) << 8) | (nd << 16)};
+            continue;
+        }
+        CandEnt ce{(int32_t)p, 0, 0, 0u};
+        uint32_t nd = 0;
 #pragma unroll
-    for (int z = 0; z < kWinT; z++) {
-        if (mx[z] < 0) continue;
-        if (nd == 0) { ce.g0 = mx[z]; ce.meta |= (uint32_t)z; }
-        if (nd == 1) { ce.g1 = mx[z]; ce.meta |= (uint32_t)z << 8; }
-        nd++;
+        for (int z = 0; z < kWinT; z++) {
+            if (mx[z] < 0) continue;
+            if (nd == 0) { ce.g0 = mx[z]; ce.meta |= (uint32_t)z; }
+            if (nd == 1) { ce.g1 = mx[z]; ce.meta |= (uint32_t)z << 8; }
+            nd++;
+        }
+        ce.meta |= nd << 16;
+        pent[i] = ce;
     }
-    ce.meta |= nd << 16;
-    pent[i] = ce;
+    if (hi == n && threadIdx.x == 0) {
+        cidx[n] = (int32_t)(at >> 32);
+        req_ptr[at >> 32] = at & 0xffffffffll;
+        lw->reqs = at & 0xffffffffll;
+    }
 }
 
-// (also closes the requirement lists: req_ptr[C] = R, from the scan totals)
-__global__ __launch_bounds__(kBS) void k_cand_base(int32_t T, int64_t n, const int64_t *__restrict__ base,
-                                                   const int64_t *__restrict__ cidx,
-                                                   const int64_t *__restrict__ rptr,
-                                                   int64_t *__restrict__ req_ptr,
-                                                   int64_t *__restrict__ cbase,
-                                                   int64_t *__restrict__ front,
-                                                   int64_t *__restrict__ ci) {
-    const int64_t t = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (t == 0) req_ptr[cidx[n]] = rptr[n];
-    if (t > T) return;
-    cbase[t] = cidx[base[t]];
-    if (t < T) {
-        front[t] = base[t];
-        ci[t] = cidx[base[t]];
+// What both kinds of rounds leave, and what follows from the steps: the
+// widest, the batches of k_solo.hip, and the results the host reads.
+struct StepArgs {
+    int32_t T, with_prev;
+    int64_t n;
+    const int64_t *base;           // [T+1]
+    int32_t *step_ptr;             // [n+1]
+    int32_t *segoff;               // windowed rounds: [n x T] position of each thread's run in each step
+    int4 *bat;
+    int32_t *nbat;
+    LevWork *lw;
+    LevelizeOut *out;              // host memory
+};
+
+// (the whole workgroup; step_ptr[0..R] is written)
+__device__ void finish_steps(int64_t R, int64_t nseg, const StepArgs &a) {
+    __shared__ int s_wmax, s_threads;
+    if (threadIdx.x == 0) { s_wmax = 0; s_threads = 0; }
+    __syncthreads();
+    int wmax = 0, live = 0;
+    for (int64_t t = threadIdx.x; t < a.T; t += kWG) live += a.base[t + 1] > a.base[t];
+    for (int64_t r = threadIdx.x; r < R; r += kWG) {
+        const int w = a.step_ptr[r + 1] - a.step_ptr[r];
+        wmax = w > wmax ? w : wmax;
+    }
+    if (R <= kSplitMaxSteps)
+        for (int64_t r = threadIdx.x; r <= R; r += kWG) a.out->steps[r] = a.step_ptr[r];
+    if (wmax) atomicMax(&s_wmax, wmax);
+    if (live) atomicAdd(&s_threads, live);
+    solo_batches(R, a.step_ptr, a.bat, a.nbat);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        a.lw->result[0] = R;
+        a.lw->result[1] = nseg;
+        a.out->n_steps = R;
+        a.out->n_segments = nseg;
+        a.out->max_width = s_wmax;
+        a.out->n_gathers = a.lw->reqs + (a.with_prev ? nseg - s_threads : 0);
+        a.out->err = 0;
     }
 }
 
@@ -158,19 +229,19 @@ struct KahnArgs {
     int32_t T;
     int64_t n;
     const int64_t *base;      // [T+1]
+    const int32_t *cidx;      // [n+1] candidates before each order position
     const int64_t *cand_pos;  // [C]
-    const int64_t *cbase;     // [T+1]
     const int64_t *req_ptr;   // [C+1]
     const int32_t *req_chain;
     const int64_t *req_gpos;
-    int64_t *front, *cidx, *nfront, *ncidx;   // [T]
+    int64_t *front, *ccur, *nfront, *nccur;   // [T] (more than kLdsT threads)
+    int64_t *cend;            // [T+1] the same: first candidate of each thread
     int32_t *long_list;       // [T]
     int64_t *seg_start;       // [n] order position of each segment's first task
-    int64_t *seg_len;         // [n]
+    int64_t *seg_off;         // [n+1] schedule position of it
     int32_t *seg_step;        // [n]
-    int64_t *step_seg;        // [n+1] first segment of each step
-    int64_t *result;          // [0] steps, [1] segments
-    uint32_t *err;
+    int32_t *step_ptr;        // [n+1]
+    LevWork *lw;              // steps, segments, error
 };
 
 // Round state of the generic rounds: with at most kLdsT graph threads the
@@ -188,23 +259,28 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
     __shared__ int64_t s_carry_cnt;
     __shared__ int64_t s_st[L ? 6 * (kLdsT + 1) : 1];
     const int lane = threadIdx.x & 63;
+    __shared__ int64_t s_carry_len;
     int64_t *const front = L ? s_st : a.front;
-    int64_t *const cidx = L ? s_st + (kLdsT + 1) : a.cidx;
+    int64_t *const cidx = L ? s_st + (kLdsT + 1) : a.ccur;
     int64_t *const nfront = L ? s_st + 2 * (kLdsT + 1) : a.nfront;
-    int64_t *const ncidx = L ? s_st + 3 * (kLdsT + 1) : a.ncidx;
+    int64_t *const ncidx = L ? s_st + 3 * (kLdsT + 1) : a.nccur;
     const int64_t *const base = L ? s_st + 4 * (kLdsT + 1) : a.base;
-    const int64_t *const cbase = L ? s_st + 5 * (kLdsT + 1) : a.cbase;
-    if (L) {
-        for (int t = threadIdx.x; t <= a.T; t += kWG) {
-            if (t < a.T) {
-                s_st[t] = a.front[t];
-                s_st[(kLdsT + 1) + t] = a.cidx[t];
-            }
-            s_st[4 * (kLdsT + 1) + t] = a.base[t];
-            s_st[5 * (kLdsT + 1) + t] = a.cbase[t];
+    // candidates of thread t: cbase(t) .. cbase(t + 1)
+    auto cbase = [&](int t) -> int64_t { return L ? s_st[5 * (kLdsT + 1) + t] : a.cend[t]; };
+    for (int t = threadIdx.x; t <= a.T; t += kWG) {
+        const int64_t b = a.base[t], c = a.cidx[b];
+        if (t < a.T) {
+            front[t] = b;
+            cidx[t] = c;
         }
-        __syncthreads();
+        if (L) {
+            s_st[4 * (kLdsT + 1) + t] = b;
+            s_st[5 * (kLdsT + 1) + t] = c;
+        } else {
+            a.cend[t] = c;
+        }
     }
+    __syncthreads();
     // lanes per graph thread in step A: all threads in one pass when they fit
     int gsh = 6;
     while (gsh > 0 && ((int64_t)a.T << gsh) > kWG) gsh--;
@@ -230,8 +306,9 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
         if (a.pent) return blocked_ent(a.pent[j], j);
         return blocked_list(j);
     };
-    int64_t nseg = 0;
+    int64_t nseg = 0, npos = 0;                   // segments and positions so far
     int64_t round = 0;
+    bool stalled = false;
     for (;;) {
         if (threadIdx.x == 0) {
             s_nlong = 0;
@@ -247,7 +324,7 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
             const bool act = t < a.T;
             const int64_t f = act ? front[t] : 0, end = act ? base[t + 1] : 0;
             int64_t ci = act ? cidx[t] : 0;
-            const int64_t ce = act ? cbase[t + 1] : 0;
+            const int64_t ce = act ? cbase(t + 1) : 0;
             const bool fin = !act || f >= end;
             if (act && fin && gl == 0) { nfront[t] = f; ncidx[t] = ci; }
             if (!fin && gl == 0) s_unfinished = 1;   // a flag: every writer stores 1
@@ -301,7 +378,7 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
         for (int i = 0; i < nlong; i++) {
             const int t = a.long_list[i];
             int64_t ci = ncidx[t];
-            const int64_t ce = cbase[t + 1];
+            const int64_t ce = cbase(t + 1);
             int64_t cnew = ce;
             for (;;) {
                 if (threadIdx.x == 0) s_first = ~0ull;
@@ -328,19 +405,26 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
         if (a.T <= 64) {
             if (threadIdx.x < 64) {
                 const int t = (int)threadIdx.x;
-                const int64_t len = t < a.T ? nfront[t] - front[t] : 0;
+                const int len = t < a.T ? (int)(nfront[t] - front[t]) : 0;
                 const unsigned long long bal = __ballot(len > 0);
+                int sum = len;                            // lengths up to and including t
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int y = __shfl_up(sum, o, 64);
+                    if (t >= o) sum += y;
+                }
                 if (len > 0) {
                     const int64_t sg = nseg + __popcll(bal & ((1ull << t) - 1ull));
                     a.seg_start[sg] = front[t];
-                    a.seg_len[sg] = len;
+                    a.seg_off[sg] = npos + sum - len;
                     a.seg_step[sg] = (int32_t)round;
                 }
                 if (t == 0) s_carry_cnt = __popcll(bal);
+                if (t == 63) s_carry_len = sum;
             }
             __syncthreads();
         } else {
-            if (threadIdx.x == 0) s_carry_cnt = 0;
+            if (threadIdx.x == 0) { s_carry_cnt = 0; s_carry_len = 0; }
             __syncthreads();
             for (int b0 = 0; b0 < a.T; b0 += kWG) {
                 const int t = b0 + threadIdx.x;
@@ -352,21 +436,25 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
                 if (len > 0) {
                     const int64_t sg = nseg + s_carry_cnt + (ex >> 32);
                     a.seg_start[sg] = front[t];
-                    a.seg_len[sg] = len;
+                    a.seg_off[sg] = npos + s_carry_len + (ex & 0xffffffffll);
                     a.seg_step[sg] = (int32_t)round;
                 }
                 __syncthreads();
-                if (threadIdx.x == 0) s_carry_cnt += tot >> 32;
+                if (threadIdx.x == 0) {
+                    s_carry_cnt += tot >> 32;
+                    s_carry_len += tot & 0xffffffffll;
+                }
                 __syncthreads();
             }
         }
-        const int64_t adv = s_carry_cnt;
+        const int64_t adv = s_carry_cnt, advlen = s_carry_len;
         if (adv == 0) {                               // stalled: cycle
-            if (threadIdx.x == 0) atomicOr(a.err, ERR_KAHN_CYCLE);
+            stalled = true;
             break;
         }
-        if (threadIdx.x == 0) a.step_seg[round] = nseg;
+        if (threadIdx.x == 0) a.step_ptr[round] = (int32_t)npos;
         nseg += adv;
+        npos += advlen;
         // D: advance the fronts
         for (int t = threadIdx.x; t < a.T; t += kWG) {
             front[t] = nfront[t];
@@ -376,9 +464,11 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        a.step_seg[round] = nseg;
-        a.result[0] = round;
-        a.result[1] = nseg;
+        a.step_ptr[round] = (int32_t)npos;
+        a.seg_off[nseg] = npos;
+        a.lw->result[0] = round;
+        a.lw->result[1] = nseg;
+        if (stalled) a.lw->err = ERR_KAHN_CYCLE;
     }
 }
 
@@ -400,54 +490,69 @@ constexpr int kWinBytes = 6144 * 16;    // LDS window of candidate entries, shar
 constexpr int kRefill = 16;             // window entries loaded per lane at once
 
 // tile maxima over candidates: tm1[k * T + s] = largest requirement position
-// on thread s among candidates [64k, 64k + 64) (-1 if none); one wave per tile
-__global__ __launch_bounds__(kBS) void k_tile_max1(const int64_t *__restrict__ pC, int32_t T,
-                                                   const int64_t *__restrict__ req_ptr,
-                                                   const int32_t *__restrict__ req_chain,
-                                                   const int64_t *__restrict__ req_gpos,
-                                                   int32_t *__restrict__ tm1) {
+// on thread s among candidates [64k, 64k + 64) (-1 if none), tm2 the same for
+// [4096m, 4096m + 4096); a wave per tile of 64, a workgroup per tile of 4,096
+__global__ __launch_bounds__(kWG) void k_tile_max(const int32_t *__restrict__ pC, int32_t T,
+                                                  const CandEnt *__restrict__ pent,
+                                                  const int64_t *__restrict__ req_ptr,
+                                                  const int32_t *__restrict__ req_chain,
+                                                  const int64_t *__restrict__ req_gpos,
+                                                  int32_t *__restrict__ tm1, int32_t *__restrict__ tm2) {
     const int64_t C = *pC;                // candidates (the grid covers every position)
-    const int64_t j = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    const int64_t k = j >> 6;
-    if ((k << 6) >= C) return;           // whole waves past the last tile
-    const bool ok = j < C;
-    const int64_t q0 = ok ? req_ptr[j] : 0, q1 = ok ? req_ptr[j + 1] : 0;
-    for (int32_t ts = 0; ts < T; ts++) {
-        int64_t r = -1;
-        for (int64_t q = q0; q < q1; q++)
-            if (req_chain[q] == ts && req_gpos[q] > r) r = req_gpos[q];
-        r = wave_max64(r);
-        if ((threadIdx.x & 63) == 0 && (k << 6) < C) tm1[k * T + ts] = (int32_t)r;
+    const int64_t b0 = (int64_t)blockIdx.x << 12;
+    if (b0 >= C) return;
+    __shared__ int32_t s_mx[kWG / 64][kWinT];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int32_t best[kWinT];
+#pragma unroll
+    for (int z = 0; z < kWinT; z++) best[z] = -1;
+    for (int i = wv; i < 64; i += kWG / 64) {
+        const int64_t j = b0 + i * 64 + lane, k = j >> 6;
+        if ((k << 6) >= C) break;         // whole waves past the last tile
+        const bool ok = j < C;
+        const CandEnt e = pent[ok ? j : 0];
+        const uint32_t nd = ok ? e.meta >> 16 : 0u;
+        const bool list = nd > 2;         // parents on three or more threads
+        const int64_t q0 = list ? req_ptr[j] : 0, q1 = list ? req_ptr[j + 1] : 0;
+#pragma unroll
+        for (int ts = 0; ts < kWinT; ts++) {
+            if (ts < T) {
+                int32_t r = -1;
+                if (nd > 0 && (int)(e.meta & 0xff) == ts) r = e.g0;
+                if (nd > 1 && (int)((e.meta >> 8) & 0xff) == ts) r = e.g1;
+                for (int64_t q = q0; q < q1; q++)
+                    if (req_chain[q] == ts && (int32_t)req_gpos[q] > r) r = (int32_t)req_gpos[q];
+                for (int o = 32; o > 0; o >>= 1) {
+                    const int32_t y = __shfl_xor(r, o, 64);
+                    r = y > r ? y : r;
+                }
+                if (lane == 0) tm1[k * T + ts] = r;
+                best[ts] = r > best[ts] ? r : best[ts];
+            }
+        }
     }
-}
-
-// tm2[m * T + s] = maximum of tm1 over tiles [64m, 64m + 64)
-__global__ __launch_bounds__(kBS) void k_tile_max2(const int64_t *__restrict__ pC, int32_t T,
-                                                   const int32_t *__restrict__ tm1,
-                                                   int32_t *__restrict__ tm2) {
-    const int64_t C1 = (*pC + 63) / 64;   // tiles of 64 candidates
-    const int64_t k = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    const int64_t m = k >> 6;
-    if ((m << 6) >= C1) return;          // whole waves past the last tile
-    for (int32_t ts = 0; ts < T; ts++) {
-        int64_t r = k < C1 ? tm1[k * T + ts] : -1;
-        r = wave_max64(r);
-        if ((threadIdx.x & 63) == 0 && (m << 6) < C1) tm2[m * T + ts] = (int32_t)r;
+    if (lane == 0)
+#pragma unroll
+        for (int z = 0; z < kWinT; z++) s_mx[wv][z] = best[z];
+    __syncthreads();
+    if ((int)threadIdx.x < T) {
+        int32_t r = -1;
+        for (int w = 0; w < kWG / 64; w++) r = s_mx[w][threadIdx.x] > r ? s_mx[w][threadIdx.x] : r;
+        tm2[(b0 >> 12) * T + threadIdx.x] = r;
     }
 }
 
 struct WinArgs {
     int32_t T, wlog;                    // window of 2^wlog entries per thread
     const int64_t *base;                // [T+1]
-    const int64_t *cbase;               // [T+1]
+    const int32_t *cidx;                // [n+1] candidates before each order position
     const CandEnt *pent;                // [C]
     const int64_t *req_ptr;             // [C+1]
     const int32_t *req_chain;
     const int64_t *req_gpos;
     const int32_t *tm1, *tm2;           // tile maxima (tiles of 64 and 4096 candidates)
     int32_t *ftab;                      // [(n+1) x T] fronts at the start of each round
-    int64_t *result;                    // [0] steps
-    uint32_t *err;
+    LevWork *lw;                        // steps, error
 };
 
 __device__ __forceinline__ bool win_blocked(const WinArgs &a, const CandEnt &e, int64_t j,
@@ -482,8 +587,8 @@ __global__ __launch_bounds__(kWG) void k_kahn_win(WinArgs a) {
     CandEnt *const win = s_win + (mine ? t : 0) * W;
     // the wave's own thread: front end, candidate range and window in registers
     const int end = mine ? (int)a.base[t + 1] : 0;
-    const int ce = mine ? (int)a.cbase[t + 1] : 0;
-    int ci = mine ? (int)a.cbase[t] : 0;
+    const int ce = mine ? a.cidx[a.base[t + 1]] : 0;
+    int ci = mine ? a.cidx[a.base[t]] : 0;
     int wend = ci;
     int f = mine ? (int)a.base[t] : 0;             // the wave's own front (also in LDS for the others)
     if (threadIdx.x < 32) reinterpret_cast<uint8_t *>(s_adv)[threadIdx.x] = 0;
@@ -620,196 +725,186 @@ __global__ __launch_bounds__(kWG) void k_kahn_win(WinArgs a) {
                 if (mine && slotr != 63 && lane <= slotr)
                     a.ftab[(round - slotr + lane + 1) * T + t] = frow;
             } else if (threadIdx.x == 0) {
-                atomicOr(a.err, ERR_KAHN_CYCLE);
+                a.lw->err = ERR_KAHN_CYCLE;
             }
             break;
         }
         round++;
     }
-    if (threadIdx.x == 0) a.result[0] = round;
+    if (threadIdx.x == 0) a.lw->result[0] = round;
 }
 
-// segments from the front table: thread t advanced in round r when its front
-// moved; segments are numbered in (round, thread) order
-__global__ __launch_bounds__(kBS) void k_win_seg_count(int64_t R, int32_t T,
-                                                       const int32_t *__restrict__ ftab,
-                                                       int64_t *__restrict__ cnt) {
-    const int64_t i = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (i < R * T) cnt[i] = ftab[i + T] > ftab[i];
-}
-
-// The position offset of segment (r, t) comes straight from the front table:
-// every thread's advance before round r, plus the advances of lower threads
-// in round r.  nseg[0] receives the segment count; seg_off[nseg] = n.
-__global__ __launch_bounds__(kBS) void k_win_seg_fill(int64_t R, int32_t T,
-                                                      const int32_t *__restrict__ ftab,
-                                                      const int64_t *__restrict__ off,
-                                                      int64_t *__restrict__ seg_start,
-                                                      int64_t *__restrict__ seg_len,
-                                                      int64_t *__restrict__ seg_off,
-                                                      int32_t *__restrict__ seg_step,
-                                                      int64_t *__restrict__ step_seg,
-                                                      int64_t *__restrict__ nseg) {
-    const int64_t i = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (i > R * T) return;
-    if (i % T == 0) step_seg[i / T] = off[i];          // i == R*T gives the total
-    const int64_t r = i / T;
-    const int t = (int)(i % T);
-    if (i == R * T) {
-        nseg[0] = off[i];
-        int64_t done = 0;
-        for (int z = 0; z < T; z++) done += ftab[R * T + z] - ftab[z];
-        seg_off[off[i]] = done;
+// What follows from the rounds, by one workgroup (a launch of its own: as the
+// end of k_kahn_win it cost that kernel's refills their registers, 1.2 ->
+// 1.5 ms for 1,633 rounds).  Windowed rounds: where every thread's run of
+// every step lies -- the positions of a step start at the sum of the fronts'
+// advances before it, its runs follow in thread order.
+__global__ __launch_bounds__(kWG) void k_steps(bool windowed, const int32_t *__restrict__ ftab, StepArgs a) {
+    __shared__ int s_seg;
+    const int64_t R = a.lw->result[0];
+    if (a.lw->err) {
+        if (threadIdx.x == 0) {
+            a.out->err = a.lw->err;
+            a.out->n_steps = R;
+        }
         return;
     }
-    const int32_t f0 = ftab[i], f1 = ftab[i + T];
-    if (f1 > f0) {
-        int64_t o = 0;
-        for (int z = 0; z < T; z++) o += ftab[r * T + z] - ftab[z];
-        for (int z = 0; z < t; z++) o += ftab[(r + 1) * T + z] - ftab[r * T + z];
-        const int64_t sidx = off[i];
-        seg_start[sidx] = f0;
-        seg_len[sidx] = f1 - f0;
-        seg_off[sidx] = o;
-        seg_step[sidx] = (int32_t)r;
+    if (threadIdx.x == 0) s_seg = 0;
+    __syncthreads();
+    const int T = a.T;
+    if (windowed) {
+        int segs = 0;
+        for (int64_t r = threadIdx.x; r <= R; r += kWG) {
+            int o = 0;
+            for (int z = 0; z < T; z++) o += ftab[r * T + z] - (int)a.base[z];
+            a.step_ptr[r] = o;
+            if (r < R)
+                for (int z = 0; z < T; z++) {
+                    const int len = ftab[(r + 1) * T + z] - ftab[r * T + z];
+                    a.segoff[r * T + z] = o;
+                    o += len;
+                    segs += len > 0;
+                }
+        }
+        if (segs) atomicAdd(&s_seg, segs);
     }
+    __syncthreads();
+    finish_steps(R, windowed ? (int64_t)s_seg : a.lw->result[1], a);
 }
 
-// positions in step order: segment of each position by binary search
-__global__ __launch_bounds__(kBS) void k_positions(
-    int64_t n, const int64_t *__restrict__ pnseg, const int64_t *__restrict__ seg_off,
-    const int64_t *__restrict__ seg_start,
-    const int32_t *__restrict__ seg_step, const int32_t *__restrict__ order,
-    const int64_t *__restrict__ dur, const int64_t *__restrict__ gap,
-    const uint16_t *__restrict__ cls, int32_t *__restrict__ pos_node,
-    uint8_t *__restrict__ pos_flags, int64_t *__restrict__ pos_dur,
-    int64_t *__restrict__ pos_gap, uint16_t *__restrict__ pos_cls,
-    int32_t *__restrict__ node_step) {
+// schedule position of every task from the fronts of the windowed rounds: the
+// last round whose front on the task's thread lies at or before it
+__global__ __launch_bounds__(kBS) void k_place_win(int64_t n, int32_t T, const LevWork *__restrict__ lw,
+                                                   const int32_t *__restrict__ ftab,
+                                                   const int32_t *__restrict__ segoff,
+                                                   const int32_t *__restrict__ order,
+                                                   const int32_t *__restrict__ tid,
+                                                   int32_t *__restrict__ pos_node, int32_t *__restrict__ pos_of,
+                                                   uint8_t *__restrict__ pos_flags,
+                                                   int32_t *__restrict__ node_step) {
+    const int64_t p = (int64_t)blockIdx.x * kBS + threadIdx.x;
+    if (p >= n || lw->err) return;
+    const int32_t u = order[p], t = tid[u];
+    int64_t lo = 0, hi = lw->result[0] - 1;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (ftab[mid * T + t] <= p) lo = mid; else hi = mid - 1;
+    }
+    const int32_t f = ftab[lo * T + t];
+    const int64_t q = segoff[lo * T + t] + (p - f);
+    pos_node[q] = u;
+    pos_of[u] = (int32_t)q;
+    pos_flags[q] = p == f ? 1 : 0;
+    node_step[u] = (int32_t)lo;
+}
+
+// the same from the segments of the generic rounds
+__global__ __launch_bounds__(kBS) void k_place_seg(int64_t n, const LevWork *__restrict__ lw,
+                                                   const int64_t *__restrict__ seg_off,
+                                                   const int64_t *__restrict__ seg_start,
+                                                   const int32_t *__restrict__ seg_step,
+                                                   const int32_t *__restrict__ order,
+                                                   int32_t *__restrict__ pos_node, int32_t *__restrict__ pos_of,
+                                                   uint8_t *__restrict__ pos_flags,
+                                                   int32_t *__restrict__ node_step) {
     const int64_t q = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (q >= n) return;
-    const int64_t nseg = *pnseg;
-    int64_t lo = 0, hi = nseg - 1;          // last segment with seg_off <= q
+    if (q >= n || lw->err) return;
+    int64_t lo = 0, hi = lw->result[1] - 1;          // last segment with seg_off <= q
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) >> 1;
         if (seg_off[mid] <= q) lo = mid; else hi = mid - 1;
     }
-    const int64_t p = seg_start[lo] + (q - seg_off[lo]);
-    const int32_t u = order[p];
+    const int32_t u = order[seg_start[lo] + (q - seg_off[lo])];
     pos_node[q] = u;
-    pos_flags[q] = (q == seg_off[lo]) ? 1 : 0;
-    pos_dur[q] = dur[u];
-    pos_gap[q] = gap[u];
-    pos_cls[q] = cls ? cls[u] : 0;
+    pos_of[u] = (int32_t)q;
+    pos_flags[q] = q == seg_off[lo] ? 1 : 0;
     node_step[u] = seg_step[lo];
 }
 
-__global__ __launch_bounds__(kBS) void k_step_ptr(int64_t nsteps, const int64_t *__restrict__ step_seg,
-                                                  const int64_t *__restrict__ seg_off,
-                                                  int32_t *__restrict__ step_ptr) {
-    const int64_t r = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (r <= nsteps) step_ptr[r] = (int32_t)seg_off[step_seg[r]];
-}
+// The gathers of each position (thread predecessor of a run's first task
+// without thread carries, then the active cross-thread parents) and the
+// records the simulation reads.  A workgroup takes its gather entries with
+// one atomic, so the lists of different workgroups lie in any order;
+// gat_rng[q] = first entry | entries << 32.
+struct RecArgs {
+    int64_t n;
+    uint64_t mask;
+    int32_t with_prev;
+    const int32_t *pos_node, *pos_of;
+    const uint8_t *pos_flags;
+    const int32_t *tid, *prev;
+    const int64_t *dur, *gap;
+    const uint16_t *cls;
+    const int64_t *xin_ptr;
+    const int32_t *xin_src;
+    const uint8_t *xin_cls;
+    LevWork *lw;
+    uint64_t *gat_rng;
+    int32_t *gat_src, *gat_spos;
+    uint8_t *gat_cls;
+    int64_t *gat_gap;
+    Rec *rec;
+    SoloRec *so_rec;
+};
 
-// gathers per position: thread predecessor for run heads + active cross parents
-__global__ __launch_bounds__(kBS) void k_gather_count(int64_t n, const int32_t *__restrict__ pos_node,
-                                                      const uint8_t *__restrict__ pos_flags,
-                                                      const int32_t *__restrict__ prev,
-                                                      const int64_t *__restrict__ xin_ptr,
-                                                      const uint8_t *__restrict__ xin_cls,
-                                                      uint64_t mask, bool with_prev,
-                                                      int64_t *__restrict__ cnt) {
+__global__ __launch_bounds__(kBS) void k_records(RecArgs a) {
+    __shared__ int64_t s_base;
+    if (a.lw->err) return;
     const int64_t q = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (q >= n) return;
-    const int32_t u = pos_node[q];
-    int64_t c = (with_prev && (pos_flags[q] & 1) && prev[u] >= 0) ? 1 : 0;
-    for (int64_t k = xin_ptr[u]; k < xin_ptr[u + 1]; k++) c += on(mask, xin_cls[k]);
-    cnt[q] = c;
-}
-
-__global__ __launch_bounds__(kBS) void k_gather_fill(
-    int64_t n, const int32_t *__restrict__ pos_node, const uint8_t *__restrict__ pos_flags,
-    const int32_t *__restrict__ prev, const int64_t *__restrict__ xin_ptr,
-    const int32_t *__restrict__ xin_src, const uint8_t *__restrict__ xin_cls, uint64_t mask,
-    bool with_prev, const int64_t *__restrict__ gap, const int64_t *__restrict__ gptr,
-    int32_t *__restrict__ gsrc, int32_t *__restrict__ gpos, uint8_t *__restrict__ gcls,
-    int64_t *__restrict__ ggap) {
-    const int64_t q = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (q >= n) return;
-    const int32_t u = pos_node[q];
-    int64_t o = gptr[q];
-    if (with_prev && (pos_flags[q] & 1) && prev[u] >= 0) {
-        gsrc[o] = prev[u]; gpos[o] = (int32_t)q; gcls[o] = 255; ggap[o] = gap[prev[u]];
-        o++;
+    const bool ok = q < a.n;
+    int32_t u = 0, pv = -1;
+    int64_t k0 = 0, k1 = 0, ng = 0;
+    uint32_t head = 0;
+    if (ok) {
+        u = a.pos_node[q];
+        head = a.pos_flags[q] & 1u;
+        pv = a.with_prev && head ? a.prev[u] : -1;
+        k0 = a.xin_ptr[u];
+        k1 = a.xin_ptr[u + 1];
+        ng = pv >= 0 ? 1 : 0;
+        for (int64_t k = k0; k < k1; k++) ng += on(a.mask, a.xin_cls[k]);
     }
-    for (int64_t k = xin_ptr[u]; k < xin_ptr[u + 1]; k++) {
-        if (!on(mask, xin_cls[k])) continue;
-        const int32_t s = xin_src[k];
-        gsrc[o] = s; gpos[o] = (int32_t)q; gcls[o] = xin_cls[k]; ggap[o] = gap[s];
-        o++;
-    }
-}
-
-__global__ __launch_bounds__(kBS) void k_inverse(int64_t n, const int32_t *__restrict__ pos_node,
-                                                 int32_t *__restrict__ pos_of) {
-    const int64_t q = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (q < n) pos_of[pos_node[q]] = (int32_t)q;
-}
-
-__global__ __launch_bounds__(kBS) void k_gather_spos(const int64_t *__restrict__ pG,
-                                                     const int32_t *__restrict__ gsrc,
-                                                     const int32_t *__restrict__ pos_of,
-                                                     int32_t *__restrict__ gspos) {
-    const int64_t e = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (e < *pG) gspos[e] = pos_of[gsrc[e]];
-}
-
-// the per-position record the simulation streams through LDS
-__global__ __launch_bounds__(kBS) void k_records(
-    int64_t n, const int32_t *__restrict__ tid, const int32_t *__restrict__ pos_node,
-    const uint8_t *__restrict__ pos_flags,
-    const int64_t *__restrict__ pos_dur, const int64_t *__restrict__ pos_gap,
-    const uint16_t *__restrict__ pos_cls, const int64_t *__restrict__ gptr,
-    const int32_t *__restrict__ gsrc, const int32_t *__restrict__ gspos,
-    const uint8_t *__restrict__ gcls, const int64_t *__restrict__ ggap, Rec *__restrict__ rec,
-    SoloRec *__restrict__ so_rec) {
-    const int64_t q = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (q >= n) return;
+    int64_t tot;
+    const int64_t ex = block_excl_scan<kBS>(ng, &tot);
+    if (threadIdx.x == 0) s_base = tot ? (int64_t)atomicAdd(&a.lw->gctr, (unsigned long long)tot) : 0;
+    __syncthreads();
+    if (!ok) return;
+    int64_t o = s_base + ex;
+    a.gat_rng[q] = (uint64_t)o | ((uint64_t)ng << 32);
     Rec r;
-    r.dur = pos_dur[q];
-    r.gap = pos_gap[q];
-    r.node = pos_node[q];
-    const int32_t t = tid[r.node];
-    const int64_t e0 = gptr[q], e1 = gptr[q + 1];
-    const int64_t ng = e1 - e0;
-    uint32_t c0 = 0, c1 = 0;
+    r.dur = a.dur[u];
+    r.gap = a.gap[u];
+    r.node = u;
     r.g0_src = -1; r.g1_src = -1; r.g0_spos = 0; r.g1_spos = 0;
     r.g0_gap32 = 0;
-    if (ng > 0) {
-        r.g0_src = gsrc[e0]; r.g0_spos = gspos[e0]; c0 = gcls[e0];
-        r.g0_gap32 = (uint32_t)ggap[e0];
-    }
-    if (ng > 1) { r.g1_src = gsrc[e0 + 1]; r.g1_spos = gspos[e0 + 1]; c1 = gcls[e0 + 1]; }
-    r.cls = (uint32_t)pos_cls[q] | (c0 << 16) | (c1 << 24);
-    int64_t extra = ng > 2 ? ng - 2 : 0;   // count saturates; the gather pointers are exact
+    uint32_t c0 = 0, c1 = 0;
+    int i = 0;
+    auto add = [&](int32_t s, uint32_t c) {
+        const int32_t sp = a.pos_of[s];
+        const int64_t g = a.gap[s];
+        a.gat_src[o] = s; a.gat_spos[o] = sp; a.gat_cls[o] = (uint8_t)c; a.gat_gap[o] = g;
+        o++;
+        if (i == 0) { r.g0_src = s; r.g0_spos = sp; r.g0_gap32 = (uint32_t)g; c0 = c; }
+        if (i == 1) { r.g1_src = s; r.g1_spos = sp; c1 = c; }
+        i++;
+    };
+    if (pv >= 0) add(pv, 255u);
+    for (int64_t k = k0; k < k1; k++)
+        if (on(a.mask, a.xin_cls[k])) add(a.xin_src[k], a.xin_cls[k]);
+    const int32_t t = a.tid[u];
+    r.cls = (uint32_t)a.cls[u] | (c0 << 16) | (c1 << 24);
+    int64_t extra = ng > 2 ? ng - 2 : 0;   // count saturates; the gather ranges are exact
     if (extra > 0xFFFFFF) extra = 0xFFFFFF;
     // last task of a run: the next position starts a run (or the schedule ends)
-    const bool last = (q + 1 == n) || (pos_flags[q + 1] & 1);
-    r.flags = (uint32_t)(pos_flags[q] & 1) | (last ? 2u : 0u) |
+    const bool last = (q + 1 == a.n) || (a.pos_flags[q + 1] & 1);
+    r.flags = head | (last ? 2u : 0u) |
               ((uint32_t)(t < kMaxCarryThreads ? t : 0) << 2) | ((uint32_t)extra << 8);
-    rec[q] = r;
-    if (!so_rec) return;                     // durations or gaps past 32 bits
+    a.rec[q] = r;
+    if (!a.so_rec) return;                   // durations or gaps past 32 bits
     if (extra > 0xFFFF) extra = 0xFFFF;
-    so_rec[q] = SoloRec{(uint32_t)r.dur, (uint32_t)r.gap, r.node, r.g0_src >= 0 ? r.g0_spos : -1, r.cls,
-                        (r.flags & 0xffu) | (r.g1_src >= 0 ? kSoG1 : 0u) | ((uint32_t)extra << 16),
-                        r.g1_spos, 0};
-}
-
-__global__ __launch_bounds__(kBS) void k_step_width(int64_t nsteps, const int32_t *__restrict__ step_ptr,
-                                                    unsigned long long *__restrict__ wmax) {
-    const int64_t r = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    int64_t w = r < nsteps ? (int64_t)(step_ptr[r + 1] - step_ptr[r]) : 0;
-    w = wave_max64(w);
-    if ((threadIdx.x & 63) == 0) atomic_max_hot(wmax, (unsigned long long)w);
+    a.so_rec[q] = SoloRec{(uint32_t)r.dur, (uint32_t)r.gap, r.node, r.g0_src >= 0 ? r.g0_spos : -1, r.cls,
+                          (r.flags & 0xffu) | (r.g1_src >= 0 ? kSoG1 : 0u) | ((uint32_t)extra << 16),
+                          r.g1_spos, 0};
 }
 
 // Kahn levels from the phase schedule (one workgroup, phases in order)
@@ -899,25 +994,23 @@ __global__ __launch_bounds__(kBS) void k_level_count(int32_t n, const int32_t *_
 
 __global__ __launch_bounds__(kBS) void k_level_scatter(int32_t n, const int32_t *__restrict__ level,
                                                        int64_t *__restrict__ fill,
-                                                       const int64_t *__restrict__ dur,
-                                                       const int64_t *__restrict__ gap,
-                                                       const uint16_t *__restrict__ cls,
                                                        int32_t *__restrict__ pos_node,
+                                                       int32_t *__restrict__ pos_of,
                                                        uint8_t *__restrict__ pos_flags,
-                                                       int64_t *__restrict__ pos_dur,
-                                                       int64_t *__restrict__ pos_gap,
-                                                       uint16_t *__restrict__ pos_cls,
                                                        int32_t *__restrict__ node_step) {
     const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
     if (u >= n) return;
     const int32_t l = level[u];
     const int64_t q = (int64_t)atomicAdd((unsigned long long *)&fill[l], 1ull);
     pos_node[q] = (int32_t)u;
+    pos_of[u] = (int32_t)q;
     pos_flags[q] = 1;            // every task is its own run: thread predecessor gathered
-    pos_dur[q] = dur[u];
-    pos_gap[q] = gap[u];
-    pos_cls[q] = cls ? cls[u] : 0;
     node_step[u] = l;
+}
+
+// (levels) the widest step, the batches and the steps for the host
+__global__ __launch_bounds__(kWG) void k_level_finish(int64_t R, StepArgs a) {
+    finish_steps(R, a.n, a);
 }
 
 __global__ __launch_bounds__(kBS) void k_i64_to_i32(int64_t n, const int64_t *__restrict__ in,
@@ -943,264 +1036,168 @@ dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sch
     dd_status st = DD_OK;
     const int64_t n = g->n;
     const int32_t T = g->n_threads;
-    const int64_t N1 = n + 1;
-    const int64_t Cmax = n;                  // candidates <= tasks
-    const int64_t Rmax = g->n_cross;         // requirements <= cross edges
-    int64_t *cnt = nullptr, *flag = nullptr, *cidx = nullptr, *rptr = nullptr, *cand_pos = nullptr,
-            *req_ptr = nullptr, *req_gpos = nullptr, *cbase = nullptr, *front = nullptr,
-            *ci = nullptr, *nfront = nullptr, *nci = nullptr, *seg_start = nullptr,
-            *seg_len = nullptr, *seg_off = nullptr, *step_seg = nullptr, *result = nullptr,
-            *gcnt = nullptr, *lvl_cnt = nullptr;
-    int32_t *req_chain = nullptr, *long_list = nullptr, *seg_step = nullptr, *level = nullptr;
-    CandEnt *pent = nullptr;
-    int32_t *ftab = nullptr, *tm1 = nullptr, *tm2 = nullptr;
-    int64_t *seg_cnt = nullptr;
+    const size_t N1 = (size_t)n + 1;
+    const size_t Cmax = (size_t)n;                       // candidates <= tasks
+    const size_t Rmax = (size_t)g->n_cross;              // requirements <= cross edges
     const bool windowed = T <= kWinT;
-    uint32_t *err = nullptr;
-    unsigned long long *wmax = nullptr;
-    int64_t h_res[2] = {0, 0};
-    uint32_t h_err = 0;
-    unsigned long long h_w = 0;
-    Req rq{g->thread_base, g->order, g->rank, g->thread_id, g->xin_ptr, g->xin_src, g->xin_cls};
+    const bool with_prev = T > kMaxCarryThreads;
+    const size_t Gmax = Rmax + (with_prev ? (size_t)n : 0);
+    char *m = nullptr;                                   // working memory of the call
+    int64_t *lvl_cnt = nullptr;
+    int32_t *level = nullptr, *tmp_ptr = nullptr;
+    unsigned long long *lmax = nullptr;
+    LevelizeOut *out = nullptr, *out_dev = nullptr;
     const int gN = grid_for(n, kBS);
+    const int64_t chunk = ((n + kChunks - 1) / kChunks + kBS - 1) / kBS * kBS;
+    Req rq{g->thread_base, g->order, g->rank, g->thread_id, g->xin_ptr, g->xin_src, g->xin_cls};
+    size_t off = 0;
+    auto put = [&](size_t bytes) {
+        const size_t at = off;
+        off = (off + bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t C1 = (Cmax + 63) / 64, C2 = (C1 + 63) / 64;   // tiles at most
+    const size_t o_lw = put(sizeof(LevWork)), o_csum = put(8 * kChunks), o_cidx = put(4 * N1),
+                 o_cpos = put(8 * (Cmax + 1)), o_rptr = put(8 * (Cmax + 1)), o_rch = put(4 * (Rmax + 1)),
+                 o_rgp = put(8 * (Rmax + 1)), o_pent = put(T <= kEntT ? sizeof(CandEnt) * (Cmax + 1) : 0),
+                 o_ftab = put(windowed ? 4 * (size_t)(n + 2) * T : 0),
+                 o_segoff = put(windowed ? 4 * (size_t)(n + 1) * T : 0),
+                 o_tm1 = put(windowed ? 4 * (C1 + 1) * T : 0), o_tm2 = put(windowed ? 4 * (C2 + 1) * T : 0),
+                 o_gen = put(windowed ? 0 : 8 * (5 * (size_t)T + 1)), o_long = put(windowed ? 0 : 4 * (size_t)T),
+                 o_sst = put(windowed ? 0 : 8 * N1), o_sof = put(windowed ? 0 : 8 * (N1 + 1)),
+                 o_sstep = put(windowed ? 0 : 4 * N1), o_posof = put(4 * N1), o_flags = put(N1);
+    LevWork *lw;
+    int64_t *csum, *cand_pos, *req_ptr, *req_gpos, *gen, *seg_start, *seg_off;
+    int32_t *cidx, *req_chain, *ftab, *segoff, *tm1, *tm2, *long_list, *seg_step, *pos_of;
+    uint8_t *pos_flags;
+    CandEnt *pent;
+    StepArgs sa{};
 
     sch->n = (int32_t)n;
     sch->mode = mode;
     sch->mask = mask;
-    sch->thread_carry = T <= kMaxCarryThreads;
-    CK(dalloc_n(&cnt, N1, s));
-    CK(dalloc_n(&flag, N1, s));
-    CK(dalloc_n(&cidx, N1, s));
-    CK(dalloc_n(&rptr, N1, s));
-    CK(dalloc_n(&err, 1, s));
-    CK(dalloc_n(&result, 4, s));
-    CK(dalloc_n(&wmax, 1, s));
-    CK(hipMemsetAsync(err, 0, sizeof(uint32_t), s));
-    CK(hipMemsetAsync(result, 0, 4 * sizeof(int64_t), s));
-    CK(hipMemsetAsync(wmax, 0, sizeof(unsigned long long), s));
-    if (n > 0) {
-        k_req_count<<<gN, kBS, 0, s>>>((int32_t)n, rq, mask, cnt, flag);
-        CK(hipGetLastError());
+    sch->thread_carry = !with_prev;
+    {
+        void *h = nullptr, *d = nullptr;
+        CK(direct_buf(&h, &d));
+        out = static_cast<LevelizeOut *>(h);
+        out_dev = static_cast<LevelizeOut *>(d);
+        static_assert(sizeof(LevelizeOut) <= kDirectBytes, "results fit the buffer");
     }
-    CK(scan_exclusive(flag, cidx, n, s));
-    CK(scan_exclusive(cnt, rptr, n, s));
-    // sized by their bounds, so no count has to come back to the host first
-    CK(dalloc_n(&cand_pos, (size_t)Cmax + 1, s));
-    CK(dalloc_n(&req_ptr, (size_t)Cmax + 1, s));
-    CK(dalloc_n(&req_chain, (size_t)Rmax + 1, s));
-    CK(dalloc_n(&req_gpos, (size_t)Rmax + 1, s));
-    if (T <= kEntT) CK(dalloc_n(&pent, (size_t)Cmax + 1, s));
-    CK(dalloc_n(&cbase, (size_t)T + 1, s));
-    CK(dalloc_n(&front, (size_t)T, s));
-    CK(dalloc_n(&ci, (size_t)T, s));
-    CK(dalloc_n(&nfront, (size_t)T, s));
-    CK(dalloc_n(&nci, (size_t)T, s));
-    CK(dalloc_n(&long_list, (size_t)T, s));
-    CK(dalloc_n(&seg_start, N1, s));
-    CK(dalloc_n(&seg_len, N1, s));
-    CK(dalloc_n(&seg_step, N1, s));
-    CK(dalloc_n(&seg_off, N1 + 1, s));
-    CK(dalloc_n(&step_seg, N1 + 1, s));
-    if (n > 0) {
-        k_req_fill<<<gN, kBS, 0, s>>>((int32_t)n, T, rq, mask, cidx, rptr, cand_pos, req_ptr,
-                                      req_chain, req_gpos, pent);
-        CK(hipGetLastError());
+    memset(static_cast<void *>(out), 0, offsetof(LevelizeOut, steps));
+    CK(dalloc(reinterpret_cast<void **>(&m), off, s));
+    lw = (LevWork *)(m + o_lw);
+    csum = (int64_t *)(m + o_csum); cidx = (int32_t *)(m + o_cidx); cand_pos = (int64_t *)(m + o_cpos);
+    req_ptr = (int64_t *)(m + o_rptr); req_chain = (int32_t *)(m + o_rch); req_gpos = (int64_t *)(m + o_rgp);
+    pent = T <= kEntT ? (CandEnt *)(m + o_pent) : nullptr;
+    ftab = (int32_t *)(m + o_ftab); segoff = (int32_t *)(m + o_segoff);
+    tm1 = (int32_t *)(m + o_tm1); tm2 = (int32_t *)(m + o_tm2);
+    gen = (int64_t *)(m + o_gen); long_list = (int32_t *)(m + o_long);
+    seg_start = (int64_t *)(m + o_sst); seg_off = (int64_t *)(m + o_sof); seg_step = (int32_t *)(m + o_sstep);
+    pos_of = (int32_t *)(m + o_posof); pos_flags = (uint8_t *)(m + o_flags);
+    // the schedule, sized by bounds (at most n steps), so nothing has to come
+    // back to the host before the end
+    CK(dalloc_n(&sch->step_ptr, N1, s));
+    CK(dalloc_n(&sch->pos_node, N1, s));
+    CK(dalloc_n(&sch->node_step, N1, s));
+    CK(dalloc_n(&sch->gat_rng, N1, s));
+    CK(dalloc_n(&sch->gat_src, Gmax + 1, s));
+    CK(dalloc_n(&sch->gat_spos, Gmax + 1, s));
+    CK(dalloc_n(&sch->gat_cls, Gmax + 1, s));
+    CK(dalloc_n(&sch->gat_gap, Gmax + 1, s));
+    CK(dalloc_n(&sch->rec, N1, s));
+    CK(dalloc_n(&sch->bat, (size_t)solo_batch_max(n), s));
+    CK(dalloc_n(&sch->nbat, 1, s));
+    // (one more than n: idle lanes read it)
+    if (g->dmax < (int64_t(1) << 32) && g->gmax < (int64_t(1) << 32)) CK(dalloc_n(&sch->so_rec, N1, s));
+    if (n == 0) {
+        CK(hipMemsetAsync(sch->step_ptr, 0, sizeof(int32_t), s));
+        sch->h_step_ptr.assign(1, 0);
+        CK(hipStreamSynchronize(s));
+        goto done;
     }
-    k_cand_base<<<grid_for((int64_t)T + 1, kBS), kBS, 0, s>>>(T, n, g->thread_base, cidx, rptr,
-                                                               req_ptr, cbase, front, ci);
-    CK(hipGetLastError());
+    sa = StepArgs{T, with_prev ? 1 : 0, n, g->thread_base, sch->step_ptr, segoff, sch->bat, sch->nbat, lw, out_dev};
+    k_req_count<<<(unsigned)((n + chunk - 1) / chunk), kBS, 0, s>>>((int32_t)n, chunk, rq, mask, csum, lw);
+    k_req_fill<<<(unsigned)((n + chunk - 1) / chunk), kBS, 0, s>>>((int32_t)n, T, chunk, rq, mask, csum, cidx,
+                                                                  cand_pos, req_ptr, req_chain, req_gpos,
+                                                                  pent, lw);
     if (windowed) {
         int wlog = 6;                                  // 2^wlog entries per thread
         while ((int64_t)T << (wlog + 1) <= kWinBytes / (int64_t)sizeof(CandEnt)) wlog++;
-        CK(dalloc_n(&ftab, (size_t)(n + 2) * T, s));
-        const int64_t C1 = (Cmax + 63) / 64, C2 = (C1 + 63) / 64;   // tiles at most
-        CK(dalloc_n(&tm1, (size_t)(C1 > 0 ? C1 : 1) * T, s));
-        CK(dalloc_n(&tm2, (size_t)(C2 > 0 ? C2 : 1) * T, s));
-        if (n > 0) {
-            k_tile_max1<<<grid_for(C1 * 64, kBS), kBS, 0, s>>>(cidx + n, T, req_ptr, req_chain,
-                                                               req_gpos, tm1);
-            CK(hipGetLastError());
-            k_tile_max2<<<grid_for(C2 * 64, kBS), kBS, 0, s>>>(cidx + n, T, tm1, tm2);
-            CK(hipGetLastError());
-        }
-        WinArgs wa{T, wlog, g->thread_base, cbase, pent, req_ptr, req_chain, req_gpos,
-                   tm1, tm2, ftab, result, err};
+        k_tile_max<<<(unsigned)C2, kWG, 0, s>>>(cidx + n, T, pent, req_ptr, req_chain, req_gpos, tm1, tm2);
+        WinArgs wa{T, wlog, g->thread_base, cidx, pent, req_ptr, req_chain, req_gpos, tm1, tm2, ftab, lw};
         k_kahn_win<<<1, kWG, 0, s>>>(wa);
-        CK(hipGetLastError());
+        k_steps<<<1, kWG, 0, s>>>(true, ftab, sa);
+        k_place_win<<<gN, kBS, 0, s>>>(n, T, lw, ftab, segoff, g->order, g->thread_id, sch->pos_node, pos_of,
+                                       pos_flags, sch->node_step);
     } else {
-        KahnArgs ka{pent, T, n, g->thread_base, cand_pos, cbase, req_ptr, req_chain, req_gpos,
-                    front, ci, nfront, nci, long_list, seg_start, seg_len, seg_step, step_seg,
-                    result, err};
+        KahnArgs ka{pent, T, n, g->thread_base, cidx, cand_pos, req_ptr, req_chain, req_gpos,
+                    gen, gen + T, gen + 2 * (size_t)T, gen + 3 * (size_t)T,
+                    gen + 4 * (size_t)T, long_list, seg_start,
+                    seg_off, seg_step, sch->step_ptr, lw};
         if (T <= kLdsT) k_kahn_rounds<true><<<1, kWG, 0, s>>>(ka);
         else k_kahn_rounds<false><<<1, kWG, 0, s>>>(ka);
+        k_steps<<<1, kWG, 0, s>>>(false, nullptr, sa);
+        k_place_seg<<<gN, kBS, 0, s>>>(n, lw, seg_off, seg_start, seg_step, g->order, sch->pos_node, pos_of,
+                                       pos_flags, sch->node_step);
+    }
+    CK(hipGetLastError());
+    if (mode == DD_LEVELS) {
+        // levels from phases, then tasks sorted by level
+        CK(hipStreamSynchronize(s));
+        if (out->err) goto cycle;
+        const int64_t nph = out->n_steps;
+        unsigned long long h_lmax = 0;
+        CK(dalloc_n(&level, N1, s));
+        CK(dalloc_n(&tmp_ptr, (size_t)nph + 1, s));
+        CK(dalloc_n(&lmax, 1, s));
+        CK(hipMemsetAsync(lmax, 0, sizeof(unsigned long long), s));
+        CK(hipMemcpyAsync(tmp_ptr, sch->step_ptr, sizeof(int32_t) * ((size_t)nph + 1), hipMemcpyDeviceToDevice, s));
+        LevelArgs la{nph, tmp_ptr, sch->pos_node, pos_flags, g->thread_prev, g->xin_ptr,
+                     g->xin_src, g->xin_cls, mask, level, lmax};
+        k_levels<<<1, kWG, 0, s>>>(la);
         CK(hipGetLastError());
-    }
-    {
-        ReadBack rb(s, 2 * sizeof(int64_t) + sizeof(uint32_t));
-        CK(rb.add(h_res, result, 2 * sizeof(int64_t)));
-        CK(rb.add(&h_err, err, sizeof(uint32_t)));
-        CK(rb.finish());
-    }
-    if (h_err & ERR_KAHN_CYCLE) {
-        snprintf(msg, msg_len, "dependencies plus thread order contain a cycle "
-                               "(Kahn rounds stalled after %lld steps)", (long long)h_res[0]);
-        st = DD_ECYCLE;
-        goto done;
-    }
-    if (windowed) {                                    // cut the segments from the fronts
-        const int64_t R = h_res[0], RT = R * T;
-        CK(dalloc_n(&seg_cnt, (size_t)RT + 1, s));
-        if (RT > 0) {
-            k_win_seg_count<<<grid_for(RT, kBS), kBS, 0, s>>>(R, T, ftab, seg_cnt);
-            CK(hipGetLastError());
-        }
-        CK(scan_exclusive(seg_cnt, seg_cnt, RT, s));
-        k_win_seg_fill<<<grid_for(RT + 1, kBS), kBS, 0, s>>>(R, T, ftab, seg_cnt, seg_start,
-                                                             seg_len, seg_off, seg_step, step_seg,
-                                                             result + 1);
-        CK(hipGetLastError());
-    }
-    {
-        // (the windowed rounds leave the segment count on the device; it
-        // comes back with the gather count below)
-        const int64_t nph = h_res[0];
-        if (!windowed) CK(scan_exclusive(seg_len, seg_off, h_res[1], s));
-        CK(dalloc_n(&sch->pos_node, N1, s));
-        CK(dalloc_n(&sch->pos_flags, N1, s));
-        CK(dalloc_n(&sch->pos_dur, N1, s));
-        CK(dalloc_n(&sch->pos_gap, N1, s));
-        CK(dalloc_n(&sch->pos_cls, N1, s));
-        CK(dalloc_n(&sch->node_step, N1, s));
-        CK(dalloc_n(&sch->gat_ptr, N1, s));
-        if (n > 0) {
-            k_positions<<<gN, kBS, 0, s>>>(n, result + 1, seg_off, seg_start, seg_step, g->order, g->dur,
-                                           g->gap, g->cls, sch->pos_node, sch->pos_flags,
-                                           sch->pos_dur, sch->pos_gap, sch->pos_cls,
-                                           sch->node_step);
-            CK(hipGetLastError());
-        }
-        if (mode == DD_PHASES) {
-            sch->n_steps = nph;
-            CK(dalloc_n(&sch->step_ptr, (size_t)nph + 1, s));
-            k_step_ptr<<<grid_for(nph + 1, kBS), kBS, 0, s>>>(nph, step_seg, seg_off, sch->step_ptr);
-            CK(hipGetLastError());
-        } else {
-            // levels from phases, then tasks sorted by level
-            int32_t *tmp_ptr = nullptr;
-            unsigned long long *lmax = nullptr;
-            unsigned long long h_lmax = 0;
-            CK(dalloc_n(&level, N1, s));
-            CK(dalloc_n(&tmp_ptr, (size_t)nph + 1, s));
-            CK(dalloc_n(&lmax, 1, s));
-            CK(hipMemsetAsync(lmax, 0, sizeof(unsigned long long), s));
-            k_step_ptr<<<grid_for(nph + 1, kBS), kBS, 0, s>>>(nph, step_seg, seg_off, tmp_ptr);
-            LevelArgs la{nph, tmp_ptr, sch->pos_node, sch->pos_flags, g->thread_prev, g->xin_ptr,
-                         g->xin_src, g->xin_cls, mask, level, lmax};
-            k_levels<<<1, kWG, 0, s>>>(la);
-            CK(hipGetLastError());
-            {
-                ReadBack rb(s, sizeof(h_lmax));
-                CK(rb.add(&h_lmax, lmax, sizeof(h_lmax)));
-                CK(rb.finish());
-            }
-            dfree(tmp_ptr, s);
-            dfree(lmax, s);
-            const int64_t nl = n > 0 ? (int64_t)h_lmax + 1 : 0;
-            CK(dalloc_n(&lvl_cnt, (size_t)nl + 1, s));
-            CK(hipMemsetAsync(lvl_cnt, 0, sizeof(int64_t) * ((size_t)nl + 1), s));
-            if (n > 0) {
-                k_level_count<<<gN, kBS, 0, s>>>((int32_t)n, level, lvl_cnt);
-                CK(hipGetLastError());
-            }
-            CK(scan_exclusive(lvl_cnt, lvl_cnt, nl, s));
-            CK(dalloc_n(&sch->step_ptr, (size_t)nl + 1, s));
-            k_i64_to_i32<<<grid_for(nl + 1, kBS), kBS, 0, s>>>(nl + 1, lvl_cnt, sch->step_ptr);
-            CK(hipGetLastError());
-            if (n > 0) {
-                k_level_scatter<<<gN, kBS, 0, s>>>((int32_t)n, level, lvl_cnt, g->dur, g->gap,
-                                                   g->cls, sch->pos_node, sch->pos_flags,
-                                                   sch->pos_dur, sch->pos_gap, sch->pos_cls,
-                                                   sch->node_step);
-                CK(hipGetLastError());
-            }
-            sch->n_steps = nl;
-            sch->n_segments = n;
-        }
-        // gathers
-        CK(dalloc_n(&gcnt, N1, s));
-        if (n > 0) {
-            k_gather_count<<<gN, kBS, 0, s>>>(n, sch->pos_node, sch->pos_flags, g->thread_prev,
-                                              g->xin_ptr, g->xin_cls, mask, !sch->thread_carry,
-                                              gcnt);
-            CK(hipGetLastError());
-        }
-        CK(scan_exclusive(gcnt, sch->gat_ptr, n, s));
-        // gather lists sized by their bound (cross edges, plus one thread
-        // predecessor per run head without thread carries); the count comes
-        // back with the last read-back
-        const int64_t Gmax = g->n_cross + (sch->thread_carry ? 0 : n);
-        CK(dalloc_n(&sch->gat_src, (size_t)Gmax + 1, s));
-        CK(dalloc_n(&sch->gat_pos, (size_t)Gmax + 1, s));
-        CK(dalloc_n(&sch->gat_cls, (size_t)Gmax + 1, s));
-        CK(dalloc_n(&sch->gat_gap, (size_t)Gmax + 1, s));
-        if (n > 0) {
-            k_gather_fill<<<gN, kBS, 0, s>>>(n, sch->pos_node, sch->pos_flags, g->thread_prev,
-                                             g->xin_ptr, g->xin_src, g->xin_cls, mask,
-                                             !sch->thread_carry, g->gap,
-                                             sch->gat_ptr, sch->gat_src, sch->gat_pos,
-                                             sch->gat_cls, sch->gat_gap);
-            CK(hipGetLastError());
-        }
         {
-            int32_t *pos_of = nullptr;
-            CK(dalloc_n(&pos_of, N1, s));
-            CK(dalloc_n(&sch->gat_spos, (size_t)Gmax + 1, s));
-            CK(dalloc_n(&sch->rec, N1, s));
-            // (one more than n: idle lanes read it)
-            if (g->dmax < (int64_t(1) << 32) && g->gmax < (int64_t(1) << 32))
-                CK(dalloc_n(&sch->so_rec, N1, s));
-            if (n > 0) {
-                k_inverse<<<gN, kBS, 0, s>>>(n, sch->pos_node, pos_of);
-                if (Gmax > 0)
-                    k_gather_spos<<<grid_for(Gmax, kBS), kBS, 0, s>>>(sch->gat_ptr + n, sch->gat_src,
-                                                                     pos_of, sch->gat_spos);
-                k_records<<<gN, kBS, 0, s>>>(n, g->thread_id, sch->pos_node, sch->pos_flags, sch->pos_dur,
-                                             sch->pos_gap, sch->pos_cls, sch->gat_ptr, sch->gat_src,
-                                             sch->gat_spos, sch->gat_cls, sch->gat_gap, sch->rec,
-                                             sch->so_rec);
-                CK(hipGetLastError());
-            }
-            dfree(pos_of, s);
+            ReadBack rb(s, sizeof(h_lmax));
+            CK(rb.add(&h_lmax, lmax, sizeof(h_lmax)));
+            CK(rb.finish());
         }
-        k_step_width<<<grid_for(sch->n_steps, kBS), kBS, 0, s>>>(sch->n_steps, sch->step_ptr, wmax);
+        const int64_t nl = (int64_t)h_lmax + 1;
+        CK(dalloc_n(&lvl_cnt, (size_t)nl + 1, s));
+        CK(hipMemsetAsync(lvl_cnt, 0, sizeof(int64_t) * ((size_t)nl + 1), s));
+        k_level_count<<<gN, kBS, 0, s>>>((int32_t)n, level, lvl_cnt);
         CK(hipGetLastError());
-        CK(dalloc_n(&sch->bat, (size_t)solo_batch_max(n, sch->n_steps), s));
-        CK(dalloc_n(&sch->nbat, 1, s));
-        CK(launch_batches(sch, s));
-        int64_t h_G = 0;
-        const bool keep_steps = sch->n_steps <= kSplitMaxSteps;
-        if (keep_steps) sch->h_step_ptr.resize((size_t)sch->n_steps + 1);
-        ReadBack rb(s, sizeof(h_w) + 2 * sizeof(int64_t) +
-                           (keep_steps ? sizeof(int32_t) * ((size_t)sch->n_steps + 1) : 0));
-        CK(rb.add(&h_w, wmax, sizeof(h_w)));
-        CK(rb.add(&h_G, sch->gat_ptr + n, sizeof(int64_t)));
-        if (mode == DD_PHASES) CK(rb.add(&h_res[1], result + 1, sizeof(int64_t)));
-        if (keep_steps)
-            CK(rb.add(sch->h_step_ptr.data(), sch->step_ptr,
-                      sizeof(int32_t) * ((size_t)sch->n_steps + 1)));
-        CK(rb.finish());
-        sch->max_width = (int64_t)h_w;
-        sch->n_gathers = h_G;
-        if (mode == DD_PHASES) sch->n_segments = h_res[1];
+        CK(scan_exclusive(lvl_cnt, lvl_cnt, nl, s));
+        k_i64_to_i32<<<grid_for(nl + 1, kBS), kBS, 0, s>>>(nl + 1, lvl_cnt, sch->step_ptr);
+        k_level_scatter<<<gN, kBS, 0, s>>>((int32_t)n, level, lvl_cnt, sch->pos_node, pos_of, pos_flags,
+                                           sch->node_step);
+        k_level_finish<<<1, kWG, 0, s>>>(nl, sa);
+        CK(hipGetLastError());
     }
+    {
+        RecArgs ra{n, mask, with_prev ? 1 : 0, sch->pos_node, pos_of, pos_flags, g->thread_id, g->thread_prev,
+                   g->dur, g->gap, g->cls, g->xin_ptr, g->xin_src, g->xin_cls, lw, sch->gat_rng,
+                   sch->gat_src, sch->gat_spos, sch->gat_cls, sch->gat_gap, sch->rec, sch->so_rec};
+        k_records<<<gN, kBS, 0, s>>>(ra);
+        CK(hipGetLastError());
+    }
+    CK(hipStreamSynchronize(s));
+    if (out->err) goto cycle;
+    sch->n_steps = out->n_steps;
+    sch->n_segments = out->n_segments;
+    sch->max_width = out->max_width;
+    sch->n_gathers = out->n_gathers;
+    if (sch->n_steps <= kSplitMaxSteps)
+        sch->h_step_ptr.assign(out->steps, out->steps + sch->n_steps + 1);
+    goto done;
+cycle:
+    snprintf(msg, msg_len, "dependencies plus thread order contain a cycle "
+                           "(Kahn rounds stalled after %lld steps)", (long long)out->n_steps);
+    st = DD_ECYCLE;
 done:
-    dfree(cnt, s); dfree(flag, s); dfree(cidx, s); dfree(rptr, s); dfree(err, s);
-    dfree(result, s); dfree(wmax, s); dfree(cand_pos, s); dfree(req_ptr, s);
-    dfree(req_chain, s); dfree(req_gpos, s); dfree(cbase, s); dfree(front, s); dfree(ci, s);
-    dfree(nfront, s); dfree(nci, s); dfree(long_list, s); dfree(seg_start, s);
-    dfree(seg_len, s); dfree(seg_off, s); dfree(seg_step, s); dfree(step_seg, s);
-    dfree(gcnt, s); dfree(lvl_cnt, s); dfree(level, s); dfree(pent, s);
-    dfree(ftab, s); dfree(tm1, s); dfree(tm2, s); dfree(seg_cnt, s);
+    if (st != DD_OK && st != DD_ECYCLE) (void)hipStreamSynchronize(s);
+    dfree(m, s);
+    dfree(lvl_cnt, s); dfree(level, s); dfree(tmp_ptr, s); dfree(lmax, s);
     return st;
 }
 

@@ -54,7 +54,7 @@ __device__ __forceinline__ int64_t scaled(int64_t d, const ScaleEntry &se) {
 }
 
 struct PipeArgs {
-    const int64_t *gat_ptr;       // [n+1] gathers of each position
+    const uint64_t *gat_rng;      // [n] gathers of each position: first entry | entries << 32
     const int32_t *gat_src;       // gathers beyond two per position
     const int32_t *gat_spos;
     const uint8_t *gat_cls;
@@ -515,7 +515,9 @@ __global__ __launch_bounds__(NT) void k_sim_pipe(const int32_t *__restrict__ rou
                         while (todo) {
                             const int ld = __ffsll((unsigned long long)todo) - 1;
                             todo &= todo - 1;
-                            const int64_t e0 = a.gat_ptr[r0 + ld] + 2, e1 = a.gat_ptr[r0 + ld + 1];
+                            const uint64_t rg = a.gat_rng[r0 + ld];
+                            const int64_t e0 = (int64_t)(uint32_t)rg + 2,
+                                          e1 = (int64_t)(uint32_t)rg + (int64_t)(rg >> 32);
                             int64_t mx = 0;
                             for (int64_t eb = e0; eb < e1; eb += 64) {
                                 const int64_t e = eb + lane;
@@ -728,7 +730,9 @@ __global__ __launch_bounds__(NT) void k_sim_pipe(const int32_t *__restrict__ rou
                         const int ld = __ffsll((unsigned long long)todo) - 1;
                         todo &= todo - 1;
                         const int qs = __shfl(q, ld, 64);
-                        const int64_t e0 = a.gat_ptr[r0 + qs] + 2, e1 = a.gat_ptr[r0 + qs + 1];
+                        const uint64_t rg = a.gat_rng[r0 + qs];
+                        const int64_t e0 = (int64_t)(uint32_t)rg + 2,
+                                      e1 = (int64_t)(uint32_t)rg + (int64_t)(rg >> 32);
                         int64_t mx[VPL];
 #pragma unroll
                         for (int j = 0; j < VPL; j++) mx[j] = 0;
@@ -1190,7 +1194,7 @@ hipError_t launch_pipe(const dd_graph *g, const dd_sched *sch, const dd_variants
     if (e == hipSuccess && ns > 0)
         k_round_fill<<<grid_for(ns, 256), 256, 0, s>>>(ns, sch->step_ptr, cnt, RP, r0, rn);
     const uint64_t cls_mask = sch->mask & g->cross_mask;
-    PipeArgs args{sch->gat_ptr, sch->gat_src, sch->gat_spos, sch->gat_cls, sch->gat_gap, g->gap,
+    PipeArgs args{sch->gat_rng, sch->gat_src, sch->gat_spos, sch->gat_cls, sch->gat_gap, g->gap,
                   var->table, var->n_cls, var->rm_bits, rmp, rstride, var->edge_on,
                   cls_mask, sch->thread_carry ? 1 : 0, var->V, var->W, finish, start, makespan,
                   dummy};

@@ -11,7 +11,7 @@
 //
 // How.  A workgroup of 512 threads walks the whole schedule for one variant,
 // a lane per position.  The schedule is cut into batches of at most 512
-// positions once, when it is levelized (k_batches): a batch is either a run
+// positions once, when it is levelized (dd_batches.h): a batch is either a run
 // of consecutive narrow steps or a part of a wider step.  Whatever a position
 // needs that does not depend on the batch in progress -- its record, removal
 // bit, scaled duration, and the release of a parent that finished in an
@@ -49,43 +49,10 @@ namespace {
 constexpr int kSoNT = kSoloPos;        // threads per workgroup: one per position of a batch
 constexpr int kSoW = kSoNT / 64;
 
-// Batches of a schedule.  Entry b: first position, first step, wide flag;
-// the batch ends where the next one begins (the list is closed by an entry
-// {n, steps}).  Narrow steps are grouped by the kSoloGroup-aligned span of
-// positions in which they start, so a group holds fewer than kSoloGroup + 64
-// positions.
-__global__ __launch_bounds__(1024) void k_batches(int64_t nsteps, const int32_t *__restrict__ step_ptr,
-                                                  int32_t rpw, int4 *__restrict__ bat,
-                                                  int32_t *__restrict__ nbat) {
-    int64_t carry = 0;
-    for (int64_t base = 0; base < nsteps; base += 1024) {
-        const int64_t r = base + threadIdx.x;
-        int32_t p0 = 0, p1 = 0, pm = 0;
-        if (r < nsteps) {
-            p0 = step_ptr[r];
-            p1 = step_ptr[r + 1];
-            pm = r > 0 ? step_ptr[r - 1] : 0;
-        }
-        const bool wide = p1 - p0 > kSoloNarrow;
-        const bool first = r == 0 || p0 - pm > kSoloNarrow || p0 / kSoloGroup != pm / kSoloGroup;
-        int64_t cnt = 0;
-        if (r < nsteps) cnt = wide ? (p1 - p0 + rpw - 1) / rpw : (first ? 1 : 0);
-        int64_t tot;
-        const int64_t ex = block_excl_scan<1024>(cnt, &tot);
-        for (int64_t i = 0; i < cnt; i++)
-            bat[carry + ex + i] = make_int4(p0 + (int32_t)i * rpw, (int32_t)r, wide ? 1 : 0, 0);
-        carry += tot;
-    }
-    if (threadIdx.x == 0) {
-        bat[carry] = make_int4(step_ptr[nsteps], (int32_t)nsteps, 1, 0);
-        nbat[0] = (int32_t)carry;
-    }
-}
-
 struct SoloArgs {
     const int32_t *step_ptr;
     const SoloRec *rec;           // [n] by position
-    const int64_t *gat_ptr;       // all parents on other threads, by position
+    const uint64_t *gat_rng;      // all gathers of a position: first entry | entries << 32
     const int32_t *gat_src, *gat_spos;
     const uint8_t *gat_cls;
     const int64_t *gap;           // [n] gap of every task
@@ -251,18 +218,18 @@ __global__ __launch_bounds__(kSoNT, 4) void k_sim_solo(const int4 *__restrict__ 
         if (__any(far0 | (flags >= kSoG1))) {
             // rarer cases: a parent older than the ring, further parents (the
             // second to fourth here, the rest when the batch is resolved)
-            if (far0) x = TM::mx(x, old_rel(a.gat_src[a.gat_ptr[q]]));
+            if (far0) x = TM::mx(x, old_rel(a.gat_src[(uint32_t)a.gat_rng[q]]));
             if ((flags & kSoG1) && cls_on(eon, cl >> 24)) {
                 const int s1 = (int)r.w.z;
                 if (s1 >= lo) o.i1 = ((uint32_t)s1 & (WIN - 1)) * 8u;
                 else if (s1 >= rlo) x = TM::mx(x, ring[(uint32_t)s1 & rmask]);
-                else x = TM::mx(x, old_rel(a.gat_src[a.gat_ptr[q] + 1]));
+                else x = TM::mx(x, old_rel(a.gat_src[(uint32_t)a.gat_rng[q] + 1u]));
             }
             const uint32_t extra = flags >> 16;
             if (extra > 2u) more = kSoMore;
             else if (extra != 0u) {
                 more = kSoTwo;
-                const int64_t e0 = a.gat_ptr[q] + 2;
+                const int64_t e0 = (int64_t)(uint32_t)a.gat_rng[q] + 2;
                 for (uint32_t z = 0; z < extra; z++) {
                     const int32_t sp = a.gat_spos[e0 + z];
                     if (!cls_on(eon, a.gat_cls[e0 + z])) continue;
@@ -307,7 +274,8 @@ __global__ __launch_bounds__(kSoNT, 4) void k_sim_solo(const int4 *__restrict__ 
             const int ld = __ffsll((unsigned long long)todo) - 1;
             todo &= todo - 1;
             const int qs = __shfl(q, ld, 64);
-            const int64_t e0 = a.gat_ptr[qs] + 2, e1 = a.gat_ptr[qs + 1];
+            const uint64_t rg = a.gat_rng[qs];
+            const int64_t e0 = (int64_t)(uint32_t)rg + 2, e1 = (int64_t)(uint32_t)rg + (int64_t)(rg >> 32);
             int64_t mx = 0;
             for (int64_t e = e0 + lane; e < e1; e += 64) {
                 const int32_t sp = a.gat_spos[e];
@@ -492,17 +460,6 @@ hipError_t launch_k(const dd_sched *sch, const SoloArgs &args, hipStream_t s) {
 
 }  // namespace
 
-int64_t solo_batch_max(int64_t n, int64_t nsteps) {
-    // a wide step gives one batch per kSoloPos positions (rounded up), a
-    // group of narrow steps at most one batch per step
-    return nsteps + n / kSoloPos + 2;
-}
-
-hipError_t launch_batches(dd_sched *sch, hipStream_t s) {
-    k_batches<<<1, 1024, 0, s>>>(sch->n_steps, sch->step_ptr, kSoloPos, sch->bat, sch->nbat);
-    return hipGetLastError();
-}
-
 hipError_t launch_rm_bits(int64_t n, int32_t V, int32_t W, int64_t stride, const int32_t *order,
                           const uint32_t *rm, uint32_t *rmb, hipStream_t s) {
     const int64_t bx = (n + 255) / 256;
@@ -529,7 +486,7 @@ hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants
         e = launch_rm_bits(n, var->V, var->W, stride, sch->pos_node, var->rm_bits, rmb, s);
     }
     if (e == hipSuccess) {
-        SoloArgs args{sch->step_ptr, sch->so_rec, sch->gat_ptr, sch->gat_src, sch->gat_spos,
+        SoloArgs args{sch->step_ptr, sch->so_rec, sch->gat_rng, sch->gat_src, sch->gat_spos,
                       sch->gat_cls, g->gap, var->table, var->rm_bits, rmb, var->edge_on,
                       sch->mask & g->cross_mask, var->n_cls, var->V, var->W,
                       sch->thread_carry ? 1 : 0, stride, rings + 16, ring, finish, start, makespan,

@@ -65,7 +65,7 @@ __device__ __forceinline__ int64_t dec(uint64_t w) { return (int64_t)(w ^ (1ull 
 
 struct SplitArgs {
     const Rec *rec;
-    const int64_t *gat_ptr;       // [n+1] gathers of each position
+    const uint64_t *gat_rng;      // [n] gathers of each position: first entry | entries << 32
     const int32_t *gat_src;       // (gathers beyond two of a position)
     const uint8_t *gat_cls;
     const int32_t *thread_prev;   // [n] previous task on the thread
@@ -215,8 +215,9 @@ __global__ __launch_bounds__(kSpNT) void k_sim_phase(int32_t p, int32_t ps0, int
         if (r.g1_src >= 0 && cls_on(eon, r.cls >> 24))
             x = max64(x, d.f1 + ((d.r1w & vbit) ? 0 : d.g1));
         if (r.flags >> 8) {                    // gathers beyond two
-            const int64_t e1 = a.gat_ptr[q + 1];
-            for (int64_t e = a.gat_ptr[q] + 2; e < e1; e++)
+            const uint64_t rg = a.gat_rng[q];
+            const int64_t e1 = (int64_t)(uint32_t)rg + (int64_t)(rg >> 32);
+            for (int64_t e = (int64_t)(uint32_t)rg + 2; e < e1; e++)
                 if (cls_on(eon, a.gat_cls[e])) x = max64(x, rel(a.gat_src[e]));
         }
         const bool head = r.flags & 1u;
@@ -411,7 +412,7 @@ hipError_t run_phases(const dd_graph *g, const dd_sched *sch, const dd_variants 
                                                           makespan, var->V);
         e = hipGetLastError();
     }
-    SplitArgs args{sch->rec, sch->gat_ptr, sch->gat_src, sch->gat_cls, g->thread_prev, g->gap,
+    SplitArgs args{sch->rec, sch->gat_rng, sch->gat_src, sch->gat_cls, g->thread_prev, g->gap,
                    var->table, var->rm_bits, var->edge_on, var->V, var->W,
                    sch->thread_carry ? 1 : 0, ngrp, g_polls.load(), finish, start,
                    reinterpret_cast<unsigned long long *>(makespan), look};

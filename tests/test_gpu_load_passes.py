@@ -1,0 +1,131 @@
+"""The fused passes of graph load and levelization at their edges, through
+the C-ABI against the oracle: sizes around the tiles and chunks they cut a
+graph into, task ids in random order (more chain crossings between tiles
+than one workgroup ranks), arrays on the host, on the device and on the
+device at odd addresses, and the errors of each pass, which come back
+together."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2006_03318_amd import binding as B
+from paper_2006_03318_amd import workloads as W
+from tests.gpu_common import assert_equal_arrays, gpu_run, require_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(rng, n, T, shuffle=False):
+    g = W.random_graph_sparse(rng, n, T, mean_in=0.4, window=300, n_edge_cls=2, run_len=20)
+    if not shuffle:
+        return g
+    new = rng.permutation(n)                  # task u becomes new[u]
+    dst = np.repeat(np.arange(n), np.diff(g.in_ptr))
+    src, dst = new[g.in_src], new[dst]
+    o = np.argsort(dst, kind="stable")
+    ptr = np.zeros(n + 1, np.int64)
+    np.add.at(ptr, dst + 1, 1)
+    old = np.empty(n, np.int64)
+    old[new] = np.arange(n)
+    prev = g.thread_prev[old]
+    g.thread_prev = np.where(prev >= 0, new[prev], -1).astype(np.int32)
+    for f in ("thread_id", "dur", "gap", "node_cls"):
+        setattr(g, f, getattr(g, f)[old])
+    g.in_ptr, g.in_src, g.edge_cls = np.cumsum(ptr), src[o].astype(np.int32), g.edge_cls[o]
+    return g
+
+
+@pytest.mark.parametrize("n,T,shuffle", [
+    (1, 1, False), (255, 3, False), (1024, 2, False), (1025, 5, False), (2049, 70, False),
+    (5000, 4, True), (30_000, 20, True), (262_145, 3, False), (300_000, 300, False)])
+def test_sizes_and_id_orders(n, T, shuffle):
+    require_gpu()
+    rng = np.random.default_rng(700_000 + n + T)
+    g = _graph(rng, n, T, shuffle)
+    vs = W.random_variants(rng, g, 5, p_remove=0.2)
+    say("load passes n=%d T=%d shuffled=%d" % (n, T, shuffle))
+    S, F, M = gpu_run(g, vs)
+    oS, oF, oM, _ = O.run(g, vs)
+    assert_equal_arrays("makespan", M, oM)
+    assert_equal_arrays("finish", F, oF)
+    assert_equal_arrays("start", S, oS)
+
+
+def _load(g, where, **bad):
+    """dd_graph_load with every array on the host, on the device, or on the
+    device one byte off its alignment."""
+    import torch
+    a = dict(in_ptr=g.in_ptr, in_src=g.in_src, edge_cls=g.edge_cls, thread_prev=g.thread_prev,
+             thread_id=g.thread_id, dur=g.dur, gap=g.gap, node_cls=g.node_cls)
+    a.update(bad)
+    keep, ptr = [], []
+    for x in a.values():
+        x = np.ascontiguousarray(x)
+        if where == "host":
+            keep.append(x)
+            ptr.append(x.ctypes.data)
+        else:
+            shift = 1 if where == "odd" else 0
+            t = torch.zeros(x.nbytes + 8, dtype=torch.uint8, device="cuda")
+            t[shift:shift + x.nbytes] = torch.from_numpy(x.view(np.uint8).reshape(-1)).cuda()
+            torch.cuda.synchronize()
+            keep.append(t)
+            ptr.append(t.data_ptr() + shift)
+    import ctypes
+    out = ctypes.c_void_p()
+    rc = B.lib().dd_graph_load(g.n, g.n_threads, *ptr, None, ctypes.byref(out))
+    return rc, out
+
+
+@pytest.mark.parametrize("where", ["host", "device", "odd"])
+def test_where_the_arrays_are(where):
+    import torch
+    require_gpu()
+    rng = np.random.default_rng(710_000)
+    g = _graph(rng, 3000, 7)
+    want = O.steps(g)[1]
+    rc, h = _load(g, where)
+    assert rc == B.DD_OK, B.dd_last_error()
+    s, _ = B.dd_levelize(h, 3, B.DD_PHASES)
+    steps = torch.empty(g.n, dtype=torch.int32, device="cuda")
+    B.dd_sched_task_steps(s, steps)
+    B.dd_sched_free(s)
+    B.dd_graph_free(h)
+    assert_equal_arrays("phases", steps.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("where", ["host", "device"])
+def test_errors_of_every_pass(where):
+    require_gpu()
+    rng = np.random.default_rng(720_000)
+    g = _graph(rng, 3000, 4)
+    ordered = [u for u in range(g.n) if g.thread_id[u] == 0]
+
+    def changed(name, at, value):
+        a = getattr(g, name).copy()
+        a[at] = value
+        return {name: a}
+    back = int(np.nonzero(g.thread_id == g.thread_id[int(g.in_src[0])])[0][-1])
+    cases = [
+        (changed("thread_id", 5, 4), B.DD_EINVAL), (changed("dur", 7, -1), B.DD_EINVAL),
+        (changed("gap", 7, 1 << 62), B.DD_ERANGE), (changed("in_src", 3, g.n), B.DD_EINVAL),
+        (changed("edge_cls", 3, 64), B.DD_EINVAL), (changed("in_ptr", 1, -2), B.DD_EINVAL),
+        (changed("in_ptr", 0, 1), B.DD_EINVAL),
+        (changed("thread_prev", ordered[9], ordered[3]), B.DD_ECHAIN),
+        (changed("thread_prev", ordered[9], -1), B.DD_ECHAIN),
+        (changed("thread_prev", ordered[0], ordered[-1]), B.DD_ECHAIN),
+        (changed("thread_prev", ordered[9], g.n), B.DD_EINVAL)]
+    dst = int(np.nonzero(np.diff(g.in_ptr) > 0)[0][0])
+    k = int(g.in_ptr[dst])
+    later = int(np.nonzero(g.thread_id == g.thread_id[dst])[0][-1])
+    cases.append((changed("in_src", k, dst), B.DD_ECYCLE))
+    if later != dst:
+        cases.append((changed("in_src", k, later), B.DD_ECYCLE))
+    del back
+    for bad, want in cases:
+        say("load error", where, list(bad))
+        rc, h = _load(g, where, **bad)
+        assert rc == want and not h.value, (list(bad), rc, want, B.dd_last_error())
+    rc, h = _load(g, where)                   # and the next load is not affected
+    assert rc == B.DD_OK
+    B.dd_graph_free(h)
