@@ -513,43 +513,52 @@ dd_status dd_apply_transforms(const dd_graph *g, int32_t n_variants, int32_t n_c
     x->n_cls = n_cls;
     x->stream = s;
     dd_ratio *d_scale = nullptr;
-    uint32_t *err = nullptr;
-    uint32_t h_err[6] = {0, 0, 0, 0, 0, 0};
-    uint64_t *h_on = nullptr;
+    dd::TransformOut *o = nullptr, *o_dev = nullptr;
+    dd::TransformIn t{n_cls, n_variants, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
     const size_t cv = (size_t)n_cls * n_variants;
+    const size_t rmw = (size_t)g->n * x->W;
+    {
+        void *h = nullptr, *d = nullptr;
+        TRY(dd::direct_buf(&h, &d), "alloc read-back buffer");
+        o = static_cast<dd::TransformOut *>(h);
+        o_dev = static_cast<dd::TransformOut *>(d);
+        static_assert(sizeof(dd::TransformOut) <= dd::kDirectBytes, "results fit the buffer");
+    }
     TRY(dd::dalloc_n(&x->table, cv, s), "alloc table");
-    if (scale) TRY(copy_in(&d_scale, scale, cv, s), "copy scale");
-    TRY(copy_in(&err, (const uint32_t *)nullptr, 6, s), "alloc");
-    TRY(dd::launch_build_scale_table(d_scale, n_cls, n_variants, x->table, err, s), "scale table");
-    TRY(copy_in(&x->rm_bits, remove_bits, (size_t)g->n * x->W, s), "copy remove_bits");
+    if (scale && !on_device(scale, alignof(dd_ratio))) {
+        TRY(copy_in(&d_scale, scale, cv, s), "copy scale");
+        t.scale = d_scale;
+    } else {
+        t.scale = scale;
+    }
+    // removal bits: with the rest where they are few (a copy of its own
+    // costs a launch), else by the runtime's copy
+    if ((!remove_bits || on_device(remove_bits, sizeof(uint32_t))) && rmw <= ((size_t)2 << 20)) {
+        TRY(dd::dalloc_n(&x->rm_bits, rmw, s), "alloc remove_bits");
+        t.rm_src = remove_bits;
+        t.rm_dst = x->rm_bits;
+        t.rm_words = (int64_t)rmw;
+    } else {
+        TRY(copy_in(&x->rm_bits, remove_bits, rmw, s), "copy remove_bits");
+    }
     TRY(dd::dalloc_n(&x->edge_on, (size_t)n_variants, s), "alloc edge_on");
-    h_on = (uint64_t *)malloc(sizeof(uint64_t) * (size_t)n_variants);
-    if (!h_on) { st = fail(DD_ENOMEM, "host allocation"); goto fail_out; }
-    {
-        dd::ReadBack rb(s, sizeof(uint64_t) * (size_t)n_variants + sizeof(h_err));
-        if (edge_on) {
-            TRY(rb.add(h_on, edge_on, sizeof(uint64_t) * (size_t)n_variants), "read edge_on");
-        } else {
-            for (int32_t v = 0; v < n_variants; v++) h_on[v] = ~0ull;
-        }
-        TRY(rb.add(h_err, err, sizeof(h_err)), "read err");
-        TRY(rb.finish(), "sync");
+    t.on_dst = x->edge_on;
+    if (edge_on && !on_device(edge_on, sizeof(uint64_t))) {
+        TRY(hipMemcpyAsync(x->edge_on, edge_on, sizeof(uint64_t) * (size_t)n_variants, hipMemcpyDefault, s),
+            "copy edge_on");
+        t.on_src = x->edge_on;
+    } else {
+        t.on_src = edge_on;
     }
-    TRY(hipMemcpyAsync(x->edge_on, h_on, sizeof(uint64_t) * (size_t)n_variants, hipMemcpyHostToDevice, s), "copy edge_on");
-    x->used_mask = 0;
-    x->all_mask = ~0ull;
-    for (int32_t v = 0; v < n_variants; v++) {
-        x->used_mask |= h_on[v];
-        x->all_mask &= h_on[v];
-    }
-    x->any_magic = h_err[1] != 0;
-    if (h_err[0]) { st = map_err_bits(h_err[0]); goto fail_out; }
+    TRY(dd::transforms_device(t, x->table, o, o_dev, s), "transforms");
+    x->used_mask = o->used_mask;
+    x->all_mask = o->all_mask;
+    x->any_magic = o->magic != 0;
+    if (o->err) { st = map_err_bits(o->err); goto fail_out; }
     {
-        uint64_t pmax, rbits;
-        memcpy(&pmax, &h_err[2], 8);
-        memcpy(&rbits, &h_err[4], 8);
+        const uint64_t pmax = (uint64_t)o->pmax;
         double rmax;
-        memcpy(&rmax, &rbits, 8);
+        memcpy(&rmax, &o->rmax_bits, 8);
         // d * p must stay below 2^62, and so must every time in the simulation
         if ((__int128)g->dmax * (__int128)pmax >= ((__int128)1 << 62)) {
             st = fail(DD_ERANGE, "largest duration times largest p reaches 2^62");
@@ -566,18 +575,13 @@ dd_status dd_apply_transforms(const dd_graph *g, int32_t n_variants, int32_t n_c
                     (__int128)g->dmax * (__int128)pmax < ((__int128)1 << 53);
         x->quot_ok = x->f64_ok && (__int128)g->dmax * (__int128)pmax < ((__int128)1 << 50);
     }
-    TRY(hipStreamSynchronize(s), "sync");
     TRY(dd::note_use(g->uses, g->stream, s), "record stream use");
-    free(h_on);
     dd::dfree(d_scale, s);
-    dd::dfree(err, s);
     *out = x;
     return DD_OK;
 fail_out:
     (void)hipStreamSynchronize(s);
-    free(h_on);
     dd::dfree(d_scale, s);
-    dd::dfree(err, s);
     dd::dfree(x->table, s); dd::dfree(x->rm_bits, s); dd::dfree(x->edge_on, s);
     delete x;
     return st;

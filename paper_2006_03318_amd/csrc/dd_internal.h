@@ -284,9 +284,29 @@ struct LevelizeOut {
 dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sched *sch,
                           hipStream_t s, char *msg, size_t msg_len);
 
-// transforms (k_transform.hip)
-hipError_t launch_build_scale_table(const dd_ratio *scale_dev, int32_t n_cls, int32_t V,
-                                    ScaleEntry *table, uint32_t *err, hipStream_t s);
+// transforms (k_transform.hip): everything dd_apply_transforms does on the
+// device, complete on return
+constexpr int kTransformBlocks = 512;
+struct TransformIn {
+    int32_t n_cls, V;
+    const dd_ratio *scale;        // device, or null: 1/1
+    const uint64_t *on_src;       // device, or null: all classes
+    uint64_t *on_dst;
+    const uint32_t *rm_src;       // device, or null: none removed
+    uint32_t *rm_dst;
+    int64_t rm_words;             // 0: copied elsewhere
+};
+struct TransformOut {
+    uint64_t used_mask, all_mask; // OR and AND of the edge-class masks
+    uint32_t err, magic;          // error bits; some q is not a power of two
+    int64_t pmax, rmax_bits;      // largest p, largest p / q (bits of a double)
+    struct Block {
+        uint32_t err, magic;
+        int64_t pmax, rmax_bits;
+    } blk[kTransformBlocks];
+};
+DD_PASS hipError_t transforms_device(const TransformIn &t, ScaleEntry *table, TransformOut *out,
+                                     TransformOut *out_dev, hipStream_t s);
 
 // few-variant simulation (k_split.hip): every step cut across several
 // workgroups per variant, one launch per step.  split_width() gives the

@@ -23,20 +23,55 @@ __device__ uint32_t ceil_log2(uint32_t q) {
     return l;
 }
 
-constexpr int kTabBlocks = 512;   // grid-stride blocks: one set of atomics per block
+constexpr int kTabBlocks = kTransformBlocks;   // grid-stride blocks of the table
 
-__global__ __launch_bounds__(kBS) void k_scale_table(const dd_ratio *__restrict__ in, int64_t count,
-                                                     ScaleEntry *__restrict__ out,
-                                                     uint32_t *__restrict__ err,
-                                                     unsigned long long *__restrict__ pmax,
-                                                     unsigned long long *__restrict__ rmax_bits) {
+// One launch per call: the first blocks build the table and leave what they
+// saw (errors, bounds) in host memory, one line per block; one block copies
+// the edge-class masks and folds them; the rest copy the removal bits (large
+// ones are copied by the runtime).
+__global__ __launch_bounds__(kBS) void k_transforms(TransformIn t, ScaleEntry *__restrict__ table,
+                                                    int32_t tab_blocks, TransformOut *__restrict__ out) {
+    const int b = (int)blockIdx.x;
+    constexpr int NW = kBS / 64;
+    __shared__ int64_t red[4][NW];
+    const int w = threadIdx.x >> 6;
+    if (b > tab_blocks) {                            // removal bits
+        const int64_t step = (int64_t)(gridDim.x - tab_blocks - 1) * kBS;
+        for (int64_t i = (int64_t)(b - tab_blocks - 1) * kBS + threadIdx.x; i < t.rm_words; i += step)
+            t.rm_dst[i] = t.rm_src ? t.rm_src[i] : 0u;
+        return;
+    }
+    if (b == tab_blocks) {                           // edge classes
+        uint64_t any = 0, all = ~0ull;
+        for (int64_t v = threadIdx.x; v < t.V; v += kBS) {
+            const uint64_t m = t.on_src ? t.on_src[v] : ~0ull;
+            if (t.on_dst != t.on_src) t.on_dst[v] = m;
+            any |= m;
+            all &= m;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            any |= (uint64_t)shfl_xor64((int64_t)any, o);
+            all &= (uint64_t)shfl_xor64((int64_t)all, o);
+        }
+        if ((threadIdx.x & 63) == 0) { red[0][w] = (int64_t)any; red[1][w] = (int64_t)all; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 1; k < NW; k++) {
+                any |= (uint64_t)red[0][k];
+                all &= (uint64_t)red[1][k];
+            }
+            out->used_mask = any;
+            out->all_mask = all;
+        }
+        return;
+    }
     uint32_t e = 0, mg = 0;
     int64_t pm = 0;
     int64_t rb = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kBS + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * kBS) {
+    const int64_t count = (int64_t)t.n_cls * t.V;
+    for (int64_t i = (int64_t)b * kBS + threadIdx.x; i < count; i += (int64_t)tab_blocks * kBS) {
         int32_t p = 1, q = 1;
-        if (in) { p = in[i].p; q = in[i].q; }
+        if (t.scale) { p = t.scale[i].p; q = t.scale[i].q; }
         ScaleEntry se{0ull, 0u, 0u};
         if (p < 0 || q < 1) {
             e |= ERR_SCALE;
@@ -50,32 +85,29 @@ __global__ __launch_bounds__(kBS) void k_scale_table(const dd_ratio *__restrict_
                 // m = floor(2^(62+l) / q) + 1 by long division in base 2^32:
                 // 2^(62+l) = hi * 2^64 with hi = 2^(l-2) < q (l >= 2 here)
                 uint64_t r = 1ull << (l - 2);
-                uint64_t t = r << 32;
-                const uint64_t d1 = t / uq;
-                r = t % uq;
-                t = r << 32;
-                const uint64_t d0 = t / uq;
+                uint64_t x = r << 32;
+                const uint64_t d1 = x / uq;
+                r = x % uq;
+                x = r << 32;
+                const uint64_t d0 = x / uq;
                 se.magic = ((d1 << 32) | d0) + 1;  // q is not a power of two: remainder != 0
                 se.shift = l - 2;
                 mg = 1;
             }
             pm = p > pm ? p : pm;
             const double ratio = (double)p / (double)q;
-            const int64_t b = (int64_t)__double_as_longlong(ratio);   // order-preserving for ratio >= 0
-            rb = b > rb ? b : rb;
+            const int64_t bits = (int64_t)__double_as_longlong(ratio);   // order-preserving for ratio >= 0
+            rb = bits > rb ? bits : rb;
         }
-        out[i] = se;
+        table[i] = se;
     }
-    // wave, then the block's waves through LDS: one set of atomics per block
+    // wave, then the block's waves through LDS
     pm = wave_max64(pm);
     rb = wave_max64(rb);
     for (int o = 32; o > 0; o >>= 1) {
         e |= (uint32_t)__shfl_xor((int)e, o, 64);
         mg |= (uint32_t)__shfl_xor((int)mg, o, 64);
     }
-    constexpr int NW = kBS / 64;
-    __shared__ int64_t red[4][NW];
-    const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         red[0][w] = pm; red[1][w] = rb; red[2][w] = e; red[3][w] = mg;
     }
@@ -87,27 +119,31 @@ __global__ __launch_bounds__(kBS) void k_scale_table(const dd_ratio *__restrict_
             e |= (uint32_t)red[2][k];
             mg |= (uint32_t)red[3][k];
         }
-        atomic_or_hot(err, e);
-        atomic_or_hot(err + 1, mg);
-        atomic_max_hot(pmax, (unsigned long long)pm);
-        atomic_max_hot(rmax_bits, (unsigned long long)rb);
+        out->blk[b] = TransformOut::Block{e, mg, pm, rb};
     }
 }
 
 }  // namespace
 
-hipError_t launch_build_scale_table(const dd_ratio *scale_dev, int32_t n_cls, int32_t V,
-                                    ScaleEntry *table, uint32_t *err, hipStream_t s) {
-    // err[0] = error bits, err[1] = some q is not a power of two, err[2..3] = pmax,
-    // err[4..5] = max ratio bits (caller-zeroed)
-    const int64_t count = (int64_t)n_cls * V;
-    unsigned long long *pmax = reinterpret_cast<unsigned long long *>(err + 2);
-    unsigned long long *rmax = reinterpret_cast<unsigned long long *>(err + 4);
-    const int64_t nb = grid_for(count, kBS);
-    if (count > 0)
-        k_scale_table<<<(unsigned)(nb < kTabBlocks ? nb : kTabBlocks), kBS, 0, s>>>(scale_dev, count, table,
-                                                                                   err, pmax, rmax);
-    return hipGetLastError();
+hipError_t transforms_device(const TransformIn &t, ScaleEntry *table, TransformOut *out, TransformOut *out_dev,
+                             hipStream_t s) {
+    const int64_t nb = grid_for((int64_t)t.n_cls * t.V, kBS);
+    const int tab = (int)(nb < kTabBlocks ? nb : kTabBlocks);
+    int64_t rmb = (t.rm_words + 4 * kBS - 1) / (4 * kBS);
+    if (rmb > 512) rmb = 512;
+    k_transforms<<<(unsigned)(tab + 1 + rmb), kBS, 0, s>>>(t, table, tab, out_dev);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    out->err = out->magic = 0;
+    out->pmax = out->rmax_bits = 0;
+    for (int b = 0; b < tab; b++) {
+        out->err |= out->blk[b].err;
+        out->magic |= out->blk[b].magic;
+        if (out->blk[b].pmax > out->pmax) out->pmax = out->blk[b].pmax;
+        if (out->blk[b].rmax_bits > out->rmax_bits) out->rmax_bits = out->blk[b].rmax_bits;
+    }
+    return hipSuccess;
 }
 
 }  // namespace dd
