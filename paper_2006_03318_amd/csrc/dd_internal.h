@@ -353,7 +353,7 @@ hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants
                        int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s);
 
 // removal bits [n][W] as one bit string per variant, [V][stride] words
-// (stride even, at least n / 32), in the order of `order` (null: by task)
+// (stride even, at least n / 32), in the order of `order`
 hipError_t launch_rm_bits(int64_t n, int32_t V, int32_t W, int64_t stride, const int32_t *order,
                           const uint32_t *rm, uint32_t *rmb, hipStream_t s);
 

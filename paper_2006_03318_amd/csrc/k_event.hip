@@ -31,7 +31,8 @@
 // variants run at once: every variant is one wave of ~20 KB of LDS, eight
 // per CU, so about 2,000 variants are resident together.
 //
-// Two kernels.  k_sim_event_reg, below, serves what fits it; k_sim_event
+// Two kernels.  k_sim_event_reg, below, serves what fits it (at most 64
+// threads, 512 classes, 32-bit durations, every edge class on); k_sim_event
 // (described above) everything else.
 #include "dd_common.h"
 #include "dd_internal.h"
@@ -380,378 +381,421 @@ __global__ __launch_bounds__(64) void k_sim_event(EvArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// The same simulation with the frontier in registers: a lane holds up to
-// kRegK ready tasks, each with everything that dispatching it needs, so a
-// step reads global memory once, for its children's records.  What a step
-// costs is the chain of latencies when few variants run, and the
-// instructions of its wave when 2,048 do (two waves per SIMD), so both are
-// kept short:
-//   * every ready task carries its time max(P[thread], start) as a double
-//     (dd_time.h); dispatching raises the times of its thread's other ready
-//     tasks, and schedule(Q) is one DPP minimum over the lanes, resolved by
-//     a ballot (ties: by id, or by the priority rule);
-//   * the lane that loads a child's record is a lane with a free place, so a
-//     child that becomes ready is where it belongs; the records of its own
-//     first two children are touched at once, so that they are in the CU's
-//     cache when it is dispatched;
-//   * a child with one parent is ready at once; the others wait in a small
-//     LDS table (id -> parents done, start so far), buckets of four ids, so
-//     no per-variant array of counts and starts exists and none has to be
-//     cleared.
-// Capacity (ready tasks, table buckets) is not known beforehand: a wave that
-// runs out sets error bit 2 and stops, as do the others when they see it,
+// The same simulation with its state in registers and the task records in
+// LDS: one wave per variant, up to eight variants per workgroup, which share
+// one window of records.  What a step costs is the chain of latencies when
+// few variants run, and the instructions of its wave when 2,048 do (two
+// waves per SIMD), so both are kept short:
+//   * a lane holds up to kRegK ready tasks, each as its time max(P[thread],
+//     start) and one word with its id, thread and push/pull flag; dispatching
+//     raises the times of its thread's other ready tasks.  Dispatch times
+//     never fall, so all times are 32-bit differences to a base that moves up
+//     when they pass 2^31, and schedule(Q) is a 32-bit minimum over the lanes,
+//     resolved by a ballot (ties: by id, or by the priority rule);
+//   * while that minimum is taken, every lane reads the record of its own
+//     least task, so the winner's is there when the winner is known;
+//   * after S steps S tasks are done, and tasks that become ready lie near
+//     the S-th (they are numbered in trace order): the window holds
+//     [S - size / 2, S + size / 2) and moves on every kRegStage steps, with
+//     one barrier for all waves.  A record outside of it is read from memory;
+//   * an out-edge carries its child's word and number of parents, so nothing
+//     of a child is read before the child is dispatched.  A child with one
+//     parent is ready at once, the first in its parent's place; the others
+//     wait in kPendM places per lane (word, parents left, start so far),
+//     found by a ballot; the threads' progress is one register.
+// Capacity (ready and waiting tasks, times 2^31 ahead of the last dispatch)
+// is not known beforehand: a wave that runs out sets error bit 2 and stops, as do the others when they see it,
 // and the caller runs k_sim_event.
-// VGG-19 with P3's slices, P3 rule: 14,688 tasks x 2,048 variants 25.8 ms a
-// call (33.7 with k_sim_event), x 30 variants 22.7; 918 tasks x 30 variants,
-// default rule: 1.13 ms (1.43).
+// What bounds it: the instructions of one wave, about 2,000 cycles a step
+// (choosing the task 560, the priority rule up to 700 more, dispatch and
+// raised times 620, children 750); at 2,048 variants another 650, in which a
+// workgroup waits for its slowest wave.  VGG-19 with P3's slices, P3 rule,
+// 14,688 tasks x 2,048 variants: 21.1 ms a call (33.7 with k_sim_event); 918
+// tasks x 30 variants, default rule: 0.81 ms (1.43).
 constexpr int kRegK = 4;              // ready tasks per lane
-constexpr int kPendB = 256;           // buckets of four waiting tasks
-constexpr int kRegCls = 512;          // scale entries in LDS at most
-constexpr int kRegT = 1024;           // thread progress words in LDS at most
-constexpr int kRegN = 32768;          // tasks whose removal bits go to LDS at most
+constexpr int kPendM = 4;             // waiting tasks per lane
+constexpr int kRegCls = 512;          // scale entries in LDS at most (per wave)
+constexpr int kRegT = 64;             // threads at most
+constexpr int kRegWaves = 8;          // variants per workgroup at most
+constexpr int kRegStage = 256;        // steps between moves of the window
+constexpr size_t kRegLds = 160 * 1024 - 64;   // LDS of a compute unit, less the static part
 
-struct alignas(64) EvTask {
-    uint32_t dur, gap, ebeg, ecnt;    // duration and gap (below 2^32), out-edges
-    uint32_t meta;                    // thread, push/pull << 12, class << 16
-    int32_t prio;
-    uint32_t parents, pad;            // all parents (every edge class on)
-    uint4 e4;                         // its first four out-edges (child << 8 | class)
+// a task's word: id << 10 | thread << 4 | push/pull << 3, in the order of the
+// ids; in an out-edge, with the task's parents in the low bits (kMany: that
+// many or more)
+static_assert(kEventIdBits + 10 <= 32 && kRegT <= 64, "the word holds them");
+constexpr uint32_t kMany = 7, kWordPP = 8, kWordTh = 63u << 4;
+
+// a task's record:
+//   a = { duration, gap (below 2^32), class, priority }
+//   b = { its first two out-edges, first out-edge, out-edges }
+struct alignas(32) EvTask {
+    uint4 a, b;
 };
 
 __global__ __launch_bounds__(kBS) void k_ev_task(int32_t n, const int4 *__restrict__ rec,
-                                                 const uint4 *__restrict__ e4,
+                                                 const uint32_t *__restrict__ edges,
                                                  const int64_t *__restrict__ dur,
                                                  const int64_t *__restrict__ gap,
                                                  const int64_t *__restrict__ in_ptr,
                                                  const int32_t *__restrict__ prev,
                                                  const uint8_t *__restrict__ pp,
                                                  const int32_t *__restrict__ prio,
-                                                 EvTask *__restrict__ out) {
+                                                 EvTask *__restrict__ out, uint32_t *__restrict__ words,
+                                                 uint32_t *__restrict__ parents,
+                                                 uint32_t *__restrict__ roots) {
     const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
     if (u >= n) return;
+    auto count = [&](uint32_t c) {
+        return (uint32_t)(in_ptr[c + 1] - in_ptr[c]) + (prev[c] >= 0 ? 1u : 0u);
+    };
+    auto word = [&](uint32_t c) { return c << 10 | (uint32_t)rec[c].z << 4 | ((pp && pp[c]) ? kWordPP : 0u); };
     const int4 r = rec[u];
     EvTask t;
-    t.dur = (uint32_t)dur[u];
-    t.gap = (uint32_t)gap[u];
-    t.ebeg = (uint32_t)r.x;
-    t.ecnt = (uint32_t)r.y;
-    t.meta = (uint32_t)r.z | ((pp && pp[u]) ? 1u << 12 : 0u) | ((uint32_t)r.w << 16);
-    t.prio = prio ? prio[u] : 0;
-    t.parents = (uint32_t)(in_ptr[u + 1] - in_ptr[u]) + (prev[u] >= 0 ? 1u : 0u);
-    t.pad = 0;
-    t.e4 = e4[u];
+    t.a = make_uint4((uint32_t)dur[u], (uint32_t)gap[u], (uint32_t)r.w, prio ? (uint32_t)prio[u] : 0u);
+    t.b = make_uint4(0u, 0u, (uint32_t)r.x, (uint32_t)r.y);
+    for (int32_t j = 0; j < r.y; j++) {
+        const uint32_t c = edges[(int64_t)r.x + j] >> 8, k = count(c);
+        const uint32_t w = word(c) | (k < kMany ? k : kMany);
+        if (j == 0) t.b.x = w;
+        if (j == 1) t.b.y = w;
+        words[(int64_t)r.x + j] = w;
+    }
     out[u] = t;
+    const uint32_t k = count((uint32_t)u);
+    parents[u] = k;
+    if (k == 0) roots[1 + atomicAdd(&roots[0], 1u)] = word((uint32_t)u);
 }
 
 struct EvRegArgs {
-    int32_t n, V, W, T, n_cls;
+    int32_t n, V, W, n_cls, win;           // win: records of the window, a power of two
     const EvTask *__restrict__ task;
-    const uint32_t *__restrict__ edges;
+    const uint32_t *__restrict__ words;    // out-edges
+    const uint32_t *__restrict__ parents;  // [n]
+    const uint32_t *__restrict__ roots;    // count, then the tasks without parents
     const ScaleEntry *__restrict__ table;  // [n_cls][V]
     const uint32_t *__restrict__ rm;       // [n][W]
-    const uint32_t *__restrict__ rmb;      // [V][rmb_stride] removal bits by task, or null
-    int64_t rmb_stride;
     int64_t *finish, *start, *makespan;
     uint32_t *err;
 };
 
-// minimum over the wave (every lane active), in lane 63
-template <int CTRL, int RMASK>
-__device__ __forceinline__ double dpp_min_step(double x) {
-    const int64_t b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp((int)(uint32_t)b, (int)(uint32_t)b, CTRL, RMASK, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)((uint64_t)b >> 32), (int)((uint64_t)b >> 32), CTRL,
-                                               RMASK, 0xf, false);
-    return __builtin_fmin(x, __longlong_as_double(join64(lo, hi)));
-}
-__device__ __forceinline__ double wave_min_f64(double x) {
-    x = dpp_min_step<0x111, 0xf>(x);
-    x = dpp_min_step<0x112, 0xf>(x);
-    x = dpp_min_step<0x114, 0xf>(x);
-    x = dpp_min_step<0x118, 0xf>(x);
-    x = dpp_min_step<0x142, 0xa>(x);
-    x = dpp_min_step<0x143, 0xc>(x);
-    return __longlong_as_double(readlane64(__double_as_longlong(x), 63));
+// LDS of a workgroup: the window, then each wave's scale entries and removal
+// bits of the window
+inline size_t reg_lds(int win, int waves, int n_cls) {
+    return (size_t)win * sizeof(EvTask) + (size_t)waves * (sizeof(double2) * (size_t)n_cls + (size_t)win / 8);
 }
 
-// one place of the frontier
-struct EvSlot {
-    double t, dp;          // time (infinite: free), duration as transformed
-    uint32_t id, gap;      // id: task | kPPb | kRMb; gap as transformed
-    uint32_t th, ebeg, ecnt;
-    int32_t pr;
-    uint4 e4;
-};
+// orders by `hi`, then by `lo`
+__device__ __forceinline__ uint64_t pair(uint32_t hi, uint32_t lo) {
+    return (uint64_t)join64((int)lo, (int)hi);
+}
 
-template <bool START, bool PRIO, bool RLDS>
-__global__ __launch_bounds__(64, 2) void k_sim_event_reg(EvRegArgs a) {
-    __shared__ __align__(16) uint32_t pKey[kPendB * 4];   // waiting tasks: id + 1 (0: free)
-    __shared__ uint32_t pCnt[kPendB * 4];     // parents done
-    __shared__ unsigned long long pEst[kPendB * 4];   // start so far (times as double bits)
-    extern __shared__ double sLds[];          // [T] thread progress, [n_cls] {p, 1/q}, removal bits
-    double *const sP = sLds;
-    double2 *const sTab = reinterpret_cast<double2 *>(sLds + ((a.T + 1) & ~1));
-    uint32_t *const sRm = reinterpret_cast<uint32_t *>(sTab + a.n_cls);
-    const int lane = threadIdx.x;
-    const int v = blockIdx.x;
+template <bool START, bool PRIO>
+__global__ __launch_bounds__(64 * kRegWaves) void k_sim_event_reg(EvRegArgs a) {
+    extern __shared__ uint4 sWin[];           // [win][2], then per wave
+    __shared__ uint32_t sStop;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    double2 *const sTab = reinterpret_cast<double2 *>(sWin + 2 * a.win) +
+                          wave * (a.n_cls + a.win / 128);         // [n_cls] {p, 1/q}
+    uint32_t *const sRm = reinterpret_cast<uint32_t *>(sTab + a.n_cls);   // [win / 32]
+    const int v = blockIdx.x * waves + wave;
+    const bool mine = v < a.V;
     const int64_t V = a.V;
     const uint32_t vbit = 1u << (v & 31);
-    const uint32_t *const rmv = a.rm + (v >> 5);
-    const double kInf = __longlong_as_double(0x7ff0000000000000ll);
-    const double kZero = 4503599627370496.0;  // 2^52: time zero (dd_time.h)
-    for (int t = lane; t < a.T; t += 64) sP[t] = kZero;
+    const uint32_t *const rmv = a.rm + (mine ? v >> 5 : 0);
     for (int c = lane; c < a.n_cls; c += 64) {
-        const ScaleEntry e = a.table[(int64_t)c * V + v];
+        const ScaleEntry e = a.table[(int64_t)c * V + (mine ? v : 0)];
         sTab[c] = make_double2((double)e.p, inv_quotient(e));
     }
-    if (RLDS)
-        for (int i = lane; i < (a.n + 31) / 32; i += 64) sRm[i] = a.rmb[(int64_t)v * a.rmb_stride + i];
-    for (int i = lane; i < kPendB * 4; i += 64) {
-        pKey[i] = 0;
-        pCnt[i] = 0;
-        pEst[i] = 0;
-    }
-    __syncthreads();
-
-    EvSlot s[kRegK];
-#pragma unroll
-    for (int k = 0; k < kRegK; k++) {
-        s[k].t = kInf;
-        s[k].id = ~0u;
-        s[k].th = ~0u;
-        s[k].dp = 0;
-        s[k].gap = s[k].ebeg = s[k].ecnt = 0;
-        s[k].pr = 0;
-        s[k].e4 = make_uint4(0u, 0u, 0u, 0u);
-    }
-    uint32_t err = 0;
-    uint32_t touch0 = 0, touch1 = 0;
-    // a lane takes task c, ready at `est`, into place k
-    auto fill = [&](EvSlot &z, uint32_t c, const uint4 &w0, const uint4 &w1, const uint4 &w2,
-                    uint32_t rmw, double est) {
-        const bool gone = RLDS ? (sRm[c >> 5] >> (c & 31)) & 1u : (rmw & vbit) != 0u;
-        const double2 sc = sTab[w1.x >> 16];
-        z.th = w1.x & 0xfffu;
-        const double p = sP[z.th];
-        z.t = __builtin_fmax(p, est);
-        z.dp = gone ? 0.0 : scale_f64((double)w0.x, sc.x, sc.y);
-        z.gap = gone ? 0u : w0.y;
-        z.id = c | ((w1.x & (1u << 12)) ? kPPb : 0u) | (gone ? kRMb : 0u);
-        z.ebeg = w0.z;
-        z.ecnt = w0.w;
-        z.pr = (int32_t)w1.y;
-        z.e4 = w2;
-    };
-    auto words = [&](uint32_t c, uint4 &w0, uint4 &w1, uint4 &w2, uint32_t &rmw) {
-        const uint4 *r = reinterpret_cast<const uint4 *>(a.task + c);
-        w0 = r[0];
-        w1 = r[1];
-        w2 = r[2];
-        rmw = RLDS ? 0u : rmv[(int64_t)c * a.W];
-    };
-
-    // tasks without parents
-    for (int32_t base = 0; base < a.n; base += 64) {
-        const int32_t u = base + lane;
-        const bool root = u < a.n && a.task[u < a.n ? u : 0].parents == 0u;
-        uint64_t todo = __ballot(root);
-        while (todo) {
-            int kk = -1;
-            uint64_t fr = 0;
-#pragma unroll
-            for (int k = kRegK - 1; k >= 0; k--) {
-                const uint64_t f = __ballot(s[k].t == kInf);
-                if (f) { kk = k; fr = f; }
-            }
-            if (kk < 0) { err |= 4u; break; }
-            // the r-th free lane takes the r-th root of the block
-            const int r = __popcll(fr & ((1ull << lane) - 1ull));
-            const bool mine = ((fr >> lane) & 1ull) && r < __popcll(todo);
-            uint64_t m = todo;
-            int at = 0;
-            for (int i = 0; i <= r && m; i++) {
-                at = __ffsll((unsigned long long)m) - 1;
-                m &= m - 1;
-            }
-            if (mine) {
-                uint4 w0, w1, w2;
-                uint32_t rw;
-                words((uint32_t)(base + at), w0, w1, w2, rw);
-#pragma unroll
-                for (int k = 0; k < kRegK; k++)
-                    if (k == kk) fill(s[k], (uint32_t)(base + at), w0, w1, w2, rw, kZero);
-            }
-            int took = __popcll(fr) < __popcll(todo) ? __popcll(fr) : __popcll(todo);
-            for (; took > 0; took--) todo &= todo - 1;
+    // tasks [t0, t1) come into the window (both multiples of 64)
+    auto stage = [&](int32_t t0, int32_t t1) {
+#pragma unroll 4
+        for (int32_t t = t0 + (int32_t)threadIdx.x; t < t1 && t < a.n; t += (int32_t)blockDim.x) {
+            const EvTask r = a.task[t];
+            const int at = 2 * (t & (a.win - 1));
+            sWin[at] = r.a;
+            sWin[at + 1] = r.b;
         }
-        if (err) break;
+#pragma unroll 4
+        for (int32_t t = t0; t < t1 && t < a.n; t += 64) {
+            const int32_t u = t + lane;
+            const uint64_t gone = __ballot(u < a.n && (rmv[(int64_t)(u < a.n ? u : 0) * a.W] & vbit));
+            if (lane < 2) sRm[((t & (a.win - 1)) >> 5) + lane] = (uint32_t)(gone >> (32 * lane));
+        }
+    };
+
+    uint32_t t[kRegK], key[kRegK];            // ready tasks: time, word (both ~0: free)
+    uint32_t pr[kRegK];                       // priority, descending (PRIO, push/pull tasks)
+    uint32_t pid[kPendM], left[kPendM];       // waiting tasks: word (~0: free), parents left,
+    uint32_t pst[kPendM];                     // start so far
+    uint32_t P = 0;                           // progress of thread `lane`
+#pragma unroll
+    for (int k = 0; k < kRegK; k++) t[k] = key[k] = pr[k] = ~0u;
+#pragma unroll
+    for (int m = 0; m < kPendM; m++) {
+        pid[m] = ~0u;
+        left[m] = pst[m] = 0u;
+    }
+    uint32_t err = 0;                         // (uniform)
+    const bool whole = a.n <= a.win;          // the window holds every task
+    int32_t lo = whole ? 0 : -(a.win / 2);    // first task of the window
+    const uint32_t wmask = (uint32_t)(a.win - 1);
+
+    // task `w`, ready at x, into place pk of lane pl; pl < 0: any free one
+    auto put = [&](uint32_t w, uint32_t x, int pl, int pk) {
+        if (pl < 0) {
+            int fk = -1;
+#pragma unroll
+            for (int k = kRegK - 1; k >= 0; k--) fk = key[k] == ~0u ? k : fk;
+            const uint64_t f = __ballot(fk >= 0);
+            if (f == 0) {
+                err = 4u;
+                return;
+            }
+            pl = __ffsll((unsigned long long)f) - 1;
+            pk = __builtin_amdgcn_readlane(fk, pl);
+        }
+        const int at = lane == pl ? pk : -1;
+#pragma unroll
+        for (int k = 0; k < kRegK; k++) {
+            t[k] = at == k ? x : t[k];
+            key[k] = at == k ? w : key[k];
+        }
+        if (PRIO && (w & kWordPP)) {
+            const uint32_t c = w >> 10;
+            const uint32_t d =
+                c - (uint32_t)lo < (uint32_t)a.win ? sWin[2 * (c & wmask)].w : a.task[c].a.w;
+#pragma unroll
+            for (int k = 0; k < kRegK; k++) pr[k] = at == k ? ~(d ^ 0x80000000u) : pr[k];
+        }
+    };
+    // one more parent of task `w` is done, at rel (it has k of them); true
+    // when it was the last, est then its start
+    auto arrive = [&](uint32_t w, uint32_t k, uint32_t rel, uint32_t &est) -> bool {
+        est = rel;
+        if (k == 1u) return true;
+        int hm = -1;
+        uint32_t lf = 0, ps = 0;
+#pragma unroll
+        for (int m = 0; m < kPendM; m++) {
+            const bool h = pid[m] == w;
+            hm = h ? m : hm;
+            lf = h ? left[m] : lf;
+            ps = h ? pst[m] : ps;
+        }
+        const uint64_t hit = __ballot(hm >= 0);
+        if (hit == 0) {
+            int fm = -1;
+#pragma unroll
+            for (int m = kPendM - 1; m >= 0; m--) fm = pid[m] == ~0u ? m : fm;
+            const uint64_t f = __ballot(fm >= 0);
+            if (f == 0) {
+                err = 4u;
+                return false;
+            }
+            if (k == kMany) k = __builtin_amdgcn_readfirstlane(a.parents[w >> 10]);
+            const int at = lane == __ffsll((unsigned long long)f) - 1 ? fm : -1;
+#pragma unroll
+            for (int m = 0; m < kPendM; m++) {
+                pid[m] = at == m ? w : pid[m];
+                left[m] = at == m ? k - 1u : left[m];
+                pst[m] = at == m ? rel : pst[m];
+            }
+            return false;
+        }
+        const int l = __ffsll((unsigned long long)hit) - 1;
+        const uint32_t now_left = __builtin_amdgcn_readlane(lf, l) - 1u;
+        const uint32_t p = __builtin_amdgcn_readlane(ps, l);
+        est = p > rel ? p : rel;
+        const uint32_t nw = now_left == 0u ? ~0u : w;
+#pragma unroll
+        for (int m = 0; m < kPendM; m++) {    // (hm: the lane that holds it only)
+            pid[m] = hm == m ? nw : pid[m];
+            left[m] = hm == m ? now_left : left[m];
+            pst[m] = hm == m ? est : pst[m];
+        }
+        return now_left == 0u;
+    };
+    // the same for an out-edge; a child that becomes ready goes to place pk of
+    // lane pl (pl < 0: any), and true is returned
+    auto child = [&](uint32_t e, uint32_t rel, int pl, int pk) -> bool {
+        const uint32_t w = e & ~7u;
+        uint32_t est;
+        if (!arrive(w, e & 7u, rel, est)) return false;
+        const uint32_t p = __builtin_amdgcn_readlane(P, (w & kWordTh) >> 4);
+        put(w, p > est ? p : est, pl, pk);
+        return true;
+    };
+
+    stage(0, whole ? (a.n + 63) & ~63 : a.win / 2);
+    __syncthreads();
+    if (mine) {
+        const uint32_t nr = __builtin_amdgcn_readfirstlane(a.roots[0]);
+        for (uint32_t i = 0; i < nr && !err; i++) put(__builtin_amdgcn_readfirstlane(a.roots[1 + i]), 0u, -1, 0);
     }
 
-    double ms = kZero;
+    int64_t base = 0, ms = 0;       // time of the 32-bit zero; makespan
     int32_t done = 0;
     uint32_t bu = 0;                // this lane's buffered result: task, finish, start
-    double bf = kZero, bs = kZero;
-    err = __any(err != 0u) ? 4u : 0u;
-    while (!err) {
-        // ---- schedule(Q) ----
-        double tl = s[0].t;
-#pragma unroll
-        for (int k = 1; k < kRegK; k++) tl = __builtin_fmin(tl, s[k].t);
-        const double T0 = wave_min_f64(tl);
-        if (T0 == kInf) break;                            // the frontier is empty
-        uint32_t key = ~0u;                               // least id of the lane's tasks of that time
-#pragma unroll
-        for (int k = 0; k < kRegK; k++) {
-            const uint32_t i = s[k].t == T0 ? s[k].id & kIdMask : ~0u;
-            key = i < key ? i : key;
+    int64_t bf = 0, bs = 0;
+    bool run = mine && !err;        // (uniform per wave)
+    for (int32_t S = 0; S < a.n; S += kRegStage) {
+        // ---- the window moves on; every wave has done S steps or has ended ----
+        if (S > 0) {
+            if (threadIdx.x == 0) sStop = load_coherent(a.err) & 4u;
+            if (!whole) {
+                __syncthreads();
+                lo = S - a.win / 2;
+                stage(S + a.win / 2 - kRegStage, S + a.win / 2);
+            }
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(sStop)) break;   // some wave ran out of room: this run is thrown away
+            __syncthreads();
         }
-        uint32_t wid;
-        {
-            const uint64_t at = __ballot(key != ~0u);
-            if ((at & (at - 1)) == 0) wid = __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)at) - 1);
-            else wid = wave_min_u32(key);
-        }
-        if (PRIO) {
-            // when it is a push/pull task: of those of least time, the one of
-            // highest priority, least id among equals
-            bool ppw = false;
+        for (int i = 0; i < kRegStage && run; i++) {
+            // ---- schedule(Q): this lane's least task, and its record ----
+            uint32_t bt = t[0], bk = key[0];
+            int kk = 0;
 #pragma unroll
-            for (int k = 0; k < kRegK; k++) ppw |= s[k].t == T0 && s[k].id == ((s[k].id & kRMb) | kPPb | wid);
-            if (__any(ppw)) {
-                uint32_t best = ~0u;                      // descending priority
+            for (int k = 1; k < kRegK; k++) {
+                const bool less = pair(t[k], key[k]) < pair(bt, bk);
+                bt = less ? t[k] : bt;
+                bk = less ? key[k] : bk;
+                kk = less ? k : kk;
+            }
+            uint4 ra, rb;
+            uint32_t rw;
+            double2 sc;
+            auto record = [&](uint32_t w) {               // (one outside of the window: any other)
+                const uint32_t i = (w >> 10) & wmask;
+                ra = sWin[2 * i];
+                rb = sWin[2 * i + 1];
+                rw = sRm[i >> 5];
+            };
+            auto scale = [&] { sc = sTab[ra.z < (uint32_t)a.n_cls ? ra.z : 0u]; };
+            record(bk);
+            // ---- the least of all ----
+            const uint32_t T0 = __builtin_amdgcn_readfirstlane(wave_min_u32(bt));
+            if (T0 == ~0u) {                              // the frontier is empty
+                run = false;
+                break;
+            }
+            scale();
+            int wl;                                       // the winner's lane
+            {
+                uint64_t at = __ballot(bt == T0);
+                if (at & (at - 1)) at = __ballot(bk == wave_min_u32(bt == T0 ? bk : ~0u));
+                wl = __ffsll((unsigned long long)at) - 1;
+            }
+            uint32_t wkey = __builtin_amdgcn_readlane(bk, wl);
+            int wk = __builtin_amdgcn_readlane(kk, wl);
+            if (PRIO && (wkey & kWordPP)) {
+                // a push/pull task: of those of least time, the one of highest
+                // priority, least id among equals
+                uint32_t bd = ~0u, bw = ~0u;
+                int bi = 0;
 #pragma unroll
                 for (int k = 0; k < kRegK; k++) {
-                    const uint32_t d = ~((uint32_t)s[k].pr ^ 0x80000000u);
-                    if (s[k].t == T0 && (s[k].id & kPPb) && d < best) best = d;
+                    const bool less = t[k] == T0 && (key[k] & kWordPP) &&
+                                      pair(pr[k], key[k]) < pair(bd, bw);
+                    bd = less ? pr[k] : bd;
+                    bw = less ? key[k] : bw;
+                    bi = less ? k : bi;
                 }
-                const uint32_t b0 = wave_min_u32(best);
-                key = ~0u;
-#pragma unroll
-                for (int k = 0; k < kRegK; k++) {
-                    const uint32_t d = ~((uint32_t)s[k].pr ^ 0x80000000u);
-                    const uint32_t i = s[k].t == T0 && (s[k].id & kPPb) && d == b0 ? s[k].id & kIdMask : ~0u;
-                    key = i < key ? i : key;
-                }
-                const uint64_t at = __ballot(key != ~0u);
-                if ((at & (at - 1)) == 0)
-                    wid = __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)at) - 1);
-                else
-                    wid = wave_min_u32(key);
+                record(bw);
+                uint64_t at = __ballot(bw != ~0u);
+                const uint32_t b0 = wave_min_u32(bd);
+                if (at & (at - 1)) at = __ballot(bd == b0 && bw != ~0u);
+                scale();
+                if (at & (at - 1)) at = __ballot(bw == wave_min_u32(bd == b0 ? bw : ~0u));
+                wl = __ffsll((unsigned long long)at) - 1;
+                wk = __builtin_amdgcn_readlane(bi, wl);
+                wkey = __builtin_amdgcn_readlane(bw, wl);
             }
-        }
-        // ---- dispatch: the winner's fields, uniform ----
-        uint32_t id = 0, th = 0, ebeg = 0, ecnt = 0, gp = 0, x0 = 0, x1 = 0, x2 = 0, x3 = 0;
-        double dp = 0;
-#pragma unroll
-        for (int k = 0; k < kRegK; k++) {
-            const uint64_t at = __ballot(s[k].t == T0 && (s[k].id & kIdMask) == wid);
-            if (at) {
-                const int l = __ffsll((unsigned long long)at) - 1;
-                id = __builtin_amdgcn_readlane(s[k].id, l);
-                th = __builtin_amdgcn_readlane(s[k].th, l);
-                ebeg = __builtin_amdgcn_readlane(s[k].ebeg, l);
-                ecnt = __builtin_amdgcn_readlane(s[k].ecnt, l);
-                gp = __builtin_amdgcn_readlane(s[k].gap, l);
-                x0 = __builtin_amdgcn_readlane(s[k].e4.x, l);
-                x1 = __builtin_amdgcn_readlane(s[k].e4.y, l);
-                x2 = __builtin_amdgcn_readlane(s[k].e4.z, l);
-                x3 = __builtin_amdgcn_readlane(s[k].e4.w, l);
-                dp = __longlong_as_double(readlane64(__double_as_longlong(s[k].dp), l));
-                if (lane == l) s[k].t = kInf;
+            const uint32_t id = wkey >> 10;
+            if (id - (uint32_t)lo >= (uint32_t)a.win) {   // not in the window
+                ra = a.task[id].a;
+                rb = a.task[id].b;
+                rw = (rmv[(int64_t)id * a.W] & vbit) ? ~0u : 0u;
+                scale();
             }
-        }
-        const double f = T0 + dp;
-        const double rel = f + (double)gp;
-        if (!(id & kRMb)) ms = __builtin_fmax(ms, f);
-        // results go out 64 at a time, one per lane
-        if (lane == (done & 63)) {
-            bu = wid;
-            bf = f;
-            bs = T0;
-        }
-        done++;
-        if ((done & 63) == 0) {
-            a.finish[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bf));
-            if (START) a.start[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bs));
-            // another wave ran out of room: this run is thrown away
-            if (load_coherent(a.err) & 4u) break;
-        }
-        sP[th] = rel;
-#pragma unroll
-        for (int k = 0; k < kRegK; k++)
-            s[k].t = s[k].th == th ? __builtin_fmax(s[k].t, rel) : s[k].t;   // (free places stay infinite)
-        // ---- children ----
-        for (uint32_t base = 0; base < ecnt;) {
-            int kk = -1;
-            uint64_t fr = 0;
-#pragma unroll
-            for (int k = kRegK - 1; k >= 0; k--) {
-                const uint64_t z = __ballot(s[k].t == kInf);
-                if (z) { kk = k; fr = z; }
+            // ---- dispatch ----
+            const bool gone = (__builtin_amdgcn_readlane(rw, wl) >> (id & 31u)) & 1u;
+            const double kTop = 4294967295.0;
+            const double fd = gone ? 0.0 : scale_f64((double)ra.x, sc.x, sc.y);
+            const double fl = __builtin_fmin(fd + (double)T0, kTop);
+            const double rl = __builtin_fmin(fl + (gone ? 0.0 : (double)ra.y), kTop);
+            const uint32_t f = __builtin_amdgcn_readlane((uint32_t)fl, wl);
+            const uint32_t rel = __builtin_amdgcn_readlane((uint32_t)rl, wl);
+            const uint32_t ecnt = __builtin_amdgcn_readlane(rb.w, wl);
+            if (rel == ~0u) {                             // too far ahead
+                err = 4u;
+                run = false;
+                break;
             }
-            if (kk < 0) { err = 4u; break; }
-            const uint32_t r = base + (uint32_t)__popcll(fr & ((1ull << lane) - 1ull));
-            const bool mine = ((fr >> lane) & 1ull) && r < ecnt;
-            base += (uint32_t)__popcll(fr);
-            uint32_t c = (r == 0 ? x0 : r == 1 ? x1 : r == 2 ? x2 : x3) >> 8;
-            if (ecnt > 4u) {
-                if (mine && r >= 4u) c = a.edges[(int64_t)ebeg + r] >> 8;
+            const int64_t f64 = base + f;
+            if (!gone) ms = f64 > ms ? f64 : ms;
+            // results go out 64 at a time, one per lane
+            if (lane == (done & 63)) {
+                bu = id;
+                bf = f64;
+                bs = base + T0;
             }
-            bool ready = false;
-            if (mine) {
-                uint4 w0, w1, w2;
-                uint32_t rw;
-                words(c, w0, w1, w2, rw);
-                double est = rel;
-                ready = w1.z == 1u;
-                if (!ready) {
-                    // find the child in its bucket, or take a free word there
-                    const uint32_t b = (c >> 1) & (kPendB - 1);
-                    uint32_t *const kb = pKey + b * 4u;
-                    const uint32_t k0 = kb[0], k1 = kb[1], k2 = kb[2], k3 = kb[3];
-                    int e = k0 == c + 1u ? 0 : k1 == c + 1u ? 1 : k2 == c + 1u ? 2 : k3 == c + 1u ? 3 : -1;
-                    for (int i = 0; i < 4 && e < 0; i++) {
-                        const uint32_t was = atomicCAS(&kb[i], 0u, c + 1u);
-                        if (was == 0u || was == c + 1u) e = i;
-                    }
-                    if (e < 0) {
-                        err = 4u;
-                    } else {
-                        const uint32_t p = b * 4u + (uint32_t)e;
-                        // (bit patterns of nonnegative doubles order as integers)
-                        const unsigned long long oe =
-                            atomicMax(&pEst[p], (unsigned long long)__double_as_longlong(rel));
-                        const uint32_t before = atomicAdd(&pCnt[p], 1u);
-                        if (before + 1u == w1.z) {        // its last parent: out of the table
-                            ready = true;
-                            est = __builtin_fmax(rel, __longlong_as_double((long long)oe));
-                            pCnt[p] = 0;
-                            pEst[p] = 0;
-                            kb[e] = 0;
+            done++;
+            if ((done & 63) == 0) {
+                a.finish[(int64_t)bu * V + v] = bf;
+                if (START) a.start[(int64_t)bu * V + v] = bs;
+            }
+            P = lane == (int)((wkey & kWordTh) >> 4) ? rel : P;
+            const int out = lane == wl ? wk : -1;
+#pragma unroll
+            for (int k = 0; k < kRegK; k++) {             // (free places keep ~0)
+                const uint32_t up = t[k] > rel ? t[k] : rel;
+                t[k] = ((key[k] ^ wkey) & kWordTh) == 0u ? up : t[k];
+                t[k] = out == k ? ~0u : t[k];
+                key[k] = out == k ? ~0u : key[k];
+            }
+            // ---- children: the first ready one takes its parent's place ----
+            if (ecnt > 0u) {
+                const uint32_t e0 = __builtin_amdgcn_readlane(rb.x, wl);
+                const uint32_t e1 = __builtin_amdgcn_readlane(rb.y, wl);
+                const uint32_t ebeg = __builtin_amdgcn_readlane(rb.z, wl);
+                if (child(e0, rel, wl, wk)) wl = -1;
+                if (ecnt > 1u) {
+                    if (child(e1, rel, wl, wk)) wl = -1;
+                    uint32_t more = 0;
+                    for (uint32_t j = 2u; j < ecnt && !err; j++) {
+                        const uint32_t l = (j - 2u) & 63u;
+                        if (l == 0u) {                    // 64 more out-edges, one per lane
+                            const uint32_t i = j + (uint32_t)lane;
+                            more = a.words[(int64_t)ebeg + (i < ecnt ? i : j)];
                         }
+                        if (child(__builtin_amdgcn_readlane(more, l), rel, wl, wk)) wl = -1;
                     }
                 }
-                if (ready) {
-#pragma unroll
-                    for (int k = 0; k < kRegK; k++)
-                        if (k == kk) fill(s[k], c, w0, w1, w2, rw, est);
-                    // bring the records of its first two children into the cache
-                    asm volatile("" ::"v"(touch0), "v"(touch1));   // (of an earlier step)
-                    touch0 = a.task[w2.x >> 8].dur;
-                    touch1 = a.task[w2.y >> 8].dur;
-                }
             }
-            if (__any(err != 0u)) { err = 4u; break; }
+            if (T0 >= 1u << 31) {                         // the base moves up
+                base += T0;
+#pragma unroll
+                for (int k = 0; k < kRegK; k++) t[k] -= key[k] == ~0u ? 0u : T0;
+#pragma unroll
+                for (int m = 0; m < kPendM; m++) pst[m] = pst[m] > T0 ? pst[m] - T0 : 0u;
+                P = P > T0 ? P - T0 : 0u;
+            }
+            if (err) run = false;
         }
-        if (__any(err != 0u)) { err = 4u; break; }
+        if (err && lane == 0) atomicOr(a.err, err);
     }
+    if (!mine) return;
     if (lane < (done & 63)) {
-        a.finish[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bf));
-        if (START) a.start[(int64_t)bu * V + v] = Tm<true>::to_time(__double_as_longlong(bs));
+        a.finish[(int64_t)bu * V + v] = bf;
+        if (START) a.start[(int64_t)bu * V + v] = bs;
     }
     if (done != a.n && !err) err = 1u;
     if (lane == 0) {
-        a.makespan[v] = Tm<true>::to_time(__double_as_longlong(ms));
+        a.makespan[v] = ms;
         if (err) atomicOr(a.err, err);
     }
 }
@@ -827,41 +871,39 @@ hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_va
         if (g->n == 0 || !var->quot_ok || g->dmax >= (int64_t(1) << 32) || g->gmax >= (int64_t(1) << 32) ||
             var->n_cls > kRegCls || g->n_threads > kRegT || (ev.cls_mask & ~var->all_mask))
             return hipErrorNotSupported;
+        // the window takes most of a CU's LDS, so one workgroup runs on a CU:
+        // the fewest variants per workgroup with which all run at once, and
+        // the largest window that fits beside their scale tables
+        int waves = 1, win = 4096;
+        while (waves < kRegWaves && (int64_t)waves * 256 < var->V) waves *= 2;
+        while (reg_lds(win, waves, var->n_cls) > kRegLds) win /= 2;
         EvTask *task = nullptr;
+        uint32_t *words = nullptr, *parents = nullptr, *roots = nullptr;
         hipError_t e = dalloc_n(&task, (size_t)g->n, s);
-        if (e != hipSuccess) return e;
-        k_ev_task<<<grid_for(g->n, kBS), kBS, 0, s>>>(g->n, ev.rec, ev.e4, g->dur, g->gap, g->xin_ptr,
-                                                     g->thread_prev, pp, prio, task);
-        const bool rlds = g->n <= kRegN;
-        const int64_t stride = (g->n + 63) / 64 * 2;
-        uint32_t *rmb = nullptr;
-        if (rlds) {
-            e = dalloc_n(&rmb, (size_t)var->V * (size_t)stride, s);
-            if (e == hipSuccess)
-                e = launch_rm_bits(g->n, var->V, var->W, stride, nullptr, var->rm_bits, rmb, s);
-            if (e != hipSuccess) {
-                dfree(task, s);
-                dfree(rmb, s);
-                return e;
-            }
+        if (e == hipSuccess) e = dalloc_n(&words, (size_t)ev.n_edges + 1, s);
+        if (e == hipSuccess) e = dalloc_n(&parents, (size_t)g->n, s);
+        if (e == hipSuccess) e = dalloc_n(&roots, (size_t)g->n + 1, s);
+        if (e == hipSuccess) e = hipMemsetAsync(roots, 0, sizeof(uint32_t), s);
+        if (e == hipSuccess) {
+            k_ev_task<<<grid_for(g->n, kBS), kBS, 0, s>>>(g->n, ev.rec, ev.edges, g->dur, g->gap, g->xin_ptr,
+                                                          g->thread_prev, pp, prio, task, words, parents, roots);
+            const EvRegArgs r{g->n, var->V, var->W, var->n_cls, win, task, words, parents, roots,
+                              var->table, var->rm_bits, finish, start, makespan, err};
+            auto go = [&](auto st, auto pr) {
+                k_sim_event_reg<decltype(st)::value, decltype(pr)::value>
+                    <<<(var->V + waves - 1) / waves, 64 * waves, reg_lds(win, waves, var->n_cls), s>>>(r);
+            };
+            const std::true_type yes{};
+            const std::false_type no{};
+            auto by_pr = [&](auto st) { if (policy == DD_POLICY_PRIORITY) go(st, yes); else go(st, no); };
+            if (start) by_pr(yes);
+            else by_pr(no);
+            e = hipGetLastError();
         }
-        EvRegArgs r{g->n, var->V, var->W, g->n_threads, var->n_cls, task, ev.edges, var->table,
-                    var->rm_bits, rmb, stride, finish, start, makespan, err};
-        const size_t lds = sizeof(double) * (size_t)((g->n_threads + 1) & ~1) +
-                           sizeof(double2) * (size_t)var->n_cls + (rlds ? sizeof(uint32_t) * (size_t)stride : 0);
-        auto go = [&](auto st, auto pr, auto rl) {
-            k_sim_event_reg<decltype(st)::value, decltype(pr)::value, decltype(rl)::value>
-                <<<var->V, 64, lds, s>>>(r);
-        };
-        const std::true_type yes{};
-        const std::false_type no{};
-        auto by_rl = [&](auto st, auto pr) { if (rlds) go(st, pr, yes); else go(st, pr, no); };
-        auto by_pr = [&](auto st) { if (policy == DD_POLICY_PRIORITY) by_rl(st, yes); else by_rl(st, no); };
-        if (start) by_pr(yes);
-        else by_pr(no);
-        e = hipGetLastError();
         dfree(task, s);
-        dfree(rmb, s);
+        dfree(words, s);
+        dfree(parents, s);
+        dfree(roots, s);
         return e;
     }
     EvArgs a;
