@@ -250,16 +250,37 @@ struct KahnArgs {
 // memory); beyond that they stay in the global arrays.
 constexpr int kLdsT = 2048;
 constexpr int kProbe = 128;     // candidates a round probes per thread before the long-run scan
+constexpr int kSegBuf = 2048;   // segments and rounds kept in LDS before they go out
+constexpr int kAhead = 3;       // probes whose entries are loaded a round ahead
+constexpr int kLong = 4;        // candidates per lane and step of that scan
 
+// sums over the lanes up to and including this one (every lane active)
+__device__ __forceinline__ int wave_scan_add(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// One round is a chain of latencies in one workgroup, 2.1 us with 51 threads
+// (100 rounds of the 32,815-task data-parallel trace, two of them runs of
+// 15,000 candidates together): the probes 1.4, barriers 0.3, numbering the
+// segments 0.4.  2.5 us a round when each began with a load of its
+// candidates, looked through long requirement lists from their start, and
+// stored its segments before its last barrier.
 template <bool L>
 __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
-    __shared__ int s_nlong;
-    __shared__ int s_unfinished;
+    __shared__ int s_nlong[2];      // long runs of the round, by its parity
+    __shared__ int64_t s_unfinished;   // round + 1 when a thread is not at its end
     __shared__ unsigned long long s_first;
     __shared__ int64_t s_carry_cnt;
     __shared__ int64_t s_st[L ? 6 * (kLdsT + 1) : 1];
     const int lane = threadIdx.x & 63;
     __shared__ int64_t s_carry_len;
+    __shared__ int32_t s_seg[3][L ? kSegBuf : 1], s_step[L ? kSegBuf : 1];   // (T <= 64 only)
     int64_t *const front = L ? s_st : a.front;
     int64_t *const cidx = L ? s_st + (kLdsT + 1) : a.ccur;
     int64_t *const nfront = L ? s_st + 2 * (kLdsT + 1) : a.nfront;
@@ -286,11 +307,34 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
     while (gsh > 0 && ((int64_t)a.T << gsh) > kWG) gsh--;
     const int G = 1 << gsh;
     const unsigned long long gmask = G == 64 ? ~0ull : ((1ull << G) - 1ull);
-    // a candidate is blocked while a requirement lies at or past the front
-    // of its thread
+    // a candidate is blocked while a requirement lies at or past the front of
+    // its thread; fronts never fall, so a lane that meets the same candidate
+    // again goes on at the requirement that blocked it (a task with 53 parents
+    // is met every round), four loads in flight together
+    int64_t lj = -1, lk = 0, lend = 0;
     auto blocked_list = [&](int64_t j) {
-        for (int64_t k = a.req_ptr[j]; k < a.req_ptr[j + 1]; k++)
-            if (a.req_gpos[k] >= front[a.req_chain[k]]) return true;
+        if (lj != j) {
+            lj = j;
+            lk = a.req_ptr[j];
+            lend = a.req_ptr[j + 1];
+        }
+        while (lk < lend) {
+            int64_t gp[4];
+            int32_t ch[4];
+#pragma unroll
+            for (int z = 0; z < 4; z++) {
+                const int64_t k = lk + z < lend ? lk + z : lend - 1;
+                gp[z] = a.req_gpos[k];
+                ch[z] = a.req_chain[k];
+            }
+            bool b = false;
+#pragma unroll
+            for (int z = 0; z < 4; z++) {
+                b = b || gp[z] >= front[ch[z]];
+                lk += b ? 0 : 1;
+            }
+            if (b) return true;
+        }
         return false;
     };
     // with packed entries: one 16-byte load; only a candidate with parents
@@ -302,19 +346,34 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
         if (nd > 2) return blocked_list(j);
         return false;
     };
-    auto blocked = [&](int64_t j) {
-        if (a.pent) return blocked_ent(a.pent[j], j);
-        return blocked_list(j);
-    };
+    // with one group per thread throughout, the entries of its first probes
+    // stay in registers from round to round
+    const bool ahead = a.pent && ((int64_t)a.T << gsh) <= kWG && (kProbe >> gsh) >= kAhead;
+    CandEnt e0{}, e1{}, e2{};
+    int64_t eat = -1;                             // first candidate they hold
     int64_t nseg = 0, npos = 0;                   // segments and positions so far
     int64_t round = 0;
-    bool stalled = false;
-    for (;;) {
-        if (threadIdx.x == 0) {
-            s_nlong = 0;
-            s_unfinished = 0;
+    // At most 64 threads: segments and steps wait in LDS (a store each round
+    // makes the round wait for it at its next barrier), from seg0 and round0 on
+    int64_t seg0 = 0, round0 = 0;
+    auto flush = [&]() {
+        for (int64_t i = threadIdx.x; i < nseg - seg0; i += kWG) {
+            a.seg_start[seg0 + i] = s_seg[0][i];
+            a.seg_off[seg0 + i] = s_seg[1][i];
+            a.seg_step[seg0 + i] = s_seg[2][i];
         }
+        for (int64_t i = threadIdx.x; i < round - round0; i += kWG) a.step_ptr[round0 + i] = s_step[i];
+        seg0 = nseg;
+        round0 = round;
         __syncthreads();
+    };
+    bool stalled = false;
+    if (threadIdx.x == 0) {
+        s_nlong[0] = s_nlong[1] = 0;
+        s_unfinished = 0;
+    }
+    __syncthreads();
+    for (;;) {
         // A: a group of G lanes per graph thread (G = 64 when few threads,
         // fewer when there are more, so that every thread is probed in one
         // pass) scans up to kProbe candidates of its thread, G at a time
@@ -325,12 +384,15 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
             const int64_t f = act ? front[t] : 0, end = act ? base[t + 1] : 0;
             int64_t ci = act ? cidx[t] : 0;
             const int64_t ce = act ? cbase(t + 1) : 0;
+            const int64_t c0 = ci;
             const bool fin = !act || f >= end;
             if (act && fin && gl == 0) { nfront[t] = f; ncidx[t] = ci; }
-            if (!fin && gl == 0) s_unfinished = 1;   // a flag: every writer stores 1
+            if (!fin && gl == 0) s_unfinished = round + 1;   // (every writer the same)
             bool done = fin;
             int64_t cnew = ce;
             int32_t npos = 0;                 // order position of candidate cnew (packed entries)
+            const bool kept = ahead && eat == c0;
+            CandEnt x0 = e0, x1 = e1, x2 = e2;
             for (int w = 0; w < (kProbe >> gsh); w++) {
                 if (__all(done)) break;                           // wave-uniform
                 const int64_t j = ci + gl;
@@ -338,13 +400,16 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
                 int32_t pj = 0;
                 if (!done && j < ce) {
                     if (a.pent) {
-                        const CandEnt e = a.pent[j];
+                        CandEnt e = x0;
+                        if (!kept || w >= kAhead) e = a.pent[j];
                         pj = e.pos;
                         b = blocked_ent(e, j);
                     } else {
                         b = blocked_list(j);
                     }
                 }
+                x0 = x1;
+                x1 = x2;
                 const unsigned long long bal = __ballot(b);
                 const unsigned long long gb = (bal >> (lane & ~(G - 1))) & gmask;
                 const int fl = gb ? __ffsll((long long)gb) - 1 : 0;
@@ -362,19 +427,28 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
                     }
                 }
             }
+            // the entries of the next round's first probes, while the others
+            // finish and the segments are numbered
+            const int64_t cn = done ? cnew : ci;
+            if (ahead && !fin && cn != eat && cn < ce) {
+                eat = cn;
+                e0 = a.pent[cn + gl < ce ? cn + gl : cn];
+                e1 = a.pent[cn + G + gl < ce ? cn + G + gl : cn];
+                e2 = a.pent[cn + 2 * G + gl < ce ? cn + 2 * G + gl : cn];
+            }
             if (!fin && gl == 0) {
                 if (done) {
                     ncidx[t] = cnew;
                     nfront[t] = cnew < ce ? (a.pent ? (int64_t)npos : a.cand_pos[cnew]) : end;
                 } else {
                     ncidx[t] = ci;
-                    a.long_list[atomicAdd(&s_nlong, 1)] = t;
+                    a.long_list[atomicAdd(&s_nlong[round & 1], 1)] = t;
                 }
             }
         }
         __syncthreads();
         // B: threads with long ready runs, scanned by the whole workgroup
-        const int nlong = s_nlong;
+        const int nlong = s_nlong[round & 1];
         for (int i = 0; i < nlong; i++) {
             const int t = a.long_list[i];
             int64_t ci = ncidx[t];
@@ -383,22 +457,39 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
             for (;;) {
                 if (threadIdx.x == 0) s_first = ~0ull;
                 __syncthreads();
-                const int64_t j = ci + threadIdx.x;
-                if (j < ce && blocked(j)) atomicMin(&s_first, (unsigned long long)j);
+                // (kLong per lane, whose loads are in flight together)
+                if (a.pent) {
+                    CandEnt e[kLong];
+#pragma unroll
+                    for (int z = 0; z < kLong; z++) {
+                        const int64_t j = ci + z * kWG + threadIdx.x;
+                        e[z] = a.pent[j < ce ? j : ci];
+                    }
+#pragma unroll
+                    for (int z = 0; z < kLong; z++) {
+                        const int64_t j = ci + z * kWG + threadIdx.x;
+                        if (j < ce && blocked_ent(e[z], j)) atomicMin(&s_first, (unsigned long long)j);
+                    }
+                } else {
+                    for (int z = 0; z < kLong; z++) {
+                        const int64_t j = ci + z * kWG + threadIdx.x;
+                        if (j < ce && blocked_list(j)) atomicMin(&s_first, (unsigned long long)j);
+                    }
+                }
                 __syncthreads();
                 const unsigned long long fb = s_first;
                 __syncthreads();
                 if (fb != ~0ull) { cnew = (int64_t)fb; break; }
-                if (ci + kWG >= ce) { cnew = ce; break; }
-                ci += kWG;
+                if (ci + kLong * kWG >= ce) { cnew = ce; break; }
+                ci += kLong * kWG;
             }
             if (threadIdx.x == 0) {
                 ncidx[t] = cnew;
                 nfront[t] = cnew < ce ? a.cand_pos[cnew] : base[t + 1];
             }
         }
-        __syncthreads();
-        if (s_unfinished == 0) break;                 // every thread at its end
+        if (nlong) __syncthreads();
+        if (s_unfinished != round + 1) break;                 // every thread at its end
         // C: emit one segment per advanced thread.  Up to 64 threads: one
         // wave ranks them with a ballot; else a workgroup scan of packed
         // count<<32 | length per block of kWG threads.
@@ -407,20 +498,23 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
                 const int t = (int)threadIdx.x;
                 const int len = t < a.T ? (int)(nfront[t] - front[t]) : 0;
                 const unsigned long long bal = __ballot(len > 0);
-                int sum = len;                            // lengths up to and including t
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int y = __shfl_up(sum, o, 64);
-                    if (t >= o) sum += y;
-                }
+                const int sum = wave_scan_add(len);       // lengths up to and including t
                 if (len > 0) {
-                    const int64_t sg = nseg + __popcll(bal & ((1ull << t) - 1ull));
-                    a.seg_start[sg] = front[t];
-                    a.seg_off[sg] = npos + sum - len;
-                    a.seg_step[sg] = (int32_t)round;
+                    const int i = (int)(nseg - seg0) + __popcll(bal & ((1ull << t) - 1ull));
+                    s_seg[0][i] = (int32_t)front[t];
+                    s_seg[1][i] = (int32_t)npos + sum - len;
+                    s_seg[2][i] = (int32_t)round;
                 }
-                if (t == 0) s_carry_cnt = __popcll(bal);
+                if (t == 0) {
+                    s_step[round - round0] = (int32_t)npos;
+                    s_carry_cnt = __popcll(bal);
+                    s_nlong[(round + 1) & 1] = 0;
+                }
                 if (t == 63) s_carry_len = sum;
+                if (t < a.T) {                            // the fronts advance
+                    front[t] = nfront[t];
+                    cidx[t] = ncidx[t];
+                }
             }
             __syncthreads();
         } else {
@@ -452,17 +546,23 @@ __global__ __launch_bounds__(kWG) void k_kahn_rounds(KahnArgs a) {
             stalled = true;
             break;
         }
-        if (threadIdx.x == 0) a.step_ptr[round] = (int32_t)npos;
+        if (a.T > 64 && threadIdx.x == 0) a.step_ptr[round] = (int32_t)npos;
         nseg += adv;
         npos += advlen;
-        // D: advance the fronts
-        for (int t = threadIdx.x; t < a.T; t += kWG) {
-            front[t] = nfront[t];
-            cidx[t] = ncidx[t];
-        }
         round++;
-        __syncthreads();
+        if (a.T <= 64) {
+            if (nseg - seg0 > kSegBuf - 64 || round - round0 == kSegBuf) flush();
+        } else {
+            // D: advance the fronts
+            for (int t = threadIdx.x; t < a.T; t += kWG) {
+                front[t] = nfront[t];
+                cidx[t] = ncidx[t];
+            }
+            if (threadIdx.x == 0) s_nlong[round & 1] = 0;
+            __syncthreads();
+        }
     }
+    if (a.T <= 64) flush();
     if (threadIdx.x == 0) {
         a.step_ptr[round] = (int32_t)npos;
         a.seg_off[nseg] = npos;
