@@ -85,7 +85,7 @@ def bench_breakdown(di, g, vs, stream, reps):
     ms_call = float(np.mean(times))
     achieved = nbytes / (ms_call / 1e3) / 1e9
     pairs = float(n_role) * vs.n_variants
-    return {"kernel": "k_bd_accum", "calls_timed": reps, "avg_call_ms": round(ms_call, 4),
+    return {"kernel": "k_bd_sum", "calls_timed": reps, "avg_call_ms": round(ms_call, 4),
             "tasks_with_role": n_role, "waiting_calls": n_wait,
             "task_variant_pairs_per_s": round(pairs / (ms_call / 1e3), 1),
             "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
@@ -153,7 +153,7 @@ def bench_policy(stream, reps, cpu_workers):
     nbytes = policy_bytes(g.n, V, n_out)
     achieved = nbytes / (ms_call / 1e3) / 1e9
     steps = float(g.n) * V
-    return {"kernel": "k_sim_event", "workload": "%s: %d tasks (%d push/pull slices on 2 "
+    return {"kernel": "k_sim_event_reg", "workload": "%s: %d tasks (%d push/pull slices on 2 "
                                                  "shared channels) x %d variants" %
                                                  (g.name, g.n, int(pp.sum()), V),
             "calls_timed": reps,

@@ -305,7 +305,10 @@ dd_status dd_runtime_breakdown(const dd_graph *g, const dd_variants *var, const 
  * undefined).
  * Synchronous: returns when the simulation is done, with DD_ECYCLE if some
  * variant's active dependencies and thread chains contain a cycle.  Working
- * memory: 12 * n * V bytes of device memory for the call.
+ * memory: at most 12 * n * V bytes of device memory for the call (with at
+ * most 64 threads, 512 classes, durations and gaps below 2^32 and every edge
+ * class on, 40 bytes per task and 4 per dependency, unless more than 256
+ * tasks are ready, or wait for a part of their parents, at once).
  */
 #define DD_POLICY_EARLIEST 0
 #define DD_POLICY_PRIORITY 1
