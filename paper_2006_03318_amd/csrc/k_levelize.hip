@@ -671,7 +671,7 @@ __device__ __forceinline__ bool win_blocked(const WinArgs &a, const CandEnt &e, 
 // the advanced fronts, plus one flag per thread (advanced, unfinished), into
 // buffer (r + 1) & 1 and r & 1; a buffer is rewritten only two rounds later,
 // after the next barrier.  The fronts of every round go to a table from which
-// the segments are cut afterwards (k_win_seg_*).
+// the segments are cut afterwards (k_steps, k_place_win).
 __global__ __launch_bounds__(kWG) void k_kahn_win(WinArgs a) {
     static_assert(kWG / 64 >= kWinT, "a wave per graph thread");
     constexpr int kWinE = kWinBytes / (int)sizeof(CandEnt);
