@@ -334,18 +334,18 @@ dd_status dd_graph_load_ex(int32_t n, int32_t n_threads, const int64_t *in_ptr,
     dd::LoadOut *lo = nullptr, *lo_dev = nullptr;
     dd::LoadIn in;
     const size_t N = (size_t)n;
-    // a field of the graph: kernels copy it from device memory, anything else
-    // is copied here and then checked in place
-    auto field = [&](auto **dst, const auto *src, const auto **from) -> hipError_t {
+    // the call's own copy of an array: kernels make it from device memory
+    // while they check it, anything else is copied here and checked in place
+    auto own = [&](auto **dst, const auto *src, size_t count, const auto **from) -> hipError_t {
         *from = nullptr;
-        hipError_t e = dd::dalloc_n(dst, N, s);
+        hipError_t e = dd::dalloc_n(dst, count, s);
         if (e != hipSuccess || !src) return e;
         if (on_device(src, sizeof(*src))) {
             *from = src;
             return e;
         }
         *from = *dst;
-        return hipMemcpyAsync(*dst, src, N * sizeof(*src), hipMemcpyDefault, s);
+        return hipMemcpyAsync(*dst, src, count * sizeof(*src), hipMemcpyDefault, s);
     };
     // the edge arrays, once their length is known
     auto edges = [&](int64_t e_count) -> hipError_t {
@@ -360,19 +360,13 @@ dd_status dd_graph_load_ex(int32_t n, int32_t n_threads, const int64_t *in_ptr,
         }
         g->n_edges = e_count;
         const size_t E = (size_t)e_count;
-        hipError_t e = hipSuccess;
-        // (shared threads: the graph keeps every dependency edge as given)
-        if (g->shared || !on_device(in_src, sizeof(int32_t))) {
-            e = copy_in(&d_in_src, in_src, E, s);
-            in.in_src = d_in_src;
-        } else {
-            in.in_src = in_src;
-        }
-        if (e == hipSuccess && (g->shared || (edge_cls && !on_device(edge_cls)))) {
-            e = copy_in(&d_ecls, edge_cls, E, s);
-            in.ecls = edge_cls ? d_ecls : nullptr;
-        } else {
-            in.ecls = edge_cls;
+        hipError_t e = own(&d_in_src, E ? in_src : nullptr, E, &in.in_src);
+        in.own_src = d_in_src;
+        if (e == hipSuccess && edge_cls && E) {
+            e = own(&d_ecls, edge_cls, E, &in.ecls);
+            in.own_ecls = d_ecls;
+        } else if (e == hipSuccess && g->shared) {
+            e = copy_in(&d_ecls, (const uint8_t *)nullptr, E, s);   // (the graph keeps every edge's class)
         }
         if (e == hipSuccess && !g->shared) e = dd::dalloc_n(&g->xin_src, E + 1, s);
         if (e == hipSuccess && !g->shared) e = dd::dalloc_n(&g->xin_cls, E + 1, s);
@@ -393,27 +387,22 @@ dd_status dd_graph_load_ex(int32_t n, int32_t n_threads, const int64_t *in_ptr,
         TRY(dd::dalloc_n(&g->order, N + 1, s), "alloc");
         TRY(dd::dalloc_n(&g->xin_ptr, N + 1, s), "alloc");
     }
-    TRY(field(&g->thread_prev, thread_prev, &in.prev), "copy thread_prev");
-    TRY(field(&g->thread_id, thread_id, &in.tid), "copy thread_id");
-    TRY(field(&g->dur, dur_ns, &in.dur), "copy dur");
-    TRY(field(&g->gap, gap_ns, &in.gap), "copy gap");
-    TRY(field(&g->cls, node_cls, &in.cls), "copy node_cls");
+    TRY(own(&g->thread_prev, thread_prev, N, &in.prev), "copy thread_prev");
+    TRY(own(&g->thread_id, thread_id, N, &in.tid), "copy thread_id");
+    TRY(own(&g->dur, dur_ns, N, &in.dur), "copy dur");
+    TRY(own(&g->gap, gap_ns, N, &in.gap), "copy gap");
+    TRY(own(&g->cls, node_cls, N, &in.cls), "copy node_cls");
     {
-        const bool there = on_device(in_ptr, sizeof(int64_t));
-        if (there && !g->shared) {
-            in.in_ptr = in_ptr;
-        } else {
-            TRY(copy_in(&d_in_ptr, in_ptr, N + 1, s), "copy in_ptr");
-            in.in_ptr = d_in_ptr;
-        }
+        TRY(own(&d_in_ptr, in_ptr, N + 1, &in.in_ptr), "copy in_ptr");
+        in.own_ptr = d_in_ptr;
         if (n == 0) {
             dd::ReadBack rb(s, sizeof(int64_t));
             TRY(rb.add(&lo->ends[0], in.in_ptr, sizeof(int64_t)), "read in_ptr");
             TRY(rb.finish(), "sync");
             if (lo->ends[0] != 0) { st = fail(DD_EINVAL, "in_ptr[0] != 0"); goto fail_out; }
             if (edges(0) != hipSuccess) goto fail_out;
+            TRY(hipMemsetAsync(g->shared ? d_in_ptr : g->xin_ptr, 0, sizeof(int64_t), s), "memset");
             if (!g->shared) {
-                TRY(hipMemsetAsync(g->xin_ptr, 0, sizeof(int64_t), s), "memset");
                 TRY(hipMemsetAsync(g->thread_base, 0, sizeof(int64_t) * ((size_t)n_threads + 1), s), "memset");
             }
             TRY(hipStreamSynchronize(s), "sync");

@@ -254,13 +254,18 @@ hipError_t direct_buf(void **host, void **dev);
 #define DD_PASS __attribute__((weak))
 
 // graph load (k_graph.hip)
-struct LoadIn {                   // the caller's arrays where kernels can read them
+struct LoadIn {                   // the caller's arrays where kernels can read them (or the
+                                  // copies themselves, of arrays they cannot)
     const int64_t *in_ptr = nullptr;
     const int32_t *in_src = nullptr;
     const uint8_t *ecls = nullptr;
     const int32_t *prev = nullptr, *tid = nullptr;
     const int64_t *dur = nullptr, *gap = nullptr;
     const uint16_t *cls = nullptr;
+    // the copies that the passes check and use (own_ecls null: all class 0)
+    int64_t *own_ptr = nullptr;
+    int32_t *own_src = nullptr;
+    uint8_t *own_ecls = nullptr;
 };
 struct LoadOut {
     int64_t ends[2];              // in_ptr[0], in_ptr[n]
@@ -270,7 +275,7 @@ struct LoadOut {
 };
 // All passes of a load with n > 0, complete on return.  E: the edge count, or
 // -1 when in_ptr is on the device; edges(E) (E = -1: in_ptr[0] != 0) then
-// checks it and provides in.in_src, in.ecls and the lists of g that it sizes,
+// checks it and provides the edge arrays of in and the lists of g that it sizes,
 // or fails, and nothing more runs.  out: results (host memory, see direct_buf).
 DD_PASS hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, LoadOut *out_dev,
                                hipStream_t s, const std::function<hipError_t(int64_t)> &edges);

@@ -113,9 +113,9 @@ constexpr int kValBlocks = 512;    // grid-stride blocks: one set of atomics per
 
 // what the passes share besides the graph
 struct LoadWork {
-    const int64_t *in_ptr;         // [n+1] dependency in-edges as given
-    const int32_t *in_src;
-    const uint8_t *ecls;           // null: all class 0
+    int64_t *in_ptr;               // [n+1] dependency in-edges: the call's own copies
+    int32_t *in_src;
+    uint8_t *ecls;                 // null: all class 0
     int32_t *succ;                 // [n] successor on the thread + 1 (zeroed)
     int32_t *heads;                // [T] first tasks (zeroed)
     int32_t *last;                 // [T] last task + 1 (zeroed)
@@ -129,6 +129,9 @@ struct LoadWork {
     LoadOut *out;                  // host memory
 };
 
+// An element of the caller's arrays is read once, here: what is checked is
+// what is kept, and the later passes index by the copies alone, whatever the
+// caller writes to the arrays meanwhile.
 template <class T>
 __device__ __forceinline__ T take(const T *src, T *dst, int64_t u) {
     const T x = src[u];
@@ -138,13 +141,10 @@ __device__ __forceinline__ T take(const T *src, T *dst, int64_t u) {
 
 __global__ __launch_bounds__(kBS) void k_load_nodes(
     int32_t n, int32_t T, const int32_t *s_prev, const int32_t *s_tid, const int64_t *s_dur,
-    const int64_t *s_gap, const uint16_t *s_cls, int32_t *prev, int32_t *tid, int64_t *dur,
-    int64_t *gap, uint16_t *cls, LoadWork w, bool one_head) {
+    const int64_t *s_gap, const uint16_t *s_cls, const int64_t *s_ptr, int32_t *prev, int32_t *tid,
+    int64_t *dur, int64_t *gap, uint16_t *cls, LoadWork w, bool one_head) {
     uint32_t e = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        w.out->ends[0] = w.in_ptr[0];
-        w.out->ends[1] = w.in_ptr[n];
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) w.out->ends[1] = take(s_ptr, w.in_ptr, n);
     // sums split at bit 32 so that no partial sum can overflow
     int64_t dhi = 0, dlo = 0, ghi = 0, glo = 0, dm = 0, gm = 0, cm = 0;
     for (int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x; u < n;
@@ -156,8 +156,7 @@ __global__ __launch_bounds__(kBS) void k_load_nodes(
         if (p < -1 || p >= n || p == u) {
             e |= ERR_PREV_RANGE;
         } else if (p >= 0) {
-            if (s_tid[p] != t) e |= ERR_PREV_THREAD;
-            else w.succ[p] = (int32_t)u + 1;   // one claimer wins; the others are found later
+            w.succ[p] = (int32_t)u + 1;        // one claimer wins; the others are found later
         } else if (t_ok && one_head) {
             if (atomicAdd(&w.heads[t], 1) != 0) e |= ERR_HEADS;
         }
@@ -166,7 +165,9 @@ __global__ __launch_bounds__(kBS) void k_load_nodes(
         if (d >= kTimeLimit || g >= kTimeLimit) e |= ERR_BIG_TIME;
         if (d < 0 || d >= kTimeLimit) d = 0;
         if (g < 0 || g >= kTimeLimit) g = 0;
-        if (w.in_ptr[u + 1] < w.in_ptr[u]) e |= ERR_PTR_ORDER;
+        const int64_t k0 = take(s_ptr, w.in_ptr, u);
+        if (u == 0) w.out->ends[0] = k0;
+        if (s_ptr[u + 1] < k0) e |= ERR_PTR_ORDER;
         int64_t c = 0;
         if (s_cls) c = take(s_cls, cls, u);
         else cls[u] = 0;
@@ -263,7 +264,9 @@ constexpr int kChunks = 1024;       // chunks of tasks that the cross-edge lists
 // left only one of them in succ)
 __global__ __launch_bounds__(kRankTile) void k_load_tiles(int32_t n, int32_t T, int64_t E,
                                                           const int32_t *__restrict__ prev,
-                                                          const int32_t *__restrict__ tid, LoadWork w) {
+                                                          const int32_t *__restrict__ tid,
+                                                          const int32_t *s_src, const uint8_t *s_ecls,
+                                                          LoadWork w) {
     __shared__ int32_t sn[2][kRankTile], sd[2][kRankTile], se[2][kRankTile];
     const int64_t b0 = (int64_t)blockIdx.x * kRankTile;
     const int i = threadIdx.x;
@@ -275,14 +278,16 @@ __global__ __launch_bounds__(kRankTile) void k_load_tiles(int32_t n, int32_t T, 
     if (ok) {
         if (p >= 0 && w.succ[p] != (int32_t)u + 1) er |= ERR_SUCC;
         const int32_t t = tid[u];
+        if (p >= 0 && tid[p] != t) er |= ERR_PREV_THREAD;
         if (w.succ[u] == 0 && t >= 0 && t < T) w.last[t] = (int32_t)u + 1;
         const int64_t k0 = w.in_ptr[u] > 0 ? w.in_ptr[u] : 0;
         const int64_t k1 = w.in_ptr[u + 1] < E ? w.in_ptr[u + 1] : E;
+        if (w.in_ptr[u + 1] < w.in_ptr[u]) er |= ERR_PTR_ORDER;
         for (int64_t k = k0; k < k1; k++) {
-            const int32_t s = w.in_src[k];
+            const int32_t s = take(s_src, w.in_src, k);
             if (s < 0 || s >= n) er |= ERR_SRC_RANGE;
             else if (s == u) er |= ERR_SELF_LOOP;
-            if (w.ecls && w.ecls[k] >= 64) er |= ERR_EDGE_CLS;
+            if (w.ecls && take(s_ecls, w.ecls, k) >= 64) er |= ERR_EDGE_CLS;
         }
     }
     const bool in = p >= b0 && p < b0 + kRankTile && p < n;
@@ -544,7 +549,7 @@ hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, L
     char *m = nullptr;
     hipError_t e = dalloc(reinterpret_cast<void **>(&m), off, s);
     if (e != hipSuccess) return e;
-    LoadWork w{in.in_ptr, in.in_src, in.ecls, (int32_t *)(m + o_succ), (int32_t *)(m + o_heads),
+    LoadWork w{in.own_ptr, nullptr, nullptr, (int32_t *)(m + o_succ), (int32_t *)(m + o_heads),
                (int32_t *)(m + o_last), (int32_t *)(m + o_xslot), (uint32_t *)(m + o_err),
                (int32_t *)(m + o_xcount), (LoadStats *)(m + o_st), (int32_t *)(m + o_dloc),
                (int32_t *)(m + o_ext), (int32_t *)(m + o_xlist), (int32_t *)(m + o_xrank),
@@ -557,18 +562,18 @@ hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, L
 #define LD(x) do { if (e == hipSuccess) e = (x); } while (0)
     LD(hipMemsetAsync(m, 0, zero, s));
     if (e == hipSuccess)
-        k_load_nodes<<<nv, kBS, 0, s>>>(n, T, in.prev, in.tid, in.dur, in.gap, in.cls, g->thread_prev,
-                                        g->thread_id, g->dur, g->gap, g->cls, w, !g->shared);
+        k_load_nodes<<<nv, kBS, 0, s>>>(n, T, in.prev, in.tid, in.dur, in.gap, in.cls, in.in_ptr,
+                                        g->thread_prev, g->thread_id, g->dur, g->gap, g->cls, w, !g->shared);
     LD(hipGetLastError());
     if (E < 0) {                               // in_ptr is on the device: its ends come back first
         LD(hipStreamSynchronize(s));
         E = out->ends[0] != 0 ? -1 : out->ends[1];
     }
     if (e == hipSuccess && edges(E) == hipSuccess) {
-        w.in_src = in.in_src;
-        w.ecls = in.ecls;
-        k_load_tiles<<<(unsigned)((n + kRankTile - 1) / kRankTile), kRankTile, 0, s>>>(n, T, E, g->thread_prev,
-                                                                                     g->thread_id, w);
+        w.in_src = in.own_src;
+        w.ecls = in.own_ecls;
+        k_load_tiles<<<(unsigned)((n + kRankTile - 1) / kRankTile), kRankTile, 0, s>>>(
+            n, T, E, g->thread_prev, g->thread_id, in.in_src, in.ecls, w);
         k_load_exits<<<1, 1024, 0, s>>>(T, g->shared ? nullptr : g->thread_base, w);
         if (!g->shared) {
             k_cross_count<false><<<nc, kBS, 0, s>>>(n, chunk, g->thread_id, g->thread_base, g->rank, g->order, w);

@@ -129,3 +129,45 @@ def test_errors_of_every_pass(where):
     rc, h = _load(g, where)                   # and the next load is not affected
     assert rc == B.DD_OK
     B.dd_graph_free(h)
+
+
+def test_arrays_written_during_the_load():
+    """A caller that writes its device arrays while a load reads them gets a
+    graph or an error, never an index outside of the copies: whatever the
+    passes check is what they keep.  (The arrays' lengths, in_ptr[n], hold.)"""
+    import ctypes
+
+    import torch
+    require_gpu()
+    rng = np.random.default_rng(730_000)
+    g = _graph(rng, 40_000, 6)
+    good = dict(in_ptr=g.in_ptr, in_src=g.in_src, edge_cls=g.edge_cls, thread_prev=g.thread_prev,
+                thread_id=g.thread_id, dur=g.dur, gap=g.gap, node_cls=g.node_cls)
+    bad = {k: v.copy() for k, v in good.items()}
+    bad["in_ptr"][1:-1] = rng.integers(-2**40, 2**40, g.n - 1)
+    for k in ("in_src", "thread_prev", "thread_id"):
+        bad[k][:] = rng.integers(-2**31, 2**31, bad[k].size)
+    bad["edge_cls"][:] = 255
+    t = {k: torch.from_numpy(np.ascontiguousarray(v)).cuda() for k, v in good.items()}
+    tg = {k: v.clone() for k, v in t.items()}
+    tb = {k: torch.from_numpy(np.ascontiguousarray(v)).cuda() for k, v in bad.items()}
+    torch.cuda.synchronize()
+    writer, loader = torch.cuda.Stream(), torch.cuda.Stream()
+    codes = set()
+    for k in ("in_src", "in_ptr", "thread_id", "thread_prev", "edge_cls"):
+        say("load while", k, "is written")
+        for _ in range(10):
+            with torch.cuda.stream(writer):
+                for _ in range(20):
+                    t[k].copy_(tb[k])
+                    t[k].copy_(tg[k])
+            out = ctypes.c_void_p()
+            rc = B.lib().dd_graph_load(g.n, g.n_threads, *(x.data_ptr() for x in t.values()),
+                                       loader.cuda_stream, ctypes.byref(out))
+            codes.add(rc)
+            assert rc in (B.DD_OK, B.DD_EINVAL, B.DD_ECYCLE, B.DD_ECHAIN), B.dd_last_error()
+            B.dd_graph_free(out)
+        torch.cuda.synchronize()
+    rc, h = _load(g, "device")
+    assert rc == B.DD_OK, B.dd_last_error()
+    B.dd_graph_free(h)
