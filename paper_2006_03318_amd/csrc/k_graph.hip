@@ -425,7 +425,12 @@ __global__ __launch_bounds__(kBS) void k_cross_count(int32_t n, int64_t chunk,
                                                      const int32_t *__restrict__ tid,
                                                      const int64_t *__restrict__ base, int32_t *rank,
                                                      int32_t *__restrict__ order, LoadWork w) {
-    if (w.err[0] | (RANKED ? 0u : w.err[1])) return;
+    // (read once: workgroups that run already add errors of their own to the
+    // word, and the barrier below is for all waves of this one or none)
+    __shared__ uint32_t s_failed;
+    if (threadIdx.x == 0) s_failed = load_coherent(&w.err[0]) | (RANKED ? 0u : load_coherent(&w.err[1]));
+    __syncthreads();
+    if (s_failed) return;
     uint32_t e = 0;
     uint64_t mask = 0;
     int64_t c = 0;

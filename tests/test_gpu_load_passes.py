@@ -171,3 +171,20 @@ def test_arrays_written_during_the_load():
     rc, h = _load(g, "device")
     assert rc == B.DD_OK, B.dd_last_error()
     B.dd_graph_free(h)
+
+
+def test_backward_dependencies_in_every_workgroup():
+    """Each workgroup of the pass that counts the cross-thread edges finds
+    errors while others start: the load ends with the error, every time."""
+    require_gpu()
+    rng = np.random.default_rng(740_000)
+    g = _graph(rng, 300_000, 3)
+    tail = np.full(3, -1)
+    tail[g.thread_id] = np.arange(g.n)                    # the last task of each thread
+    deps = np.diff(g.in_ptr) > 0
+    deps[tail] = False
+    src = g.in_src.copy()
+    src[g.in_ptr[:-1][deps]] = tail[g.thread_id[deps]]
+    for _ in range(5):
+        rc, h = _load(g, "device", in_src=src)
+        assert rc == B.DD_ECYCLE and not h.value, B.dd_last_error()
