@@ -283,7 +283,10 @@ __global__ __launch_bounds__(kRankTile) void k_load_tiles(int32_t n, int32_t T, 
         const int64_t k0 = w.in_ptr[u] > 0 ? w.in_ptr[u] : 0;
         const int64_t k1 = w.in_ptr[u + 1] < E ? w.in_ptr[u + 1] : E;
         if (w.in_ptr[u + 1] < w.in_ptr[u]) er |= ERR_PTR_ORDER;
-        for (int64_t k = k0; k < k1; k++) {
+        // (offsets that go back and forth give every task up to all the edges:
+        // refused already, and hours of work at the limits of sizes)
+        const bool listed = !(load_coherent(w.err) & ERR_PTR_ORDER);
+        for (int64_t k = k0; k < k1 && listed; k++) {
             const int32_t s = take(s_src, w.in_src, k);
             if (s < 0 || s >= n) er |= ERR_SRC_RANGE;
             else if (s == u) er |= ERR_SELF_LOOP;

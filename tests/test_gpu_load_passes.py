@@ -188,3 +188,17 @@ def test_backward_dependencies_in_every_workgroup():
     for _ in range(5):
         rc, h = _load(g, "device", in_src=src)
         assert rc == B.DD_ECYCLE and not h.value, B.dd_last_error()
+
+
+def test_offsets_that_go_back_and_forth():
+    """in_ptr that names all edges for every other task: refused by the pass
+    that reads it, without going through tasks x edges."""
+    require_gpu()
+    rng = np.random.default_rng(750_000)
+    g = _graph(rng, 200_000, 4)
+    ptr = np.zeros(g.n + 1, np.int64)
+    ptr[1::2] = g.n_edges
+    ptr[-1] = g.n_edges
+    for where in ("host", "device"):
+        rc, h = _load(g, where, in_ptr=ptr)
+        assert rc == B.DD_EINVAL and not h.value, B.dd_last_error()
