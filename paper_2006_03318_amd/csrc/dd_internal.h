@@ -357,8 +357,11 @@ inline int64_t solo_batch_max(int64_t n) {
 hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants *var,
                        int64_t *finish, int64_t *start, int64_t *makespan, hipStream_t s);
 
-// removal bits [n][W] as one bit string per variant, [V][stride] words
-// (stride even, at least n / 32), in the order of `order`
+// removal bits [n][W] as one bit string per variant, [V][stride] words, in
+// the order of `order`.  rm_stride: whole pairs of words that hold bits 0 to n
+// (a lane of k_solo.hip without a position looks at bit n, where the next
+// position would be)
+inline int64_t rm_stride(int64_t n) { return (n / 64 + 1) * 2; }
 hipError_t launch_rm_bits(int64_t n, int32_t V, int32_t W, int64_t stride, const int32_t *order,
                           const uint32_t *rm, uint32_t *rmb, hipStream_t s);
 

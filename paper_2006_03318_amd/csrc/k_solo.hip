@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kSoNT, 4) void k_sim_solo(const int4 *__restrict__ 
     // stage 1: the record of the lane's position (and a step offset, if narrow)
     struct Raw { uint4 u, w; uint32_t rm; int32_t ph; };
     auto load_raw = [&](const Bat &B, Raw &r) {
-        const uint32_t q = (uint32_t)(B.p0 + (tid < B.p1 - B.p0 ? tid : 0));   // (the list is padded)
+        const uint32_t q = (uint32_t)(B.p0 + (tid < B.p1 - B.p0 ? tid : 0));   // (up to n: so_rec and rmb hold it)
         const uint4 *s = reinterpret_cast<const uint4 *>(a.rec + q);
         r.u = s[0];
         r.w = s[1];
@@ -475,7 +475,7 @@ hipError_t launch_solo(const dd_graph *g, const dd_sched *sch, const dd_variants
     // scratch of the call: removal bits by position, the rings, the target
     // of idle lanes' stores
     const int64_t n = g->n;
-    const int64_t stride = (n + 63) / 64 * 2;
+    const int64_t stride = rm_stride(n);
     int32_t ring = kSoloPos;
     while (ring < kSoloRing && ring < n) ring <<= 1;
     uint32_t *rmb = nullptr;

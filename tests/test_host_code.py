@@ -1,0 +1,25 @@
+"""Host code of the library on the CPU, compiled from its own sources."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2006_03318_amd", "csrc")
+CLANGXX = "/opt/rocm/lib/llvm/bin/clang++"
+INC = ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
+def _run(exe):
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "ALL OK" in r.stdout, (r.stdout[-2000:], r.stderr[-4000:])
+
+
+def test_sizes_of_launches_and_arrays(tmp_path):
+    """Room for every word of the removal strings that a lane reads."""
+    if not os.path.exists(CLANGXX):
+        pytest.skip("%s not present" % CLANGXX)
+    exe = str(tmp_path / "layout")
+    subprocess.check_call([CLANGXX, "-O1", "-std=c++17", *INC, os.path.join(ROOT, "tests", "host", "layout.cpp"),
+                           "-o", exe])
+    _run(exe)
