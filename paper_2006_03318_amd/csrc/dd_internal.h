@@ -242,6 +242,13 @@ inline int grid_for(int64_t n, int bs) {
     return (int)g;
 }
 
+// Passes over n > 0 tasks cut them into at most kChunks chunks, of whole
+// workgroups of `bs` threads (in 64 bits: n + kChunks passes 2^31).
+constexpr int kChunks = 1024;
+inline int64_t chunk_len(int64_t n, int bs) {
+    return ((n + kChunks - 1) / kChunks + bs - 1) / bs * bs;
+}
+
 // Results that kernels write straight into host memory (a pinned buffer per
 // host thread, kept until the process ends; read after the stream has been
 // waited for): no copy, and no launch for one.  *dev receives the address

@@ -257,7 +257,6 @@ __global__ __launch_bounds__(kBS) void k_rank_check(int32_t n, const int32_t *__
 // does.
 constexpr int kRankTile = 1024;
 constexpr int kRankXMax = 8192;     // tile exits ranked in LDS at most
-constexpr int kChunks = 1024;       // chunks of tasks that the cross-edge lists are cut into
 
 // (every index is clamped to its array: the errors of k_load_nodes have not
 // been read; also reports a task named as previous task by two tasks, which
@@ -564,7 +563,7 @@ hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, L
                (int64_t *)(m + o_csum), out_dev};
     *out = LoadOut{};
     int32_t *nxt = nullptr, *nxt2 = nullptr, *rank2 = nullptr;
-    const int64_t chunk = ((n + kChunks - 1) / kChunks + kBS - 1) / kBS * kBS;
+    const int64_t chunk = chunk_len(n, kBS);
     const unsigned nc = (unsigned)((n + chunk - 1) / chunk);
     const unsigned nv = (unsigned)(grid_for(n, kBS) < kValBlocks ? grid_for(n, kBS) : kValBlocks);
 #define LD(x) do { if (e == hipSuccess) e = (x); } while (0)
@@ -580,7 +579,7 @@ hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, L
     if (e == hipSuccess && edges(E) == hipSuccess) {
         w.in_src = in.own_src;
         w.ecls = in.own_ecls;
-        k_load_tiles<<<(unsigned)((n + kRankTile - 1) / kRankTile), kRankTile, 0, s>>>(
+        k_load_tiles<<<grid_for(n, kRankTile), kRankTile, 0, s>>>(
             n, T, E, g->thread_prev, g->thread_id, in.in_src, in.ecls, w);
         k_load_exits<<<1, 1024, 0, s>>>(T, g->shared ? nullptr : g->thread_base, w);
         if (!g->shared) {

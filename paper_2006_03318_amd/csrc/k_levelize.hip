@@ -49,8 +49,6 @@ struct Req {
 
 __device__ __forceinline__ bool on(uint64_t mask, uint8_t c) { return (mask >> c) & 1ull; }
 
-constexpr int kChunks = 1024;      // chunks of order positions in the candidate passes
-
 // small results of the passes (device memory, cleared by the first of them)
 struct LevWork {
     int64_t result[2];             // steps, segments
@@ -1148,7 +1146,7 @@ dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sch
     unsigned long long *lmax = nullptr;
     LevelizeOut *out = nullptr, *out_dev = nullptr;
     const int gN = grid_for(n, kBS);
-    const int64_t chunk = ((n + kChunks - 1) / kChunks + kBS - 1) / kBS * kBS;
+    const int64_t chunk = chunk_len(n, kBS);
     Req rq{g->thread_base, g->order, g->rank, g->thread_id, g->xin_ptr, g->xin_src, g->xin_cls};
     size_t off = 0;
     auto put = [&](size_t bytes) {

@@ -16,7 +16,8 @@ def _run(exe):
 
 
 def test_sizes_of_launches_and_arrays(tmp_path):
-    """Room for every word of the removal strings that a lane reads."""
+    """Chunks and tiles at 2^31 - 1 tasks (a sum in 32 bits wraps there), and
+    room for every word of the removal strings that a lane reads."""
     if not os.path.exists(CLANGXX):
         pytest.skip("%s not present" % CLANGXX)
     exe = str(tmp_path / "layout")
