@@ -10,6 +10,7 @@ import pytest
 from oracle import oracle as O
 from paper_2006_03318_amd import binding as B
 from paper_2006_03318_amd import workloads as W
+from tests import helpers as H
 from tests.gpu_common import assert_equal_arrays, gpu_run, require_gpu, say
 
 pytestmark = pytest.mark.gpu
@@ -202,3 +203,27 @@ def test_offsets_that_go_back_and_forth():
     for where in ("host", "device"):
         rc, h = _load(g, where, in_ptr=ptr)
         assert rc == B.DD_EINVAL and not h.value, B.dd_last_error()
+
+
+@pytest.mark.parametrize("fan", [7, 8, 9, 15, 16, 17, 1000])
+def test_many_dependencies_of_one_task(fan):
+    """Lists around the eight edges that are loaded together, from its own
+    thread and from others, of both classes; a bad entry anywhere is found."""
+    require_gpu()
+    rng = np.random.default_rng(760_000 + fan)
+    m = max(40, fan)
+    thread = rng.integers(0, 4, m).tolist() + [0, 1, 2]
+    edges = [(int(s), d) for d in (m, m + 1, m + 2) for s in rng.permutation(m)[:fan]]
+    g = H.graph(4, thread, edges, rng.integers(0, 900, m + 3), rng.integers(0, 90, m + 3),
+                edge_cls=rng.integers(0, 2, len(edges)), n_edge_cls=2)
+    vs = W.random_variants(rng, g, 5, p_remove=0.2)
+    S, F, M = gpu_run(g, vs)
+    oS, oF, oM, _ = O.run(g, vs)
+    assert_equal_arrays("makespan", M, oM)
+    assert_equal_arrays("finish", F, oF)
+    for where in ("host", "device"):
+        for k in range(fan, 2 * fan, max(1, fan // 20)):
+            src, cls = g.in_src.copy(), g.edge_cls.copy()
+            src[k], cls[k] = -1, 64
+            assert _load(g, where, in_src=src)[0] == B.DD_EINVAL
+            assert _load(g, where, edge_cls=cls)[0] == B.DD_EINVAL
