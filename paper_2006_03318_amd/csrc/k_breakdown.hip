@@ -195,17 +195,23 @@ __global__ __launch_bounds__(kBT) void k_bd_sum(BdArgs a) {
     sSum[wv][lane] = S::whole(ka);
     sSum[wv][lane + 64] = S::whole(kb);
     __syncthreads();
-    if (tid < kBV) {
-        const int64_t v = (int64_t)bx * kBV + tid;
+    {
+        // thread tid: variant tid % kBV, and every kBT / kBV-th waiting call
+        // (start minus the moment the thread reached the call; 2,048 of them
+        // in 256 variants: 135 us before this kernel, 152 with all calls on
+        // the first kBV threads, 99 now)
+        static_assert(kBT % kBV == 0, "the threads of a variant");
+        const int64_t v = (int64_t)bx * kBV + tid % kBV;
         int64_t k = 0, b = 0;
+        if (tid < kBV)
 #pragma unroll
-        for (int w = 0; w < kBW; w++) k += sSum[w][tid];
-        // waiting calls: start minus the moment the thread reached the call
+            for (int w = 0; w < kBW; w++) k += sSum[w][tid];
         const int nw = sNw;
         if (v < V) {
             const int64_t vw = v >> 5;
             const uint32_t bit = (uint32_t)(v & 31);
-            for (int i = 0; i < nw; i++) {
+#pragma unroll 2
+            for (int i = tid / kBV; i < nw; i += kBT / kBV) {
                 const int64_t u = sWait[i];
                 const bool rmu = (a.rm[u * W + vw] >> bit) & 1u;
                 S s;

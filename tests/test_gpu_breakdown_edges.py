@@ -34,3 +34,16 @@ def test_breakdown_edges(n, V, classes, big):
         role[:: 1000] = 2
     say("breakdown edges n=%d V=%d classes=%d big=%d" % (n, V, classes, big))
     assert_equal_arrays("breakdown", gpu_breakdown(g, vs, role), O.breakdown(g, vs, role))
+
+
+@pytest.mark.parametrize("n,V", [(1, 129), (2, 1), (255, 128), (513, 130), (2048, 257)])
+def test_every_task_waits(n, V):
+    """Waiting calls alone, an odd number and an even one in a chunk: the two
+    threads of a variant take them in turn."""
+    require_gpu()
+    rng = np.random.default_rng(192_000 + n + V)
+    g = W.random_graph_sparse(rng, n, 3, mean_in=0.4, window=100, n_node_cls=4, run_len=7)
+    vs = W.random_variants(rng, g, V, p_remove=0.3)
+    role = np.full(n, 2, np.uint8)
+    say("breakdown of waiting calls n=%d V=%d" % (n, V))
+    assert_equal_arrays("breakdown", gpu_breakdown(g, vs, role), O.breakdown(g, vs, role))
