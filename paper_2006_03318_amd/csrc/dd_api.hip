@@ -407,7 +407,7 @@ dd_status dd_graph_load_ex(int32_t n, int32_t n_threads, const int64_t *in_ptr,
             }
             TRY(hipStreamSynchronize(s), "sync");
         } else {
-            TRY(dd::load_device(g, in, -1, lo, lo_dev, s, edges), "load");
+            TRY(dd::load_device(g, in, lo, lo_dev, s, edges), "load");
             if (st != DD_OK) goto fail_out;
         }
     }
@@ -646,9 +646,7 @@ dd_status dd_runtime_breakdown(const dd_graph *g, const dd_variants *var, const 
     dd_status st = DD_OK;
     uint8_t *d_role = nullptr;
     if (!on_device(role)) TRY(copy_in(&d_role, role, (size_t)g->n, s), "copy role");
-    TRY(dd::launch_breakdown(g, var, d_role ? d_role : role, d_finish, d_makespan, nullptr, nullptr,
-                             d_out, s),
-        "breakdown");
+    TRY(dd::launch_breakdown(g, var, d_role ? d_role : role, d_finish, d_makespan, d_out, s), "breakdown");
     TRY(dd::note_use(g->uses, g->stream, s), "record stream use");
     TRY(dd::note_use(var->uses, var->stream, s), "record stream use");
 fail_out:

@@ -280,12 +280,12 @@ struct LoadOut {
     uint32_t err[2];
     LoadStats st;
 };
-// All passes of a load with n > 0, complete on return.  E: the edge count, or
-// -1 when in_ptr is on the device; edges(E) (E = -1: in_ptr[0] != 0) then
-// checks it and provides the edge arrays of in and the lists of g that it sizes,
-// or fails, and nothing more runs.  out: results (host memory, see direct_buf).
-DD_PASS hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, LoadOut *out_dev,
-                               hipStream_t s, const std::function<hipError_t(int64_t)> &edges);
+// All passes of a load with n > 0, complete on return.  edges(E), called with
+// the edge count once in_ptr's ends are read (-1: in_ptr[0] != 0), checks it
+// and provides the edge arrays of in and the lists of g that it sizes, or
+// fails, and nothing more runs.  out: results (host memory, see direct_buf).
+DD_PASS hipError_t load_device(dd_graph *g, const LoadIn &in, LoadOut *out, LoadOut *out_dev, hipStream_t s,
+                               const std::function<hipError_t(int64_t)> &edges);
 
 // levelization (k_levelize.hip)
 struct LevelizeOut {
@@ -392,11 +392,9 @@ inline bool solo_chosen(const dd_sched *sch, const dd_variants *var) {
     return var->V <= 768 || (int64_t)sch->n <= 32 * sch->n_steps;
 }
 
-// runtime breakdown (k_breakdown.hip): out [V][4]; scratch and order are not
-// used (nullptr)
+// runtime breakdown (k_breakdown.hip): out [V][4]
 hipError_t launch_breakdown(const dd_graph *g, const dd_variants *var, const uint8_t *role_dev,
-                            const int64_t *finish, const int64_t *makespan, int64_t *scratch,
-                            int32_t *order, int64_t *out, hipStream_t s);
+                            const int64_t *finish, const int64_t *makespan, int64_t *out, hipStream_t s);
 
 // simulation under a schedule rule (k_event.hip)
 // out-edge lists of g (dependencies in xin_*, thread order in thread_prev)
@@ -414,7 +412,5 @@ hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_va
 constexpr int kEventQueue = 1024;      // ready tasks one variant may hold
 constexpr int kEventIdBits = 22;       // tasks: n < 2^22
 constexpr int kEventMaxThreads = 4096;
-
-
 
 }  // namespace dd

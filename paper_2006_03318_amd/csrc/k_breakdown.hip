@@ -237,10 +237,7 @@ __global__ __launch_bounds__(kBT) void k_bd_sum(BdArgs a) {
 }  // namespace
 
 hipError_t launch_breakdown(const dd_graph *g, const dd_variants *var, const uint8_t *role_dev,
-                            const int64_t *finish, const int64_t *makespan, int64_t *scratch,
-                            int32_t *order, int64_t *out, hipStream_t s) {
-    (void)scratch;
-    (void)order;
+                            const int64_t *finish, const int64_t *makespan, int64_t *out, hipStream_t s) {
     k_bd_init<<<grid_for(var->V, kBT), kBT, 0, s>>>(var->V, makespan, out);
     if (g->n > 0) {
         // chunks as long as leaves about four workgroups per compute unit,

@@ -102,10 +102,10 @@ hipError_t scan_exclusive(const int64_t *in, int64_t *out, int64_t n, hipStream_
 //   k_cross_count  ranks and order of all tasks, cross-thread edges per chunk;
 //   k_cross_fill   the cross-thread in-edge lists.
 // Small graphs are bound by the launches and host waits (a load was some 27
-// launches, 10 copies, 6 fills and 5 waits, 0.2 ms for 1,612 tasks), so every
-// pass does all that its inputs allow, nothing comes back to the host before
-// the end but the edge count, and results are written straight into the
-// pinned read-back buffer.  Large graphs: each pass is bound by HBM.
+// launches, 10 copies, 6 fills and 5 waits, 0.2 ms for 1,612 tasks; five
+// launches, a fill and two waits now), so every pass does all that its inputs
+// allow, nothing comes back to the host before the end but the edge count,
+// and results are written straight into the pinned read-back buffer.  Large graphs: each pass is bound by HBM.
 namespace {
 constexpr int kBS = 256;
 
@@ -566,8 +566,8 @@ void rank_chains(const dd_graph *g, int32_t *nxt, int32_t *nxt2, int32_t *rank2,
 }
 }  // namespace
 
-hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, LoadOut *out_dev,
-                       hipStream_t s, const std::function<hipError_t(int64_t)> &edges) {
+hipError_t load_device(dd_graph *g, const LoadIn &in, LoadOut *out, LoadOut *out_dev, hipStream_t s,
+                       const std::function<hipError_t(int64_t)> &edges) {
     const int32_t n = g->n, T = g->n_threads;
     // one block of working memory, the part that starts at zero first
     size_t off = 0;
@@ -601,10 +601,9 @@ hipError_t load_device(dd_graph *g, const LoadIn &in, int64_t E, LoadOut *out, L
         k_load_nodes<<<nv, kBS, 0, s>>>(n, T, in.prev, in.tid, in.dur, in.gap, in.cls, in.in_ptr,
                                         g->thread_prev, g->thread_id, g->dur, g->gap, g->cls, w, !g->shared);
     LD(hipGetLastError());
-    if (E < 0) {                               // in_ptr is on the device: its ends come back first
-        LD(hipStreamSynchronize(s));
-        E = out->ends[0] != 0 ? -1 : out->ends[1];
-    }
+    // the edge count sizes the edge arrays: in_ptr's ends come back first
+    LD(hipStreamSynchronize(s));
+    const int64_t E = out->ends[0] != 0 ? -1 : out->ends[1];
     if (e == hipSuccess && edges(E) == hipSuccess) {
         w.in_src = in.own_src;
         w.ecls = in.own_ecls;

@@ -14,26 +14,11 @@
 namespace dd {
 #define STUB return hipErrorNoDevice
 hipError_t scan_exclusive(const int64_t *, int64_t *, int64_t, hipStream_t) { STUB; }
-hipError_t launch_validate_nodes(const dd_graph *, const int64_t *, int32_t *, int32_t *,
-                                 uint32_t *, LoadStats *, hipStream_t) { STUB; }
-hipError_t launch_validate_edges(const dd_graph *, const int64_t *, const int32_t *,
-                                 const uint8_t *, const int32_t *, uint32_t *, hipStream_t) { STUB; }
-hipError_t launch_rank_tiles(const dd_graph *, int32_t *, int32_t *, int32_t *, int64_t *,
-                             uint32_t *, hipStream_t) { STUB; }
-hipError_t launch_rank_chains(const dd_graph *, const int32_t *, int32_t *, int32_t *, int32_t *,
-                              uint32_t *, hipStream_t) { STUB; }
-hipError_t launch_build_order(const dd_graph *, const int32_t *, int64_t *, hipStream_t) { STUB; }
-hipError_t launch_cross_edges(dd_graph *, const int64_t *, const int32_t *, const uint8_t *,
-                              int64_t *, uint32_t *, LoadStats *, hipStream_t) { STUB; }
-hipError_t launch_cross_fill(dd_graph *, const int64_t *, const int32_t *, const uint8_t *,
-                             hipStream_t) { STUB; }
 dd_status levelize_device(const dd_graph *, uint64_t, int32_t, dd_sched *, hipStream_t, char *msg,
                           size_t len) {
     snprintf(msg, len, "no device");
     return DD_EHIP;
 }
-hipError_t launch_build_scale_table(const dd_ratio *, int32_t, int32_t, ScaleEntry *, uint32_t *,
-                                    hipStream_t) { STUB; }
 hipError_t launch_simulate(const dd_graph *, const dd_sched *, const dd_variants *, int64_t *,
                            int64_t *, int64_t *, int, hipStream_t) { STUB; }
 hipError_t simulate_noalloc(const dd_graph *, const dd_sched *, const dd_variants *, int64_t *,
@@ -47,7 +32,7 @@ hipError_t launch_split(const dd_graph *, const dd_sched *, const dd_variants *,
                         int64_t *, int, hipStream_t) { STUB; }
 void split_set_polls(int32_t) {}
 hipError_t launch_breakdown(const dd_graph *, const dd_variants *, const uint8_t *, const int64_t *,
-                            const int64_t *, int64_t *, int32_t *, int64_t *, hipStream_t) { STUB; }
+                            const int64_t *, int64_t *, hipStream_t) { STUB; }
 hipError_t build_event_lists(const dd_graph *, EventLists *, hipStream_t) { STUB; }
 void free_event_lists(EventLists *ev, hipStream_t) { *ev = EventLists(); }
 hipError_t launch_sim_event(const dd_graph *, const EventLists &, const dd_variants *, int32_t,

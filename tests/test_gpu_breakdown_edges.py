@@ -1,5 +1,5 @@
 """Runtime breakdown at the edges of its workgroups, bit-exact against the
-oracle: chunks of 256 to 2,048 tasks, blocks of 128 variants, removal rows
+oracle: chunks of 256 and 512 tasks, blocks of 128 variants, removal rows
 that end inside a block, more classes than the sort has buckets, and the
 integer form of the scaled durations."""
 import numpy as np
@@ -30,7 +30,7 @@ def test_breakdown_edges(n, V, classes, big):
                           np.ascontiguousarray(vs.edge_on[at]), [(0, V, vs.batches[0][2])])
     role = rng.integers(0, 4, size=g.n).astype(np.uint8)
     if n > 200_000:
-        role[role == 2] = 1          # (thousands of waiting calls are not what this path is for)
+        role[role == 2] = 1          # (a handful of waiting calls, as in a trace)
         role[:: 1000] = 2
     say("breakdown edges n=%d V=%d classes=%d big=%d" % (n, V, classes, big))
     assert_equal_arrays("breakdown", gpu_breakdown(g, vs, role), O.breakdown(g, vs, role))

@@ -106,7 +106,6 @@ def test_errors_of_every_pass(where):
         a = getattr(g, name).copy()
         a[at] = value
         return {name: a}
-    back = int(np.nonzero(g.thread_id == g.thread_id[int(g.in_src[0])])[0][-1])
     cases = [
         (changed("thread_id", 5, 4), B.DD_EINVAL), (changed("dur", 7, -1), B.DD_EINVAL),
         (changed("gap", 7, 1 << 62), B.DD_ERANGE), (changed("in_src", 3, g.n), B.DD_EINVAL),
@@ -122,7 +121,6 @@ def test_errors_of_every_pass(where):
     cases.append((changed("in_src", k, dst), B.DD_ECYCLE))
     if later != dst:
         cases.append((changed("in_src", k, later), B.DD_ECYCLE))
-    del back
     for bad, want in cases:
         say("load error", where, list(bad))
         rc, h = _load(g, where, **bad)
