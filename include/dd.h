@@ -307,8 +307,9 @@ dd_status dd_runtime_breakdown(const dd_graph *g, const dd_variants *var, const 
  * variant's active dependencies and thread chains contain a cycle.  Working
  * memory: at most 12 * n * V bytes of device memory for the call (with at
  * most 64 threads, 512 classes, durations and gaps below 2^32 and every edge
- * class on, 40 bytes per task and 4 per dependency, unless more than 256
- * tasks are ready, or wait for a part of their parents, at once).
+ * class on, 40 bytes per task, 4 per dependency and at most 6.3 KiB per
+ * variant, with the 12 * n * V bytes only if more than 256 tasks are ready, or
+ * wait for a part of their parents, at once, or times lie 2^31 ns apart).
  */
 #define DD_POLICY_EARLIEST 0
 #define DD_POLICY_PRIORITY 1

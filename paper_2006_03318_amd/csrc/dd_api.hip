@@ -677,7 +677,7 @@ dd_status dd_simulate_policy(const dd_graph *g, const dd_variants *var, int32_t 
     uint8_t *d_pp = nullptr;
     int32_t *d_prio = nullptr, *ref = nullptr;
     int64_t *est = nullptr;
-    uint32_t *err = nullptr;
+    uint32_t *err = nullptr, *keep = nullptr;
     uint32_t h_err = 0;
     const size_t nv = (size_t)g->n * (size_t)var->V;
     {
@@ -699,7 +699,7 @@ dd_status dd_simulate_policy(const dd_graph *g, const dd_variants *var, int32_t 
     }
     TRY(copy_in(&err, (const uint32_t *)nullptr, 1, s), "alloc");
     {
-        const hipError_t e = dd::launch_sim_event(g, g->ev, var, policy, d_pp, d_prio, nullptr, nullptr,
+        const hipError_t e = dd::launch_sim_event(g, g->ev, var, policy, d_pp, d_prio, nullptr, nullptr, &keep,
                                                   d_finish, d_start, d_makespan, err, s);
         if (e != hipErrorNotSupported) {
             TRY(e, "simulate");
@@ -708,14 +708,26 @@ dd_status dd_simulate_policy(const dd_graph *g, const dd_variants *var, int32_t 
             TRY(rb.finish(), "sync");
         } else {
             h_err = 4u;
+            dd::dfree(keep, s);
+            keep = nullptr;
         }
     }
     if (h_err & 4u) {
         h_err = 0;
         TRY(hipMemsetAsync(err, 0, sizeof(uint32_t), s), "memset");
-        TRY(dd::dalloc_n(&ref, nv, s), "alloc reference counts");
-        TRY(dd::dalloc_n(&est, nv, s), "alloc start times");
-        TRY(dd::launch_sim_event(g, g->ev, var, policy, d_pp, d_prio, ref, est, d_finish, d_start,
+        hipError_t e = dd::dalloc_n(&ref, nv, s);
+        if (e == hipSuccess) e = dd::dalloc_n(&est, nv, s);
+        if (e == hipErrorOutOfMemory && keep) {  // (from the start, then)
+            (void)hipGetLastError();
+            dd::dfree(keep, s);
+            dd::dfree(ref, s);
+            keep = nullptr;
+            ref = nullptr;
+            e = dd::dalloc_n(&ref, nv, s);
+            if (e == hipSuccess) e = dd::dalloc_n(&est, nv, s);
+        }
+        TRY(e, "alloc reference counts and start times");
+        TRY(dd::launch_sim_event(g, g->ev, var, policy, d_pp, d_prio, ref, est, &keep, d_finish, d_start,
                                  d_makespan, err, s), "simulate");
         dd::ReadBack rb(s, sizeof(uint32_t));
         TRY(rb.add(&h_err, err, sizeof(uint32_t)), "read err");
@@ -734,6 +746,7 @@ fail_out:
     dd::dfree(ref, s);
     dd::dfree(est, s);
     dd::dfree(err, s);
+    dd::dfree(keep, s);
     return st;
 }
 

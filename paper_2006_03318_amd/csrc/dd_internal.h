@@ -400,15 +400,17 @@ hipError_t launch_breakdown(const dd_graph *g, const dd_variants *var, const uin
 // out-edge lists of g (dependencies in xin_*, thread order in thread_prev)
 hipError_t build_event_lists(const dd_graph *g, EventLists *ev, hipStream_t s);
 void free_event_lists(EventLists *ev, hipStream_t s);
-// ref: int32 [V][n], est: int64 [V][n] working memory; err: uint32, zeroed
-// by the caller (bit 0: a cycle, bit 1: frontier capacity exceeded).  With
-// ref == nullptr (est is not used): the kernel that keeps its frontier in
-// registers; hipErrorNotSupported where it does not take the call, and err
-// bit 2 when a variant outgrew it (outputs undefined: call again with ref)
+// err: uint32, zeroed by the caller (bit 0: a cycle, bit 1: frontier capacity
+// exceeded).  First with ref == nullptr (est is not used), the kernel that
+// keeps its frontier in registers: hipErrorNotSupported where it does not take
+// the call, and err bit 2 when a variant outgrew it; *keep then holds where
+// each variant stopped (the caller frees it, whatever is returned).  After
+// either of the two with ref: int32 [V][n] and est: int64 [V][n] as working
+// memory: every variant goes on from *keep, or from the start if it is null.
 hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_variants *var,
                             int32_t policy, const uint8_t *pp, const int32_t *prio, int32_t *ref,
-                            int64_t *est, int64_t *finish, int64_t *start, int64_t *makespan,
-                            uint32_t *err, hipStream_t s);
+                            int64_t *est, uint32_t **keep, int64_t *finish, int64_t *start,
+                            int64_t *makespan, uint32_t *err, hipStream_t s);
 constexpr int kEventQueue = 1024;      // ready tasks one variant may hold
 constexpr int kEventIdBits = 22;       // tasks: n < 2^22
 constexpr int kEventMaxThreads = 4096;

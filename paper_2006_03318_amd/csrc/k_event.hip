@@ -170,7 +170,19 @@ struct EvArgs {
     unsigned long long *est;               // [V][n] (times >= 0: unsigned order is the order)
     int64_t *finish, *start, *makespan;
     uint32_t *err;
+    const uint32_t *keep;                  // what k_sim_event_reg left, or null (then from the start)
+    int64_t keep_stride;
 };
+
+// What a variant's wave of k_sim_event_reg leaves when it stops, in words:
+//   0 tasks dispatched, 1 ready tasks (kFresh: it has not begun), 2 ready and
+//   waiting tasks, 4 and 5 base, 6 and 7 makespan so far, from kKeepP the
+//   threads' progress, from kKeepEnt the tasks, the ready ones first:
+//   { word, parents left (ready: 0), time or start so far }
+// (times as differences to the base; one before it counts as it: whatever
+// depends on it starts no earlier)
+constexpr int kKeepP = 8, kKeepEnt = kKeepP + 64;
+constexpr uint32_t kFresh = ~0u;
 
 // A frontier entry is 18 bytes: what schedule(Q) reads.  The rest of a task
 // (out-edges, duration, gap, class) is read when it is dispatched.
@@ -212,14 +224,19 @@ __global__ __launch_bounds__(64) void k_sim_event(EvArgs a) {
     const uint32_t vbit = 1u << (v & 31);
     const int vw = v >> 5;
 
+    const uint32_t *const kept = a.keep ? a.keep + (int64_t)v * a.keep_stride : nullptr;
+    const bool resume = kept && kept[1] != kFresh;
+    const int32_t before = resume ? (int32_t)kept[0] : 0;
+
     for (int t = lane; t < a.T; t += 64) sP[t] = 0;
     if (TLDS)
         for (int c = lane; c < a.n_cls; c += 64) sTab[c] = a.table[(int64_t)c * V + v];
     uint32_t err = 0;
 
     // reference counts over the active parents; tasks with none are ready
+    // (a variant that has none left needs no counts)
     int32_t qn = 0;
-    for (int64_t base = 0; base < n; base += 64) {
+    for (int64_t base = 0; base < n && !(resume && kept[1] == 0u); base += 64) {
         const int64_t u = base + lane;
         bool root = false;
         if (u < n) {
@@ -230,7 +247,7 @@ __global__ __launch_bounds__(64) void k_sim_event(EvArgs a) {
             }
             ref[u] = r;
             est[u] = 0ull;
-            root = r == 0;
+            root = r == 0 && !resume;
         }
         const uint64_t b = __ballot(root);
         if (root) {
@@ -248,6 +265,27 @@ __global__ __launch_bounds__(64) void k_sim_event(EvArgs a) {
     __syncthreads();
 
     int64_t ms = 0;
+    if (resume) {
+        const int64_t base = (int64_t)((uint64_t)kept[5] << 32 | kept[4]);
+        ms = (int64_t)((uint64_t)kept[7] << 32 | kept[6]);
+        qn = (int32_t)kept[1];
+        const int32_t cnt = (int32_t)kept[2];
+        for (int32_t i = lane; i < cnt; i += 64) {
+            const uint32_t *const e = kept + kKeepEnt + 3 * i;
+            const int64_t u = e[0] >> 10;
+            const int64_t t = base + e[2];
+            if (i < qn) {
+                push_entry(q, i, (uint32_t)u, a.pp ? a.pp[u] != 0 : false, (a.rm[u * a.W + vw] & vbit) != 0u,
+                           a.tid[u], a.prio ? a.prio[u] : 0, t);
+            } else {
+                ref[u] = (int32_t)e[1];
+                est[u] = (unsigned long long)t;
+            }
+        }
+        for (int t = lane; t < a.T; t += 64) sP[t] = base + kept[kKeepP + t];
+        __threadfence();
+        __syncthreads();
+    }
     int32_t done = 0;
     int32_t bu = 0;                 // this lane's buffered result: task, finish, start
     int64_t bf = 0, bs = 0;
@@ -372,7 +410,7 @@ __global__ __launch_bounds__(64) void k_sim_event(EvArgs a) {
         a.finish[(int64_t)bu * V + v] = bf;
         if (a.start) a.start[(int64_t)bu * V + v] = bs;
     }
-    if (done != n) err |= 1u;
+    if (before + done != n) err |= 1u;
     for (int o = 32; o > 0; o >>= 1) err |= (uint32_t)__shfl_xor((int)err, o, 64);
     if (lane == 0) {
         a.makespan[v] = ms;
@@ -404,8 +442,11 @@ __global__ __launch_bounds__(64) void k_sim_event(EvArgs a) {
 //     wait in kPendM places per lane (word, parents left, start so far),
 //     found by a ballot; the threads' progress is one register.
 // Capacity (ready and waiting tasks, times 2^31 ahead of the last dispatch)
-// is not known beforehand: a wave that runs out sets error bit 2 and stops, as do the others when they see it,
-// and the caller runs k_sim_event.
+// is not known beforehand: a wave that runs out sets error bit 2 and stops, as
+// do the others when they see it, and the caller runs k_sim_event, which goes
+// on from the last move of the window: at each, every wave leaves its state in
+// memory.  (4,400 tasks of which the 3,990th releases 400:
+// 7.2 ms in k_sim_event alone, 12.6 when it began again, 6.2 now, 30 variants.)
 // What bounds it: the instructions of one wave, about 2,000 cycles a step
 // (choosing the task 560, the priority rule up to 700 more, dispatch and
 // raised times 620, children 750); at 2,048 variants another 650, in which a
@@ -433,7 +474,8 @@ struct alignas(32) EvTask {
     uint4 a, b;
 };
 
-__global__ __launch_bounds__(kBS) void k_ev_task(int32_t n, const int4 *__restrict__ rec,
+// (a thread per out-edge, and one per task: a task may have any number of them)
+__global__ __launch_bounds__(kBS) void k_ev_task(int32_t n, int64_t n_edges, const int4 *__restrict__ rec,
                                                  const uint32_t *__restrict__ edges,
                                                  const int64_t *__restrict__ dur,
                                                  const int64_t *__restrict__ gap,
@@ -445,22 +487,20 @@ __global__ __launch_bounds__(kBS) void k_ev_task(int32_t n, const int4 *__restri
                                                  uint32_t *__restrict__ parents,
                                                  uint32_t *__restrict__ roots) {
     const int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x;
-    if (u >= n) return;
     auto count = [&](uint32_t c) {
         return (uint32_t)(in_ptr[c + 1] - in_ptr[c]) + (prev[c] >= 0 ? 1u : 0u);
     };
     auto word = [&](uint32_t c) { return c << 10 | (uint32_t)rec[c].z << 4 | ((pp && pp[c]) ? kWordPP : 0u); };
+    auto edge = [&](int64_t j) {
+        const uint32_t c = edges[j] >> 8, k = count(c);
+        return word(c) | (k < kMany ? k : kMany);
+    };
+    if (u < n_edges) words[u] = edge(u);
+    if (u >= n) return;
     const int4 r = rec[u];
     EvTask t;
     t.a = make_uint4((uint32_t)dur[u], (uint32_t)gap[u], (uint32_t)r.w, prio ? (uint32_t)prio[u] : 0u);
-    t.b = make_uint4(0u, 0u, (uint32_t)r.x, (uint32_t)r.y);
-    for (int32_t j = 0; j < r.y; j++) {
-        const uint32_t c = edges[(int64_t)r.x + j] >> 8, k = count(c);
-        const uint32_t w = word(c) | (k < kMany ? k : kMany);
-        if (j == 0) t.b.x = w;
-        if (j == 1) t.b.y = w;
-        words[(int64_t)r.x + j] = w;
-    }
+    t.b = make_uint4(r.y > 0 ? edge(r.x) : 0u, r.y > 1 ? edge((int64_t)r.x + 1) : 0u, (uint32_t)r.x, (uint32_t)r.y);
     out[u] = t;
     const uint32_t k = count((uint32_t)u);
     parents[u] = k;
@@ -477,6 +517,8 @@ struct EvRegArgs {
     const uint32_t *__restrict__ rm;       // [n][W]
     int64_t *finish, *start, *makespan;
     uint32_t *err;
+    uint32_t *keep;                        // [V][keep_stride]
+    int64_t keep_stride;
 };
 
 // LDS of a workgroup: the window, then each wave's scale entries and removal
@@ -629,21 +671,54 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_sim_event_reg(EvRegArgs a) {
         return true;
     };
 
+    int64_t base = 0, ms = 0;       // time of the 32-bit zero; makespan
+    int32_t done = 0;
+    // where the variant stands, for k_sim_event to go on from
+    uint32_t *const kp = a.keep + (int64_t)(mine ? v : 0) * a.keep_stride;
+    auto keep = [&]() {
+        uint32_t c = 0;
+        auto list = [&](bool is, uint32_t w, uint32_t l, uint32_t x) {
+            const uint64_t b = __ballot(is);
+            uint32_t *const e = kp + kKeepEnt + 3 * (c + (uint32_t)__popcll(b & ((1ull << lane) - 1ull)));
+            if (is) {
+                e[0] = w;
+                e[1] = l;
+                e[2] = x;
+            }
+            c += (uint32_t)__popcll(b);
+        };
+#pragma unroll
+        for (int k = 0; k < kRegK; k++) list(key[k] != ~0u, key[k], 0u, t[k]);
+        const uint32_t r = c;
+#pragma unroll
+        for (int m = 0; m < kPendM; m++) list(pid[m] != ~0u, pid[m], left[m], pst[m]);
+        kp[kKeepP + lane] = P;
+        if (lane == 0) {
+            kp[0] = (uint32_t)done;
+            kp[1] = r;
+            kp[2] = c;
+            kp[4] = (uint32_t)base;
+            kp[5] = (uint32_t)((uint64_t)base >> 32);
+            kp[6] = (uint32_t)ms;
+            kp[7] = (uint32_t)((uint64_t)ms >> 32);
+        }
+    };
+
     stage(0, whole ? (a.n + 63) & ~63 : a.win / 2);
     __syncthreads();
     if (mine) {
         const uint32_t nr = __builtin_amdgcn_readfirstlane(a.roots[0]);
+        if (lane == 0) kp[1] = kFresh;
         for (uint32_t i = 0; i < nr && !err; i++) put(__builtin_amdgcn_readfirstlane(a.roots[1 + i]), 0u, -1, 0);
     }
 
-    int64_t base = 0, ms = 0;       // time of the 32-bit zero; makespan
-    int32_t done = 0;
     uint32_t bu = 0;                // this lane's buffered result: task, finish, start
     int64_t bf = 0, bs = 0;
     bool run = mine && !err;        // (uniform per wave)
     for (int32_t S = 0; S < a.n; S += kRegStage) {
         // ---- the window moves on; every wave has done S steps or has ended ----
         if (S > 0) {
+            if (mine && !err) keep();
             if (threadIdx.x == 0) sStop = load_coherent(a.err) & 4u;
             if (!whole) {
                 __syncthreads();
@@ -862,8 +937,9 @@ void free_event_lists(EventLists *ev, hipStream_t s) {
 
 hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_variants *var,
                             int32_t policy, const uint8_t *pp, const int32_t *prio, int32_t *ref,
-                            int64_t *est, int64_t *finish, int64_t *start, int64_t *makespan,
-                            uint32_t *err, hipStream_t s) {
+                            int64_t *est, uint32_t **keep, int64_t *finish, int64_t *start,
+                            int64_t *makespan, uint32_t *err, hipStream_t s) {
+    const int64_t keep_stride = kKeepEnt + 3 * (g->n < 64 * (kRegK + kPendM) ? g->n : 64 * (kRegK + kPendM));
     if (!ref) {
         // the frontier in registers: every edge class of the graph on in
         // every variant (a task's parents are then the same in all of them),
@@ -883,12 +959,15 @@ hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_va
         if (e == hipSuccess) e = dalloc_n(&words, (size_t)ev.n_edges + 1, s);
         if (e == hipSuccess) e = dalloc_n(&parents, (size_t)g->n, s);
         if (e == hipSuccess) e = dalloc_n(&roots, (size_t)g->n + 1, s);
+        if (e == hipSuccess) e = dalloc_n(keep, (size_t)var->V * (size_t)keep_stride, s);
         if (e == hipSuccess) e = hipMemsetAsync(roots, 0, sizeof(uint32_t), s);
         if (e == hipSuccess) {
-            k_ev_task<<<grid_for(g->n, kBS), kBS, 0, s>>>(g->n, ev.rec, ev.edges, g->dur, g->gap, g->xin_ptr,
-                                                          g->thread_prev, pp, prio, task, words, parents, roots);
+            const int64_t most = ev.n_edges > g->n ? ev.n_edges : g->n;
+            k_ev_task<<<grid_for(most, kBS), kBS, 0, s>>>(g->n, ev.n_edges, ev.rec, ev.edges, g->dur, g->gap,
+                                                          g->xin_ptr, g->thread_prev, pp, prio, task, words, parents,
+                                                          roots);
             const EvRegArgs r{g->n, var->V, var->W, var->n_cls, win, task, words, parents, roots,
-                              var->table, var->rm_bits, finish, start, makespan, err};
+                              var->table, var->rm_bits, finish, start, makespan, err, *keep, keep_stride};
             auto go = [&](auto st, auto pr) {
                 k_sim_event_reg<decltype(st)::value, decltype(pr)::value>
                     <<<(var->V + waves - 1) / waves, 64 * waves, reg_lds(win, waves, var->n_cls), s>>>(r);
@@ -904,9 +983,15 @@ hipError_t launch_sim_event(const dd_graph *g, const EventLists &ev, const dd_va
         dfree(words, s);
         dfree(parents, s);
         dfree(roots, s);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();             // k_sim_event alone may need less
+            e = hipErrorNotSupported;
+        }
         return e;
     }
     EvArgs a;
+    a.keep = *keep;
+    a.keep_stride = keep_stride;
     a.n = g->n;
     a.V = var->V;
     a.W = var->W;

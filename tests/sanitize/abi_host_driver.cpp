@@ -36,8 +36,8 @@ hipError_t launch_breakdown(const dd_graph *, const dd_variants *, const uint8_t
 hipError_t build_event_lists(const dd_graph *, EventLists *, hipStream_t) { STUB; }
 void free_event_lists(EventLists *ev, hipStream_t) { *ev = EventLists(); }
 hipError_t launch_sim_event(const dd_graph *, const EventLists &, const dd_variants *, int32_t,
-                            const uint8_t *, const int32_t *, int32_t *, int64_t *, int64_t *,
-                            int64_t *, int64_t *, uint32_t *, hipStream_t) { STUB; }
+                            const uint8_t *, const int32_t *, int32_t *, int64_t *, uint32_t **,
+                            int64_t *, int64_t *, int64_t *, uint32_t *, hipStream_t) { STUB; }
 }  // namespace dd
 
 static int g_bad = 0;

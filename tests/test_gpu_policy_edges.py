@@ -99,3 +99,92 @@ def test_long_times(policy, max_dur):
     _check(g, vs, policy, pp, prio, "long")
     vs = H.variants(g, V=2)
     _check(g, vs, policy, pp, prio, "long-unscaled")
+
+
+def _late(seed, n, fan, at, parents=1, V=5, max_dur=1000):
+    """A graph as in _case with `fan` more tasks on its last thread, each of
+    which waits for task `at` and (parents > 1) for tasks after it."""
+    g, vs, pp, prio = _case(seed, n, V=V, max_dur=max_dur)
+    ps = np.minimum(at + 3 * np.arange(parents), n - 1)
+    rep = lambda a, v: np.r_[a, np.full(fan, v)].astype(a.dtype)
+    g2 = W.TaskGraph(n + fan, g.n_threads, np.r_[g.in_ptr, g.in_ptr[-1] + parents * (1 + np.arange(fan))],
+                     np.r_[g.in_src, np.tile(ps, fan)].astype(np.int32), np.r_[g.edge_cls, np.zeros(fan * parents, np.uint8)],
+                     rep(g.thread_prev, -1), rep(g.thread_id, g.n_threads - 1), rep(g.dur, 7), rep(g.gap, 1),
+                     rep(g.node_cls, 0), g.n_node_cls, g.n_edge_cls, rep(g.kind, 0), rep(g.layer, -1),
+                     rep(g.launch_of, -1), "late")
+    rng = np.random.default_rng(seed + 1)
+    return g2, W.random_variants(rng, g2, V, p_remove=0.2), rep(pp, 1), np.r_[prio, rng.integers(-2, 3, fan)].astype(np.int32)
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("at,parents,V", [(0, 1, 3), (1, 2, 9), (63, 1, 5), (64, 3, 5), (300, 1, 33), (700, 2, 257),
+                                          (890, 1, 2049), (899, 1, 5)])
+def test_goes_on_where_it_stopped(policy, at, parents, V):
+    """300 tasks become ready, or begin to wait, late in the run: the general
+    kernel goes on from there, in every variant from its own place."""
+    require_gpu()
+    g, vs, pp, prio = _late(7000 + at, 900, 300, at, parents, V)
+    _check(g, vs, policy, pp, prio, "late%d" % at)
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+def test_some_variants_stop_and_others_end(policy):
+    """A task that lasts longer than 32-bit differences hold in the variants
+    that stretch it; the others run past it, or have ended, when they hear."""
+    require_gpu()
+    for u, n in ((40, 400), (390, 400), (20, 3000), (2990, 3000)):
+        g, _, pp, prio = _case(n + u, n, n_cls=2, max_dur=10**6)
+        g.node_cls[:] = 0
+        g.node_cls[u] = 1
+        g.dur[u] = 1 << 31
+        vs = H.variants(g, scales=[{}, {1: (2, 1)}, {1: (1, 8)}, {1: (3, 1), 0: (1, 2)}, {1: (0, 1)}] * 4)
+        _check(g, vs, policy, pp, prio, "some%d" % u)
+
+
+def test_errors_after_going_on():
+    """Past the registers, a cycle and a frontier beyond the capacity."""
+    from paper_2006_03318_amd import batch as BT
+    from paper_2006_03318_amd import binding as B
+    require_gpu()
+    g, vs, pp, prio = _late(7100, 900, 300, 500)
+    g.in_src[-1], g.in_src[-2] = g.n - 2, g.n - 1         # the last two tasks wait for each other
+    with pytest.raises(B.DDError) as ei:
+        BT.simulate_policy(g, vs, 1, pp, prio)
+    assert ei.value.code == B.DD_ECYCLE
+    g, vs, pp, prio = _late(7200, 900, 1100, 500)
+    with pytest.raises(B.DDError) as ei:
+        BT.simulate_policy(g, vs, 1, pp, prio)
+    assert ei.value.code == B.DD_ELIMIT
+
+
+def test_a_call_does_not_pay_for_both_kernels():
+    """A graph that outgrows the registers at its end takes no longer than the
+    general kernel takes for all of it (which runs where threads number 65)."""
+    import time
+
+    import torch
+    from paper_2006_03318_amd import binding as B
+    require_gpu()
+    g, vs, pp, prio = _late(7300, 4000, 400, 3990, V=30)
+
+    def seconds(n_threads):
+        t = lambda a, d: torch.from_numpy(np.ascontiguousarray(a).astype(d)).cuda()
+        h = B.dd_graph_load_ex(g.n, n_threads, t(g.in_ptr, np.int64), t(g.in_src, np.int32), None, t(g.thread_prev, np.int32),
+                               t(g.thread_id, np.int32), t(g.dur, np.int64), t(g.gap, np.int64), t(g.node_cls, np.uint16),
+                               B.DD_LOAD_SHARED_THREADS)
+        var = B.dd_apply_transforms(h, 30, int(vs.scale.shape[0]), t(vs.scale, np.int32), t(vs.remove_bits, np.uint32), None)
+        fin = torch.empty((g.n, 30), dtype=torch.int64, device="cuda")
+        ms = torch.empty(30, dtype=torch.int64, device="cuda")
+        ppd, prd = t(pp, np.uint8), t(prio, np.int32)
+        best = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            at = time.perf_counter()
+            B.dd_simulate_policy(h, var, B.DD_POLICY_PRIORITY, ppd, prd, fin, None, ms)
+            best.append(time.perf_counter() - at)
+        B.dd_variants_free(var)
+        B.dd_graph_free(h)
+        return min(best), fin.cpu().numpy()
+    (late, f0), (general, f1) = seconds(g.n_threads), seconds(65)
+    assert np.array_equal(f0, f1)
+    assert late < 1.25 * general, (late, general)
