@@ -321,8 +321,9 @@ dd_status dd_simulate_policy(const dd_graph *g, const dd_variants *var, int32_t 
 /*
  * dd_release_cache -- wait for all work on the current device, then return
  * every block of the library's device-memory cache for that device to the
- * device (hipFree).  Memory held by live handles is not touched.  For callers
- * that share the GPU with another allocator (e.g. torch) and need the space.
+ * device (hipFree), and the pinned host buffers (68 KiB each) that ended host
+ * threads left.  Memory held by live handles is not touched.  For callers that
+ * share the GPU with another allocator (e.g. torch) and need the space.
  */
 dd_status dd_release_cache(void);
 

@@ -174,15 +174,6 @@ void dfree(void *p, hipStream_t s) {
     g_live.erase(it);
 }
 
-hipError_t release_cache() {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lk(g_mu);
-    release_cached(dev);
-    return hipGetLastError();
-}
-
 hipError_t note_use(ForeignUses &u, hipStream_t own, hipStream_t s) {
     if (s == own) return hipSuccess;
     std::lock_guard<std::mutex> lk(u.mu);
@@ -208,42 +199,92 @@ void join_uses(ForeignUses &u, hipStream_t own) {
 }
 
 namespace {
-// this host thread's pinned buffer of at least `bytes`; a buffer that is
-// outgrown is kept (a copy queued earlier may still target it)
-char *stage_buf(size_t bytes, hipError_t *e) {
-    thread_local char *buf = nullptr;
-    thread_local size_t cap = 0;
-    *e = hipSuccess;
-    if (bytes > cap) {
-        size_t c = cap ? cap : 4096;
-        while (c < bytes) c *= 2;
-        char *nb = nullptr;
-        *e = hipHostMalloc(reinterpret_cast<void **>(&nb), c, hipHostMallocDefault);
-        if (*e != hipSuccess) return nullptr;
-        buf = nb;
-        cap = c;
+// Pinned host memory, a block per host thread that calls the library: results
+// that kernels write (kDirectBytes), then read-backs (kStageBytes).  A thread
+// that ends leaves its block to later ones (every call waits for its work
+// before it returns), so there are as many as threads ran at once;
+// dd_release_cache frees those that no thread holds.
+constexpr size_t kStageBytes = 4096;
+struct HostBlock {
+    char *host = nullptr, *dev = nullptr;
+};
+struct HostBlocks {
+    std::mutex mu;
+    std::vector<HostBlock> left;
+};
+HostBlocks &host_blocks() {
+    static HostBlocks *const b = new HostBlocks;   // (threads may end after static objects)
+    return *b;
+}
+struct ThreadBlock {
+    HostBlock b;
+    ~ThreadBlock() {
+        if (!b.host) return;
+        HostBlocks &all = host_blocks();
+        std::lock_guard<std::mutex> lk(all.mu);
+        try {
+            all.left.push_back(b);
+        } catch (...) {
+            (void)hipHostFree(b.host);
+        }
     }
-    return buf;
+};
+
+hipError_t host_block(HostBlock *out) {
+    thread_local ThreadBlock mine;
+    if (!mine.b.host) {
+        HostBlocks &all = host_blocks();
+        std::lock_guard<std::mutex> lk(all.mu);
+        if (!all.left.empty()) {
+            mine.b = all.left.back();
+            all.left.pop_back();
+        } else {
+            void *h = nullptr, *d = nullptr;
+            hipError_t e = hipHostMalloc(&h, kDirectBytes + kStageBytes, hipHostMallocPortable | hipHostMallocMapped);
+            if (e != hipSuccess) return e;
+            e = hipHostGetDevicePointer(&d, h, 0);
+            if (e != hipSuccess) {
+                (void)hipHostFree(h);
+                return e;
+            }
+            mine.b = HostBlock{static_cast<char *>(h), static_cast<char *>(d)};
+        }
+    }
+    *out = mine.b;
+    return hipSuccess;
+}
+
+void release_host_blocks() {
+    HostBlocks &all = host_blocks();
+    std::lock_guard<std::mutex> lk(all.mu);
+    for (const HostBlock &b : all.left) (void)hipHostFree(b.host);
+    all.left.clear();
 }
 }  // namespace
 
+hipError_t release_cache() {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    release_host_blocks();
+    std::lock_guard<std::mutex> lk(g_mu);
+    release_cached(dev);
+    return hipGetLastError();
+}
+
 hipError_t direct_buf(void **host, void **dev) {
-    thread_local void *buf = nullptr, *dbuf = nullptr;
-    if (!buf) {
-        void *nb = nullptr;
-        hipError_t e = hipHostMalloc(&nb, kDirectBytes, hipHostMallocPortable | hipHostMallocMapped);
-        if (e == hipSuccess) e = hipHostGetDevicePointer(&dbuf, nb, 0);
-        if (e != hipSuccess) return e;
-        buf = nb;
-    }
-    *host = buf;
-    *dev = dbuf;
-    return hipSuccess;
+    HostBlock b;
+    const hipError_t e = host_block(&b);
+    *host = b.host;
+    *dev = b.dev;
+    return e;
 }
 
 ReadBack::ReadBack(hipStream_t s, size_t cap) : s_(s) {
     cap_ = cap + 8 * 16;                  // room for aligning up to 16 items
-    buf_ = stage_buf(cap_, &err_);
+    HostBlock b;
+    err_ = cap_ > kStageBytes ? hipErrorInvalidValue : host_block(&b);
+    if (err_ == hipSuccess) buf_ = b.host + kDirectBytes;
 }
 
 hipError_t ReadBack::add(void *dst, const void *src, size_t n) {

@@ -197,8 +197,7 @@ struct dd_variants {
 
 namespace dd {
 
-// Read-backs of small results through a pinned host buffer (one per host
-// thread, kept until the process ends).  A copy from the device into
+// Read-backs of small results (below 4,000 bytes) through a pinned host buffer.  A copy from the device into
 // pageable memory waits for its stream by itself (about 10 us each); into
 // pinned memory it is a plain DMA, so the queued copies of one read-back
 // cost one synchronization.  cap = the bytes that will be queued.
@@ -249,9 +248,8 @@ inline int64_t chunk_len(int64_t n, int bs) {
     return ((n + kChunks - 1) / kChunks + bs - 1) / bs * bs;
 }
 
-// Results that kernels write straight into host memory (a pinned buffer per
-// host thread, kept until the process ends; read after the stream has been
-// waited for): no copy, and no launch for one.  *dev receives the address
+// Results that kernels write straight into host memory (a pinned buffer of
+// this host thread; read after the stream has been waited for): no copy, and no launch for one.  *dev receives the address
 // kernels use.
 constexpr size_t kDirectBytes = 64 << 10;
 hipError_t direct_buf(void **host, void **dev);

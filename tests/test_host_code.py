@@ -24,3 +24,17 @@ def test_sizes_of_launches_and_arrays(tmp_path):
     subprocess.check_call([CLANGXX, "-O1", "-std=c++17", *INC, os.path.join(ROOT, "tests", "host", "layout.cpp"),
                            "-o", exe])
     _run(exe)
+
+
+def test_pinned_memory_of_ended_threads(tmp_path):
+    """Host threads that come and go share their pinned buffers, and
+    dd_release_cache returns them (the API layer alone, on host memory)."""
+    hipcc = "/opt/rocm/bin/hipcc"
+    if not (os.path.exists(CLANGXX) and os.path.exists(hipcc)):
+        pytest.skip("no ROCm compilers")
+    obj, exe = str(tmp_path / "dd_api.o"), str(tmp_path / "pinned")
+    subprocess.check_call([hipcc, "--offload-host-only", "-O1", "-std=c++17", *INC[2:], "-c",
+                           os.path.join(CSRC, "dd_api.hip"), "-o", obj], stderr=subprocess.DEVNULL)
+    subprocess.check_call([CLANGXX, "-O1", "-std=c++17", *INC, os.path.join(ROOT, "tests", "host", "pinned.cpp"), obj,
+                           "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-pthread", "-o", exe])
+    _run(exe)
