@@ -1214,8 +1214,14 @@ dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sch
     CK(dalloc_n(&sch->rec, N1, s));
     CK(dalloc_n(&sch->bat, (size_t)solo_batch_max(n), s));
     CK(dalloc_n(&sch->nbat, 1, s));
-    // (one more than n: idle lanes read it)
-    if (g->dmax < (int64_t(1) << 32) && g->gmax < (int64_t(1) << 32)) CK(dalloc_n(&sch->so_rec, N1, s));
+    // Records of the one-variant-per-workgroup kernel (one more than n: idle
+    // lanes read it); where there is no memory for them, the schedule goes
+    // without, and the kernels that need less serve it.
+    if (g->dmax < (int64_t(1) << 32) && g->gmax < (int64_t(1) << 32)) {
+        const hipError_t e = dalloc_n(&sch->so_rec, N1, s);
+        if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+        else CK(e);
+    }
     if (n == 0) {
         CK(hipMemsetAsync(sch->step_ptr, 0, sizeof(int32_t), s));
         sch->h_step_ptr.assign(1, 0);

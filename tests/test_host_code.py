@@ -38,3 +38,18 @@ def test_pinned_memory_of_ended_threads(tmp_path):
     subprocess.check_call([CLANGXX, "-O1", "-std=c++17", *INC, os.path.join(ROOT, "tests", "host", "pinned.cpp"), obj,
                            "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-pthread", "-o", exe])
     _run(exe)
+
+
+def test_schedule_without_memory_for_every_record(tmp_path):
+    """dd_levelize succeeds where all but the records of the one-variant
+    kernel fit (host code alone: launches do nothing, allocations past a
+    limit fail)."""
+    hipcc = "/opt/rocm/bin/hipcc"
+    if not (os.path.exists(CLANGXX) and os.path.exists(hipcc)):
+        pytest.skip("no ROCm compilers")
+    obj, exe = str(tmp_path / "k_levelize.o"), str(tmp_path / "levelize_memory")
+    subprocess.check_call([hipcc, "--offload-host-only", "-O1", "-std=c++17", *INC[2:], "-c",
+                           os.path.join(CSRC, "k_levelize.hip"), "-o", obj], stderr=subprocess.DEVNULL)
+    subprocess.check_call([CLANGXX, "-O1", "-std=c++17", *INC, os.path.join(ROOT, "tests", "host", "levelize_memory.cpp"),
+                           obj, "-pthread", "-Wl,--unresolved-symbols=ignore-all", "-o", exe])   # (no device code)
+    _run(exe)
