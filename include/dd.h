@@ -206,11 +206,15 @@ dd_status dd_simulate_batch(const dd_graph *g, const dd_sched *sched, const dd_v
  *   path measured faster).  Otherwise up to 768 variants (2,048 when steps
  *   hold at most 32 positions on average) run one per workgroup, in a kernel
  *   that holds times as integers in doubles (scaled times below 2.0e15 ns in
- *   sum, durations and gaps below 2^32) and needs V * 256 KiB of scratch at
- *   most; the strip kernel serves every other call.
+ *   sum, durations and gaps below 2^32, each duration times p below 2^50, at
+ *   most 2,048 task classes) and needs V * (256 KiB + n / 8 bytes) of scratch
+ *   at most, which stays in the library's cache (dd_release_cache); the strip
+ *   kernel serves every other call, and those for which that scratch cannot
+ *   be had.
  * The results do not depend on the shape (Algorithm 1 per variant, Sec. 4.1);
  * only the number of workgroups and the kernel instance do.  For tuning, and
- * for checking every compiled instance.
+ * for checking the compiled instances (the strip kernel with one variant per
+ * workgroup is reached by dd_simulate_batch_noalloc with up to 256 variants).
  */
 dd_status dd_simulate_batch_vs(const dd_graph *g, const dd_sched *sched, const dd_variants *var,
                                int64_t *d_finish, int64_t *d_start, int64_t *d_makespan,
@@ -334,8 +338,9 @@ dd_status dd_sched_task_steps(const dd_sched *sched, int32_t *steps_out, void *s
  * dd_simulate_plan -- the launch shape dd_simulate_batch takes for these
  * handles, in the terms of dd_simulate_batch_vs: *variants_per_wg = 1, 2, 4,
  * 8 or 16 (one workgroup per strip of that many variants for the whole
- * schedule, one launch) or -1, -2, -4, -8 (the few-variant path, one launch per
- * step).  DD_EINVAL on a NULL argument.
+ * schedule, one launch; 1 for either kernel that owns one variant) or -1, -2,
+ * -4, -8 (the few-variant path, one launch per step).  DD_EINVAL on a NULL
+ * argument.
  */
 dd_status dd_simulate_plan(const dd_sched *sched, const dd_variants *var,
                            int32_t *variants_per_wg);
