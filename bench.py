@@ -175,7 +175,7 @@ def kernel_source_digest():
     the build script (it holds the kernel's compile flags)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("csrc/k_simulate.hip", "csrc/dd_internal.h", "csrc/dd_common.h", "build.py"):
+    for f in ("csrc/k_simulate.hip", "csrc/dd_internal.h", "csrc/dd_common.h", "csrc/dd_time.h", "build.py"):
         with open(os.path.join(ROOT, "paper_2006_03318_amd", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

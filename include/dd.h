@@ -272,7 +272,8 @@ dd_status dd_simulate_batch_noalloc(const dd_graph *g, const dd_sched *sched, co
  *              for the first task);
  *   CPU+GPU parallel = total - CPU-only - GPU-only.
  *   role        uint8 [n], host or device: 1 = GPU kernel, 2 = CPU call that
- *               waits for GPU work, any other value = neither.
+ *               waits for GPU work, any other value = neither.  On the
+ *               device it is read by the work that the call queues.
  *   d_finish    device int64 [n][V], d_makespan device int64 [V]: the outputs
  *               of dd_simulate_batch for (g, var), complete on `stream`.
  *   d_out       device int64 [V][4]: total, CPU-only, GPU-only, CPU+GPU

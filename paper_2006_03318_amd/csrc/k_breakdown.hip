@@ -23,7 +23,7 @@
 // three instructions for any q.  Sums join the output with one atomic per
 // variant and workgroup.  32,768 tasks x 256 variants: 14 us a call (199 with
 // a sort of the whole graph by class and four variants per lane), 262,144 x
-// 1,000: 72 us (250).
+// 1,000: 69 us (250).
 
 #include "dd_common.h"
 #include "dd_internal.h"
@@ -243,7 +243,7 @@ hipError_t launch_breakdown(const dd_graph *g, const dd_variants *var, const uin
         // chunks as long as leaves about four workgroups per compute unit,
         // from 256 tasks (shorter ones are mostly sorting) to 512 (longer
         // ones leave fewer workgroups resident: 262,144 tasks x 1,000 variants
-        // 95 us with 2,048 tasks per chunk, 77 with 1,024, 72 with 512)
+        // 95 us with 2,048 tasks per chunk, 77 with 1,024, 69 with 512)
         const int64_t bx = (var->V + kBV - 1) / kBV;
         int64_t chunk = kBT;
         while (chunk < kMaxChunk && (g->n + chunk - 1) / chunk * bx > 1024) chunk *= 2;

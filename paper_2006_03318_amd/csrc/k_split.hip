@@ -456,12 +456,15 @@ int split_width(const dd_sched *sch, const dd_variants *var) {
     if (sch->n <= 0 || var->V <= 0 || (int64_t)sch->h_step_ptr.size() != sch->n_steps + 1)
         return 0;
     // Fewer than 1,024 variants only: below that the one-workgroup-per-strip
-    // kernel either leaves compute units idle or runs its workgroups in two
-    // passes (one variant per workgroup up to 511 variants, two up to
-    // 1,023).  Then by measured cost: that kernel takes about 1.8 us per round
-    // of 512 positions, this path about 8 us per step (a launch and its
-    // chain of memory trips), so this one wins when steps hold more than
-    // about 4.4 rounds on average.
+    // kernel (k_simulate.hip) either leaves compute units idle or runs its
+    // workgroups in two passes (one variant per workgroup up to 511 variants,
+    // two up to 1,023).  Then by measured cost: that kernel takes about 1.8 us
+    // per round of 512 positions, this path about 8 us per step (a launch and
+    // its chain of memory trips), so this one wins when steps hold more than
+    // about 4.4 rounds on average.  The line is drawn against the strip kernel:
+    // k_solo.hip, which takes such calls up to 768 variants otherwise, costs
+    // 1.1 to 1.8 us a round, which puts the line against it at 4.4 to 7 rounds;
+    // that has not been measured.
     if (var->V >= 1024) return 0;
     const std::vector<int32_t> &sp = sch->h_step_ptr;
     int64_t rounds = 0, wmax = 0;

@@ -1,5 +1,8 @@
-"""Host code of the library on the CPU, compiled from its own sources."""
+"""Host code of the library on the CPU, compiled from its own sources, and the
+benchmark's digest of them."""
+import inspect
 import os
+import re
 import subprocess
 
 import pytest
@@ -53,3 +56,18 @@ def test_schedule_without_memory_for_every_record(tmp_path):
     subprocess.check_call([CLANGXX, "-O1", "-std=c++17", *INC, os.path.join(ROOT, "tests", "host", "levelize_memory.cpp"),
                            obj, "-pthread", "-Wl,--unresolved-symbols=ignore-all", "-o", exe])   # (no device code)
     _run(exe)
+
+
+def test_digest_covers_the_sources_of_the_kernel():
+    """bench.py quotes a measured traffic only for the sources it was measured
+    on: every file that the kernel includes counts."""
+    import bench
+    named = set(re.findall(r"csrc/([\w.]+)", inspect.getsource(bench.kernel_source_digest)))
+    todo, seen = ["k_simulate.hip"], set()
+    while todo:
+        f = todo.pop()
+        seen.add(f)
+        with open(os.path.join(CSRC, f)) as fh:
+            inc = re.findall(r'#include "([\w.]+)"', fh.read())
+        todo += [i for i in inc if i not in seen and os.path.exists(os.path.join(CSRC, i))]
+    assert seen <= named, seen - named
