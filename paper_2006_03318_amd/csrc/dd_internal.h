@@ -296,7 +296,7 @@ dd_status levelize_device(const dd_graph *g, uint64_t mask, int32_t mode, dd_sch
 
 // transforms (k_transform.hip): everything dd_apply_transforms does on the
 // device, complete on return
-constexpr int kTransformBlocks = 512;
+constexpr int kTransformBlocks = 512, kMaskBlocks = 64;
 struct TransformIn {
     int32_t n_cls, V;
     const dd_ratio *scale;        // device, or null: 1/1
@@ -314,6 +314,7 @@ struct TransformOut {
         uint32_t err, magic;
         int64_t pmax, rmax_bits;
     } blk[kTransformBlocks];
+    uint64_t used[kMaskBlocks], all[kMaskBlocks];   // the masks, per block
 };
 DD_PASS hipError_t transforms_device(const TransformIn &t, ScaleEntry *table, TransformOut *out,
                                      TransformOut *out_dev, hipStream_t s);

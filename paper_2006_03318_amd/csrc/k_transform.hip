@@ -26,24 +26,26 @@ __device__ uint32_t ceil_log2(uint32_t q) {
 constexpr int kTabBlocks = kTransformBlocks;   // grid-stride blocks of the table
 
 // One launch per call: the first blocks build the table and leave what they
-// saw (errors, bounds) in host memory, one line per block; one block copies
-// the edge-class masks and folds them; the rest copy the removal bits (large
-// ones are copied by the runtime).
+// saw (errors, bounds) in host memory, one line per block; the next copy the
+// edge-class masks and fold them; the rest copy the removal bits (large ones
+// are copied by the runtime).
 __global__ __launch_bounds__(kBS) void k_transforms(TransformIn t, ScaleEntry *__restrict__ table,
-                                                    int32_t tab_blocks, TransformOut *__restrict__ out) {
+                                                    int32_t tab_blocks, int32_t mask_blocks,
+                                                    TransformOut *__restrict__ out) {
     const int b = (int)blockIdx.x;
     constexpr int NW = kBS / 64;
     __shared__ int64_t red[4][NW];
     const int w = threadIdx.x >> 6;
-    if (b > tab_blocks) {                            // removal bits
-        const int64_t step = (int64_t)(gridDim.x - tab_blocks - 1) * kBS;
-        for (int64_t i = (int64_t)(b - tab_blocks - 1) * kBS + threadIdx.x; i < t.rm_words; i += step)
+    const int mb = b - tab_blocks, rb0 = mb - mask_blocks;
+    if (rb0 >= 0) {                                  // removal bits
+        const int64_t step = (int64_t)(gridDim.x - tab_blocks - mask_blocks) * kBS;
+        for (int64_t i = (int64_t)rb0 * kBS + threadIdx.x; i < t.rm_words; i += step)
             t.rm_dst[i] = t.rm_src ? t.rm_src[i] : 0u;
         return;
     }
-    if (b == tab_blocks) {                           // edge classes
+    if (mb >= 0) {                                   // edge classes
         uint64_t any = 0, all = ~0ull;
-        for (int64_t v = threadIdx.x; v < t.V; v += kBS) {
+        for (int64_t v = (int64_t)mb * kBS + threadIdx.x; v < t.V; v += (int64_t)mask_blocks * kBS) {
             const uint64_t m = t.on_src ? t.on_src[v] : ~0ull;
             if (t.on_dst != t.on_src) t.on_dst[v] = m;
             any |= m;
@@ -60,8 +62,8 @@ __global__ __launch_bounds__(kBS) void k_transforms(TransformIn t, ScaleEntry *_
                 any |= (uint64_t)red[0][k];
                 all &= (uint64_t)red[1][k];
             }
-            out->used_mask = any;
-            out->all_mask = all;
+            out->used[mb] = any;
+            out->all[mb] = all;
         }
         return;
     }
@@ -131,10 +133,20 @@ hipError_t transforms_device(const TransformIn &t, ScaleEntry *table, TransformO
     const int tab = (int)(nb < kTabBlocks ? nb : kTabBlocks);
     int64_t rmb = (t.rm_words + 4 * kBS - 1) / (4 * kBS);
     if (rmb > 512) rmb = 512;
-    k_transforms<<<(unsigned)(tab + 1 + rmb), kBS, 0, s>>>(t, table, tab, out_dev);
+    // one block folds 2,048 masks in the time the launch takes anyway, more
+    // share the rest (200,000 variants: 302 us a call with one block for all,
+    // 222 with a copy to the host and a loop there, 25 with these)
+    const int mask = (int)(t.V > 2048 * kMaskBlocks ? kMaskBlocks : (t.V + 2047) / 2048);
+    k_transforms<<<(unsigned)(tab + mask + rmb), kBS, 0, s>>>(t, table, tab, mask, out_dev);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
+    out->used_mask = 0;
+    out->all_mask = ~0ull;
+    for (int b = 0; b < mask; b++) {
+        out->used_mask |= out->used[b];
+        out->all_mask &= out->all[b];
+    }
     out->err = out->magic = 0;
     out->pmax = out->rmax_bits = 0;
     for (int b = 0; b < tab; b++) {
