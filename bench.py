@@ -332,7 +332,10 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": None if split else measured_traffic(args.config, g.n, vs.n_variants),
-                "kernel": "k_sim_phase" if split else "k_sim_pipe",
+                # (a plan of 1 is either kernel that owns one variant: k_sim_solo
+                # where it takes the handles)
+                "kernel": "k_sim_phase" if split else
+                          "k_sim_pipe" if all(b["plan"] > 1 for b in binfo) else "k_sim_solo or k_sim_pipe",
                 "algorithmic_bytes_per_launch": int(nbytes),
                 "avg_launch_ms": round(sim_ms / len(di.batches), 4),
                 "launches_per_step": len(di.batches),
