@@ -133,10 +133,8 @@ struct LoadWork {
 // kept, and the later passes index by the copies alone, whatever the caller
 // writes to the arrays meanwhile.
 template <class T>
-__device__ __forceinline__ T take(const T *src, T *dst, int64_t u) {
-    const T x = src[u];
+__device__ __forceinline__ void keep_own(const T *src, T *dst, int64_t u, T x) {
     if (dst != src) dst[u] = x;
-    return x;
 }
 
 // use(k, load(k)) for a task's edges, eight loads in flight where there are as
@@ -163,15 +161,29 @@ __global__ __launch_bounds__(kBS) void k_load_nodes(
     const int64_t *s_gap, const uint16_t *s_cls, const int64_t *s_ptr, int32_t *prev, int32_t *tid,
     int64_t *dur, int64_t *gap, uint16_t *cls, LoadWork w, bool one_head) {
     uint32_t e = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) w.out->ends[1] = take(s_ptr, w.in_ptr, n);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const int64_t end = s_ptr[n];
+        keep_own(s_ptr, w.in_ptr, n, end);
+        w.out->ends[1] = end;
+    }
     // sums split at bit 32 so that no partial sum can overflow
     int64_t dhi = 0, dlo = 0, ghi = 0, glo = 0, dm = 0, gm = 0, cm = 0;
     for (int64_t u = (int64_t)blockIdx.x * kBS + threadIdx.x; u < n;
          u += (int64_t)gridDim.x * kBS) {
-        const int32_t t = take(s_tid, tid, u);
+        // (all loads before the stores, which might alias them: one trip to
+        // memory, not one per field)
+        const int32_t t = s_tid[u], p = s_prev[u];
+        int64_t d = s_dur[u], g = s_gap[u];
+        const int64_t k0 = s_ptr[u], k1 = s_ptr[u + 1];
+        const uint16_t c16 = s_cls ? s_cls[u] : (uint16_t)0;
+        keep_own(s_tid, tid, u, t);
+        keep_own(s_prev, prev, u, p);
+        keep_own(s_dur, dur, u, d);
+        keep_own(s_gap, gap, u, g);
+        keep_own(s_ptr, w.in_ptr, u, k0);
+        keep_own(s_cls, cls, u, c16);
         const bool t_ok = t >= 0 && t < T;
         if (!t_ok) e |= ERR_THREAD_RANGE;
-        const int32_t p = take(s_prev, prev, u);
         if (p < -1 || p >= n || p == u) {
             e |= ERR_PREV_RANGE;
         } else if (p >= 0) {
@@ -179,17 +191,13 @@ __global__ __launch_bounds__(kBS) void k_load_nodes(
         } else if (t_ok && one_head) {
             if (atomicAdd(&w.heads[t], 1) != 0) e |= ERR_HEADS;
         }
-        int64_t d = take(s_dur, dur, u), g = take(s_gap, gap, u);
         if (d < 0 || g < 0) e |= ERR_NEG_TIME;
         if (d >= kTimeLimit || g >= kTimeLimit) e |= ERR_BIG_TIME;
         if (d < 0 || d >= kTimeLimit) d = 0;
         if (g < 0 || g >= kTimeLimit) g = 0;
-        const int64_t k0 = take(s_ptr, w.in_ptr, u);
         if (u == 0) w.out->ends[0] = k0;
-        if (s_ptr[u + 1] < k0) e |= ERR_PTR_ORDER;
-        int64_t c = 0;
-        if (s_cls) c = take(s_cls, cls, u);
-        else cls[u] = 0;
+        if (k1 < k0) e |= ERR_PTR_ORDER;
+        const int64_t c = c16;
         dhi += d >> 32; dlo += d & 0xffffffffll;
         ghi += g >> 32; glo += g & 0xffffffffll;
         dm = d > dm ? d : dm;
@@ -307,8 +315,8 @@ __global__ __launch_bounds__(kRankTile) void k_load_tiles(int32_t n, int32_t T, 
         each_edge(k0, listed ? k1 : k0,
                   [&](int64_t k) { return EdgeIn{s_src[k], 0, w.ecls ? s_ecls[k] : 0u}; },
                   [&](int64_t k, const EdgeIn &x) {
-                      if (s_src != w.in_src) w.in_src[k] = x.src;
-                      if (w.ecls && s_ecls != w.ecls) w.ecls[k] = (uint8_t)x.cls;
+                      keep_own(s_src, w.in_src, k, x.src);
+                      if (w.ecls) keep_own(s_ecls, w.ecls, k, (uint8_t)x.cls);
                       if (x.src < 0 || x.src >= n) er |= ERR_SRC_RANGE;
                       else if (x.src == u) er |= ERR_SELF_LOOP;
                       if (x.cls >= 64) er |= ERR_EDGE_CLS;
